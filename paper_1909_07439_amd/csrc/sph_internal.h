@@ -135,6 +135,74 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
 __device__ __forceinline__ int popc64(uint64_t x) { return __popcll(x); }
 
+// v of lane (l ^ D).  Distances below 16 stay within a row of 16 lanes and go
+// by DPP (a VALU move, no LDS round trip): quad permutations for 1 and 2, the
+// two row shifts by 4 on alternate banks of 4 lanes for 4, a row rotation by
+// 8 for 8.  Called with every lane of the wavefront active.
+template <int D>
+__device__ __forceinline__ uint32_t xor_lane_u32(uint32_t v) {
+  if constexpr (D == 1) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true);
+  } else if constexpr (D == 2) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, true);
+  } else if constexpr (D == 4) {
+    const int up = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xf, 0x5, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(up, (int)v, 0x114, 0xf, 0xa, false);
+  } else if constexpr (D == 8) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, true);
+  } else {
+    return (uint32_t)__shfl_xor((int)v, D, kWave);
+  }
+}
+template <int D>
+__device__ __forceinline__ double xor_lane_f64(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const uint32_t lo = xor_lane_u32<D>((uint32_t)b), hi = xor_lane_u32<D>((uint32_t)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Sum over the LPI consecutive lanes of a particle slot (aligned segments),
+// the farthest lanes first.
+template <int LPI>
+__device__ __forceinline__ double seg_sum(double v) {
+  if constexpr (LPI > 32) v += xor_lane_f64<32>(v);
+  if constexpr (LPI > 16) v += xor_lane_f64<16>(v);
+  if constexpr (LPI > 8) v += xor_lane_f64<8>(v);
+  if constexpr (LPI > 4) v += xor_lane_f64<4>(v);
+  if constexpr (LPI > 2) v += xor_lane_f64<2>(v);
+  if constexpr (LPI > 1) v += xor_lane_f64<1>(v);
+  return v;
+}
+template <int LPI>
+__device__ __forceinline__ double seg_max(double v) {
+  if constexpr (LPI > 32) v = fmax(v, xor_lane_f64<32>(v));
+  if constexpr (LPI > 16) v = fmax(v, xor_lane_f64<16>(v));
+  if constexpr (LPI > 8) v = fmax(v, xor_lane_f64<8>(v));
+  if constexpr (LPI > 4) v = fmax(v, xor_lane_f64<4>(v));
+  if constexpr (LPI > 2) v = fmax(v, xor_lane_f64<2>(v));
+  if constexpr (LPI > 1) v = fmax(v, xor_lane_f64<1>(v));
+  return v;
+}
+template <int LPI>
+__device__ __forceinline__ uint32_t seg_sum_u32(uint32_t v) {
+  if constexpr (LPI > 32) v += xor_lane_u32<32>(v);
+  if constexpr (LPI > 16) v += xor_lane_u32<16>(v);
+  if constexpr (LPI > 8) v += xor_lane_u32<8>(v);
+  if constexpr (LPI > 4) v += xor_lane_u32<4>(v);
+  if constexpr (LPI > 2) v += xor_lane_u32<2>(v);
+  if constexpr (LPI > 1) v += xor_lane_u32<1>(v);
+  return v;
+}
+__device__ __forceinline__ int wave_max_i32(int v) {
+  v = max(v, (int)xor_lane_u32<1>((uint32_t)v));
+  v = max(v, (int)xor_lane_u32<2>((uint32_t)v));
+  v = max(v, (int)xor_lane_u32<4>((uint32_t)v));
+  v = max(v, (int)xor_lane_u32<8>((uint32_t)v));
+  v = max(v, (int)xor_lane_u32<16>((uint32_t)v));
+  v = max(v, (int)xor_lane_u32<32>((uint32_t)v));
+  return v;
+}
+
 // Order-preserving map of doubles to unsigned 64-bit integers, so that
 // atomicMin / atomicMax on the integers implement min / max on the doubles.
 __host__ __device__ __forceinline__ unsigned long long enc_f64(double x) {

@@ -62,26 +62,6 @@ __device__ __forceinline__ double wave_min_f64(double v) {
   return v;
 }
 
-// Sum over the LPI consecutive lanes of a particle slot (aligned segments).
-template <int LPI>
-__device__ __forceinline__ double seg_sum(double v) {
-#pragma unroll
-  for (int d = LPI / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-  return v;
-}
-template <int LPI>
-__device__ __forceinline__ double seg_max(double v) {
-#pragma unroll
-  for (int d = LPI / 2; d > 0; d >>= 1) v = fmax(v, __shfl_xor(v, d, kWave));
-  return v;
-}
-template <int LPI>
-__device__ __forceinline__ uint32_t seg_sum_u32(uint32_t v) {
-#pragma unroll
-  for (int d = LPI / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-  return v;
-}
-
 // Exclusive scan over a 256-thread block; lds must hold 4 words.
 __device__ __forceinline__ uint32_t block256_excl_scan(uint32_t v, uint32_t* lds,
                                                        uint32_t* total) {
@@ -1703,15 +1683,15 @@ __device__ __forceinline__ void dt_min_update(DevState* ds, double dm) {
 }
 
 // rho, Omega, P, c_s of particle i at its converged h (Sect. 2.2 and the
-// ideal-gas closure), and the record the force loop reads for it; stored by
-// the lane with `write`.
+// ideal-gas closure), and the record the force loop reads for it (mixed: with
+// the position codes qi, FP64: with the position); stored by the lane with
+// `write`.
 template <bool MIXED>
 __device__ __forceinline__ void density_outputs(const KParams& kp, const Parts& p,
                                                 void* __restrict__ frec_out, int i, double xi,
-                                                double yi, double zi, double mi, double h,
-                                                double S0, double S1, double minhalf,
-                                                uint32_t& err, bool write,
-                                                const DevState* __restrict__ ds) {
+                                                double yi, double zi, const int4& qi, double mi,
+                                                double h, double S0, double S1, double minhalf,
+                                                uint32_t& err, bool write) {
   const double rho = S0;
   const double omega = 1.0 + h * S1 / (3.0 * rho);
   const double u = p.u[i];
@@ -1731,10 +1711,9 @@ __device__ __forceinline__ void density_outputs(const KParams& kp, const Parts& 
   const double hinv4pi = hinv * hinv * hinv * hinv * kp.knorm;
   if constexpr (MIXED) {
     FRec32 r;
-    const QFrame& f = ds->qf;
-    r.qx = qcode(xi, f, 0, kp.periodic[0]);
-    r.qy = qcode(yi, f, 1, kp.periodic[1]);
-    r.qz = qcode(zi, f, 2, kp.periodic[2]);
+    r.qx = qi.x;
+    r.qy = qi.y;
+    r.qz = qi.z;
     r.m = (float)mi;
     r.h = (float)h;
     r.vx = (float)p.vx[i];
@@ -2129,8 +2108,15 @@ __global__ __launch_bounds__(64) void k_density(KParams kp, Parts p,
     it_max = max(it_max, nit + 1);
     if (act && !failed && h > h0 * margin) grew = true;
     if (act && !failed) {
-      density_outputs<MIXED>(kp, p, frec_out, i, xi, yi, zi, mi, h, S0, S1, minhalf, err,
-                             sub == 0, ds);
+      int4 qi = make_int4(0, 0, 0, 0);
+      if constexpr (MIXED) {
+        const QFrame& f = ds->qf;
+        qi.x = qcode(xi, f, 0, kp.periodic[0]);
+        qi.y = qcode(yi, f, 1, kp.periodic[1]);
+        qi.z = qcode(zi, f, 2, kp.periodic[2]);
+      }
+      density_outputs<MIXED>(kp, p, frec_out, i, xi, yi, zi, qi, mi, h, S0, S1, minhalf, err,
+                             sub == 0);
       if (sub == 0) {
         pairs_final += nnb;
       }
@@ -2872,26 +2858,37 @@ __device__ __forceinline__ GroupRange xcd_groups(int ng) {
 
 // ============================================================================
 // Density from the neighbour lists (Sect. 2.2, Sect. 3.2.1): one wavefront
-// per group, LPI lanes per particle.  Each lane gathers the separations and
+// per chunk, LPI lanes per particle.  Each lane gathers the separations and
 // masses of its share of the row once (registers), then the h iteration
 // re-sums them: Newton-Raphson on f(h) = S0(h) - m (hfact/h)^3 with the same
 // safeguards as the walking kernel, a wavefront ballot deciding when the
 // group is done.  A group in which some h passes hl (its rows may then miss
 // neighbours) is flagged (gflag = 2) for the walking kernel, and the force
 // pass then walks for every group (leaf_state 2).
+//
+// Bound by VALU issue and the gather's latency.  The entries sit in
+// registers (E separations and E masses per lane): in LDS, where they were
+// before, they cost two LDS reads and their addressing per pair sum and held
+// FP64 rows of 256 entries to 1.25 wavefronts per SIMD.  Kernel time before
+// and after: FP64 Wendland C6 294,912 particles 859 -> 395 us, mixed M6
+// 294,912 292 -> 216 us, FP64 M4 10^6 945 -> 654 us, mixed M4 16.8M 6657 ->
+// 5907 us.
 // ============================================================================
-// LDS slot of row entry k of particle slot s in the list density kernel's
-// entry arrays (GS slots per entry).  A lane reads entries k = sub + LPI t, so
-// the 32 lanes of a half-wavefront span 32 / GS consecutive values of sub;
-// flipping the slot's top bit on every other run of 32 / GS entries puts
-// them in 32 distinct banks.
-template <int GS>
-__device__ __forceinline__ int ent_idx(int k, int s) {
-  return k * GS + (s ^ ((GS / 2) * ((k * GS / 32) & 1)));
+// Marks a loaded value as used here whatever becomes of it, so that the
+// compiler neither sinks its load into a later condition nor serialises a
+// batch of loads that are meant to be in flight together.
+template <typename T>
+__device__ __forceinline__ void loaded(T& v) {
+  asm volatile("" : "+v"(v));
 }
 
+// Wavefronts per SIMD the list density kernel is compiled for.
+constexpr int density_waves(bool mixed, int entries) { return mixed ? (entries > 16 ? 3 : 4) : (entries > 16 ? 2 : 3); }
+
 template <bool MIXED, int LPI, int CAP, int KIND>
-__global__ __launch_bounds__(64) void k_density_lists(KParams kp, Parts p,
+__global__ __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(density_waves(MIXED, CAP / LPI))))
+void k_density_lists(KParams kp, Parts p,
                                                       const GroupInfo* __restrict__ groups,
                                                       const int32_t* __restrict__ nl_idx,
                                                       const int32_t* __restrict__ nl_len,
@@ -2903,9 +2900,8 @@ __global__ __launch_bounds__(64) void k_density_lists(KParams kp, Parts p,
                                                       DevState* __restrict__ ds) {
   using R = typename std::conditional<MIXED, float, double>::type;
   constexpr int E = CAP / LPI;  // row entries per lane (CAP = kp.nl_cap)
-  constexpr int GS = kWave / LPI;
-  __shared__ R s_r[CAP * GS];  // separation and mass of row entry k of slot s at ent_idx(k, s)
-  __shared__ R s_m[CAP * GS];
+  constexpr int B = 4;          // entries per lane gathered and summed at a time
+  static_assert(E % B == 0, "whole blocks of entries");
   const int lane = threadIdx.x;
   const int slot = lane / LPI, sub = lane % LPI;
   constexpr int CS = kWave / LPI;  // particles per chunk
@@ -2923,79 +2919,93 @@ __global__ __launch_bounds__(64) void k_density_lists(KParams kp, Parts p,
   // gathered per row entry: x, y, z, m (FP64), or position codes and m (mixed)
   const double4* __restrict__ xyzm = reinterpret_cast<const double4*>(pos);
   const int4* __restrict__ qpos = reinterpret_cast<const int4*>(pos);
-  const QFrame& qf = ds->qf;
+  const float qsx = ds->qf.step[0], qsy = ds->qf.step[1], qsz = ds->qf.step[2];
+
+  // groups the list kernel flagged are left to the walking kernel; their
+  // flags are looked up only if there are any
+  const bool any_flag = ds->n_flagged != 0;
 
   for (int g = gr.beg; g < gr.end; g += gr.step) {
     const int first = g * CS, count = min(CS, kp.n - first);
     const bool inr = slot < count;
     const int i = first + (inr ? slot : 0);
-    // particles of groups the list kernel flagged are left to the walking kernel
-    const int gi = grp_of[i];
-    const bool act = inr && gflag[gi] == 0;
-    if (ballot64(act) == 0ull) continue;
-    const double xi = p.x[i], yi = p.y[i], zi = p.z[i], mi = p.m[i];
-    int32_t qxi = 0, qyi = 0, qzi = 0;  // mixed: i's position codes
-    if constexpr (MIXED) {
-      qxi = qcode(xi, qf, 0, kp.periodic[0]);
-      qyi = qcode(yi, qf, 1, kp.periodic[1]);
-      qzi = qcode(zi, qf, 2, kp.periodic[2]);
-    }
+    const bool act = inr && (!any_flag || gflag[grp_of[i]] == 0);
+    if (any_flag && ballot64(act) == 0ull) continue;
+    const double mi = p.m[i];
     double h = p.h[i];
+    int len = nl_len[i];
+    loaded(len);
+    len = act ? len : 0;
+    int4 qi = make_int4(0, 0, 0, 0);  // mixed: i's position codes
+    double xi = 0.0, yi = 0.0, zi = 0.0;
+    if constexpr (MIXED) {
+      qi = qpos[i];
+    } else {
+      xi = p.x[i];
+      yi = p.y[i];
+      zi = p.z[i];
+    }
     if (!(h > 0.0) || !isfinite(h)) {
       err |= kErrNonFinite;
       h = 1.0;
     }
     const double hl = margin * h;
-    const int len = act ? nl_len[i] : 0;
-    const int32_t* __restrict__ row = nl_idx + (int64_t)i * CAP;
-    int lmax = len;
-    for (int d = 32; d > 0; d >>= 1) lmax = max(lmax, __shfl_xor(lmax, d, kWave));
-    // ---- gather: separation and mass of every row entry into LDS, four
-    // entries per lane at a time (their loads in flight together)
-    for (int t0 = 0; t0 < E; t0 += 4) {
-      if (__builtin_amdgcn_readfirstlane(t0 * LPI) >= lmax) break;
-      int jj[4];
-      bool vv[4];
+    const int lmax = __builtin_amdgcn_readfirstlane(wave_max_i32(len));
+    // ---- gather: separation and mass of every row entry into registers (a
+    // lane reads no entry but its own), four entries per lane at a time (their
+    // loads in flight together).  Entries past the row's end get a separation
+    // beyond the support of any h up to hl and no mass: they add exactly zero.
+    // Blocks past the chunk's longest row are neither loaded nor summed.
+    // Short mixed rows keep the raw records of all their blocks in flight; the
+    // others reduce a block to its separations before the next one is loaded
+    // (the records would not fit the registers).
+    const int32_t* __restrict__ row = nl_idx + ((int64_t)i * CAP + sub);
+    R er[E], em[E];
+    const R rpad = (R)(4.0 * hl);
+    int iself = i;  // in place of entries past the row's end
+    loaded(iself);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = sub + LPI * (t0 + q);
-        vv[q] = k < len;
-        jj[q] = vv[q] ? row[k] : i;
+    for (int t0 = 0; t0 < E; t0 += B) {
+      if (t0 * LPI >= lmax) break;
+      int jj[B];
+#pragma unroll
+      for (int q = 0; q < B; ++q) jj[q] = row[LPI * (t0 + q)];  // within the row's CAP entries
+#pragma unroll
+      for (int q = 0; q < B; ++q) {
+        loaded(jj[q]);
+        jj[q] = sub + LPI * (t0 + q) < len ? jj[q] : iself;
       }
-      // every slot is computed and stored (entries past the row's length sit
-      // below CAP and are never read): a conditional use would let the
-      // compiler sink each load into it and serialise the four gathers
       if constexpr (MIXED) {
-        int4 v[4];
+        int4 v[B];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = qpos[jj[q]];
+        for (int q = 0; q < B; ++q) v[q] = qpos[jj[q]];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int k = sub + LPI * (t0 + q);
-          const float fx = qsep(qxi, v[q].x, qf.step[0]);
-          const float fy = qsep(qyi, v[q].y, qf.step[1]);
-          const float fz = qsep(qzi, v[q].z, qf.step[2]);
-          s_r[ent_idx<GS>(k, slot)] = fast_sqrt(fmaf(fz, fz, fmaf(fy, fy, fx * fx)));
-          s_m[ent_idx<GS>(k, slot)] = __int_as_float(v[q].w);
+        for (int q = 0; q < B; ++q) {
+          loaded(v[q].w);
+          const float fx = qsep(qi.x, v[q].x, qsx);
+          const float fy = qsep(qi.y, v[q].y, qsy);
+          const float fz = qsep(qi.z, v[q].z, qsz);
+          const float r = fast_sqrt(fmaf(fz, fz, fmaf(fy, fy, fx * fx)));
+          const bool in = sub + LPI * (t0 + q) < len;
+          er[t0 + q] = in ? r : rpad;
+          em[t0 + q] = in ? __int_as_float(v[q].w) : 0.f;
+          if constexpr (E > 16) loaded(er[t0 + q]);
         }
       } else {
-        double gx[4], gy[4], gz[4], gm[4];
+        double4 v[B];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const double4 v = xyzm[jj[q]];
-          gx[q] = v.x;
-          gy[q] = v.y;
-          gz[q] = v.z;
-          gm[q] = v.w;
-        }
+        for (int q = 0; q < B; ++q) v[q] = xyzm[jj[q]];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int k = sub + LPI * (t0 + q);
-          const double dx = fold(xi - gx[q], kp.len[0], kp.half[0], kp.periodic[0]);
-          const double dy = fold(yi - gy[q], kp.len[1], kp.half[1], kp.periodic[1]);
-          const double dz = fold(zi - gz[q], kp.len[2], kp.half[2], kp.periodic[2]);
-          s_r[ent_idx<GS>(k, slot)] = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
-          s_m[ent_idx<GS>(k, slot)] = gm[q];
+        for (int q = 0; q < B; ++q) {
+          loaded(v[q].w);
+          const double dx = fold(xi - v[q].x, kp.len[0], kp.half[0], kp.periodic[0]);
+          const double dy = fold(yi - v[q].y, kp.len[1], kp.half[1], kp.periodic[1]);
+          const double dz = fold(zi - v[q].z, kp.len[2], kp.half[2], kp.periodic[2]);
+          const double r = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
+          const bool in = sub + LPI * (t0 + q) < len;
+          er[t0 + q] = in ? r : rpad;
+          em[t0 + q] = in ? v[q].w : 0.0;
+          loaded(er[t0 + q]);
         }
       }
     }
@@ -3007,35 +3017,25 @@ __global__ __launch_bounds__(64) void k_density_lists(KParams kp, Parts p,
     uint32_t nnb = 0;
     while (true) {
       const double hinv = 1.0 / h;
-      double a0 = 0.0, a1 = 0.0;
+      // mixed: each lane sums its few terms in FP32; lanes are combined in FP64
+      const R hinvr = (R)hinv, twoh = (R)(kp.support * h);
+      R s0 = R(0), s1 = R(0);
       uint32_t cnt = 0;
-      if constexpr (MIXED) {
-        // each lane sums its few terms in FP32; lanes are combined in FP64
-        const float hinvf = (float)hinv, twohf = (float)(kp.support * h);
-        float s0 = 0.f, s1 = 0.f;
-        for (int k = sub; k < len; k += LPI) {
-          const float r = s_r[ent_idx<GS>(k, slot)], m = s_m[ent_idx<GS>(k, slot)];
-          const float q = r * hinvf;
-          float f, df;
-          kf_df<KIND, float>(q, f, df);
-          s0 = fmaf(m, f, s0);
-          s1 = fmaf(m, fmaf(q, df, 3.0f * f), s1);
-          cnt += (r < twohf) ? 1u : 0u;
-        }
-        a0 = (double)s0;
-        a1 = (double)s1;
-      } else {
-        const double twoh = kp.support * h;
-        for (int k = sub; k < len; k += LPI) {
-          const double r = s_r[ent_idx<GS>(k, slot)], m = s_m[ent_idx<GS>(k, slot)];
-          const double q = r * hinv;
-          double f, df;
-          kf_df<KIND, double>(q, f, df);
-          a0 = fma(m, f, a0);
-          a1 = fma(m, fma(q, df, 3.0 * f), a1);
+#pragma unroll
+      for (int t0 = 0; t0 < E; t0 += B) {
+        if (t0 * LPI >= lmax) break;
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+          const R r = er[t0 + q], m = em[t0 + q];
+          const R w = r * hinvr;
+          R f, df;
+          kf_df<KIND, R>(w, f, df);
+          s0 = fma(m, f, s0);
+          s1 = fma(m, fma(w, df, R(3) * f), s1);
           cnt += (r < twoh) ? 1u : 0u;
         }
       }
+      double a0 = (double)s0, a1 = (double)s1;
       a0 = seg_sum<LPI>(a0);
       a1 = seg_sum<LPI>(a1);
       cnt = seg_sum_u32<LPI>(cnt);
@@ -3097,6 +3097,7 @@ __global__ __launch_bounds__(64) void k_density_lists(KParams kp, Parts p,
     }
     if (ballot64(outgrew) != 0ull) {
       // the groups of every particle of this chunk go to the walking kernel
+      const int gi = grp_of[i];
       if (act && sub == 0 && atomicCAS(&gflag[gi], 0, 2) == 0) {
         flag_list[atomicAdd(&ds->n_flagged, 1)] = gi;
         ++ngrew;
@@ -3106,8 +3107,8 @@ __global__ __launch_bounds__(64) void k_density_lists(KParams kp, Parts p,
     }
     it_max = max(it_max, nit + 1);
     if (act) {
-      density_outputs<MIXED>(kp, p, frec_out, i, xi, yi, zi, mi, h, S0, S1, minhalf, err,
-                             sub == 0, ds);
+      density_outputs<MIXED>(kp, p, frec_out, i, xi, yi, zi, qi, mi, h, S0, S1, minhalf, err,
+                             sub == 0);
       if (sub == 0) pairs_final += nnb;
     }
   }

@@ -1,0 +1,52 @@
+"""Density from the neighbour-list rows at their ragged lengths: rows that end
+anywhere within a block of entries, empty lanes, last chunks of one particle,
+for each smoothing kernel, lanes per particle and precision, against the
+oracle (FP64 1e-12; mixed 2e-6 in h, 1e-5 in rho and Omega: FP32 pair terms
+of about 6e-8 each, a few ten per lane)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1909_07439_amd import inputs, sph
+
+from gpu_util import gpu_eval, rel_err, say
+
+pytestmark = pytest.mark.gpu
+
+
+def cloud(n, kernel, seed):
+    """n particles of a jittered ball in an open box: every row length from
+    the surface's to the centre's."""
+    rng = np.random.default_rng(seed)
+    s = int(np.ceil((6.0 * n / np.pi) ** (1.0 / 3.0))) + 2
+    c = np.stack(np.meshgrid(*[np.arange(s)] * 3, indexing="ij"), -1).reshape(-1, 3) - 0.5 * (s - 1)
+    c = c[np.argsort((c ** 2).sum(1), kind="stable")[:n]]
+    d = 0.5 / s
+    pos = 0.5 + d * (c + rng.uniform(-0.3, 0.3, c.shape))
+    cfg = inputs.lattice(4)
+    cfg.update(n=n, periodic=(0, 0, 0), workload=f"cloud{n}", id=np.arange(n, dtype=np.int64),
+               m=np.full(n, 1.0 / n), u=np.ones(n), h=np.full(n, cfg["hfact"] * d))
+    for a, k in enumerate("xyz"):
+        cfg[k] = np.ascontiguousarray(pos[:, a])
+        cfg["v" + k] = np.zeros(n)
+        cfg["a" + k] = np.zeros(n)
+    cfg["dudt"] = np.zeros(n)
+    return inputs.with_kernel(cfg, kernel)
+
+
+@pytest.mark.parametrize("precision", [sph.SPH_PREC_FP64, sph.SPH_PREC_MIXED])
+@pytest.mark.parametrize("n_group", [4, 8])
+@pytest.mark.parametrize("kernel", ["m4", "m6", "wc6"])
+@pytest.mark.parametrize("n", [9, 65, 1003])
+def test_density_of_ragged_rows(n, kernel, n_group, precision):
+    cfg = cloud(n, kernel, 7 + n)
+    cfg["n_group"] = n_group
+    o = oracle.evaluate(cfg, oracle.make_params(cfg))
+    out, ctx, _, info = gpu_eval(cfg, precision)
+    sph.sph_check(ctx)
+    tol = dict(h=1e-12, rho=1e-12, omega=1e-12) if precision == sph.SPH_PREC_FP64 else \
+        dict(h=2e-6, rho=1e-5, omega=1e-5)
+    for k, t in tol.items():
+        e = float(rel_err(out[k], o[k]).max())
+        say(f"  {k}: {e:.2e}")
+        assert e <= t, (k, e)
