@@ -136,6 +136,13 @@ sph_status sync_state(sph_ctx* c, bool clear_err) {
   return status_of_err(c, e);
 }
 
+// The Courant step of the last force pass: the smallest of the tallies' minima.
+double courant_dt(const sph::DevState& s) {
+  unsigned long long e = sph::enc_f64(__builtin_huge_val());
+  for (const sph::WaveTally& t : s.tally) e = std::min(e, t.dt_min_enc);
+  return sph::dec_f64(e);
+}
+
 template <typename T>
 hipError_t dalloc(T** p, size_t count) {
   return hipMalloc((void**)p, sizeof(T) * (count ? count : 1));
@@ -299,7 +306,7 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   e = hipHostMalloc((void**)&c->hs, sizeof(sph::DevState), hipHostMallocDefault);
   if (e != hipSuccess) return bail(e, "hipHostMalloc");
   memset(c->hs, 0, sizeof(sph::DevState));
-  c->hs->dt_min_enc = sph::enc_f64(__builtin_huge_val());
+  for (sph::WaveTally& t : c->hs->tally) t.dt_min_enc = sph::enc_f64(__builtin_huge_val());
   e = hipMemcpyAsync(c->ds, c->hs, sizeof(sph::DevState), hipMemcpyHostToDevice, c->stream);
   if (e != hipSuccess) return bail(e, "init state");
   e = hipStreamSynchronize(c->stream);
@@ -448,7 +455,11 @@ sph_status sph_density(sph_ctx* c, sph_particles* p, int32_t* iters_out) {
   if (st != SPH_OK) return st;
   if (iters_out) {
     st = sync_state(c, true);
-    *iters_out = c->hs->max_iter;
+    {
+      int32_t most = 0;
+      for (const sph::WaveTally& t : c->hs->tally) most = std::max(most, t.max_iter);
+      *iters_out = most;
+    }
     return st;
   }
   return SPH_OK;
@@ -465,7 +476,7 @@ sph_status sph_force(sph_ctx* c, sph_particles* p, double* dt_next_out) {
   if (st != SPH_OK) return st;
   if (dt_next_out) {
     st = sync_state(c, true);
-    *dt_next_out = sph::dec_f64(c->hs->dt_min_enc);
+    *dt_next_out = courant_dt(*c->hs);
     return st;
   }
   return SPH_OK;
@@ -497,7 +508,7 @@ sph_status sph_step(sph_ctx* c, sph_particles* p, double dt, double* dt_next_out
   ph_end(c, kPhStep);
   if (dt_next_out) {
     st = sync_state(c, true);
-    *dt_next_out = sph::dec_f64(c->hs->dt_min_enc);
+    *dt_next_out = courant_dt(*c->hs);
     return st;
   }
   return SPH_OK;
@@ -814,23 +825,26 @@ sph_status sph_stats(sph_ctx* c, int64_t out[18]) {
   HIPCHK(c, hipMemcpyAsync(c->hs, c->ds, sizeof(sph::DevState), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   const sph::DevState& s = *c->hs;
+  for (int k = 0; k < 18; ++k) out[k] = 0;
   out[0] = s.n_nodes;
   out[1] = s.n_groups;
-  out[2] = s.max_iter;
-  out[3] = (int64_t)s.n_pairs_density;
-  out[4] = (int64_t)s.n_pairs_force;
-  out[5] = (int64_t)s.n_sums_density;
-  out[6] = (int64_t)s.n_cand_density;
-  out[7] = (int64_t)s.n_cand_force;
-  out[8] = s.n_rewalk;
+  for (const sph::WaveTally& t : s.tally) {
+    out[2] = std::max<int64_t>(out[2], t.max_iter);
+    out[3] += (int64_t)t.n_pairs_density;
+    out[4] += (int64_t)t.n_pairs_force;
+    out[5] += (int64_t)t.n_sums_density;
+    out[6] += (int64_t)t.n_cand_density;
+    out[7] += (int64_t)t.n_cand_force;
+    out[8] += t.n_rewalk;
+    out[10] += (int64_t)t.tot_sums_density;
+    out[11] += (int64_t)t.tot_pairs_force;
+    out[16] += (int64_t)t.tot_cand_lists;
+  }
   out[9] = s.err;
-  out[10] = (int64_t)s.tot_sums_density;
-  out[11] = (int64_t)s.tot_pairs_force;
   out[12] = c->density_launches;
   out[13] = c->force_launches;
   out[14] = s.n_flag_rows;
   out[15] = s.n_flag_grew;
-  out[16] = (int64_t)s.tot_cand_lists;
   out[17] = c->lists_launches;
   return SPH_OK;
 }

@@ -52,10 +52,30 @@ __device__ __forceinline__ float qsep(int32_t a, int32_t b, float step) {
   return (float)(int32_t)((uint32_t)a - (uint32_t)b) * step;
 }
 
+// Work counts and the Courant minimum, which every wavefront of the list and
+// walk kernels adds to once, when it ends.  On small and mid-sized sets all of
+// them end together, and their atomics on one set of counters queued up: 13 to
+// 37 us of every such kernel (32^3 FP64: lists 86 -> 65 us, density 62 -> 26,
+// force 75 -> 49 with the counts spread; 294,912 mixed: 193 -> 176, 111 -> 98,
+// 161 -> 132).  So there are kTallies sets, 128 bytes apart; a block adds to
+// set blockIdx mod kTallies (all blocks of a set run on one XCD), and the
+// readers combine them.
+constexpr int kTallies = 64;
+struct alignas(128) WaveTally {
+  unsigned long long n_pairs_density;   // true neighbours (r < 2h) at the final pass
+  unsigned long long n_pairs_force;     // force pairs
+  unsigned long long n_sums_density;    // sum over groups of (density passes * pairs)
+  unsigned long long n_cand_density;    // candidate tests in the density walks
+  unsigned long long n_cand_force;      // candidate tests in the force walks
+  unsigned long long tot_sums_density;  // n_sums_density over every launch so far
+  unsigned long long tot_pairs_force;   // n_pairs_force over every launch so far
+  unsigned long long tot_cand_lists;    // candidate tests of the list kernel so far
+  unsigned long long dt_min_enc;        // ordered encoding of min_i c_cour h_i / vsig_i
+  int32_t max_iter;                     // most density sums any group needed
+  int32_t n_rewalk;
+};
+
 // Device-resident scalars of one context.
-// Every wavefront of the walk kernels adds its counts once; the counters
-// that all of them update sit 256 bytes apart (separate cache lines and L2
-// channels), so those atomics do not queue behind each other.
 struct DevState {
   int32_t n_nodes;
   int32_t n_groups;
@@ -67,18 +87,8 @@ struct DevState {
   int32_t pad1;
   double dt_cur;          // step used by the running sph_step
   alignas(256) uint32_t err;
-  alignas(256) int32_t max_iter;                  // most density sums any group needed
-  alignas(256) unsigned long long dt_min_enc;     // ordered encoding of min_i c_cour h_i / vsig_i
-  alignas(256) unsigned long long n_pairs_density;  // true neighbours (r < 2h) at the final pass
-  alignas(256) unsigned long long n_pairs_force;    // force pairs
-  alignas(256) unsigned long long n_sums_density;   // sum over groups of (density passes * pairs)
-  alignas(256) unsigned long long n_cand_density;   // candidate tests in the density walks
-  alignas(256) unsigned long long n_cand_force;     // candidate tests in the force walks
-  alignas(256) int32_t n_rewalk;
-  alignas(256) unsigned long long tot_sums_density;  // n_sums_density over every launch so far
-  alignas(256) unsigned long long tot_pairs_force;   // n_pairs_force over every launch so far
-  alignas(256) unsigned long long tot_cand_lists;    // candidate tests of the list kernel so far
   alignas(256) QFrame qf;  // frame of the mixed force records (set with each tree's node boxes)
+  WaveTally tally[kTallies];
 };
 
 // Walk view of a tree node: centre, conservative half-widths, largest h.

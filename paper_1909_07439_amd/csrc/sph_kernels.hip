@@ -1673,13 +1673,18 @@ constexpr float kBorder = 4e-5f;
 // and stores the group's leaf list, so that the force pass can replay it.
 // ============================================================================
 
-// Global Courant minimum: the atomic is skipped when the stored value is
+// This block's set of counters.
+__device__ __forceinline__ WaveTally& my_tally(DevState* ds) {
+  return ds->tally[blockIdx.x % kTallies];
+}
+
+// Courant minimum of a tally: the atomic is skipped when the stored value is
 // already smaller (most wavefronts once the first ones have finished).
-__device__ __forceinline__ void dt_min_update(DevState* ds, double dm) {
+__device__ __forceinline__ void dt_min_update(WaveTally& t, double dm) {
   const unsigned long long e = enc_f64(dm);
   const unsigned long long cur =
-      __hip_atomic_load(&ds->dt_min_enc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (e < cur) atomicMin(&ds->dt_min_enc, e);
+      __hip_atomic_load(&t.dt_min_enc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (e < cur) atomicMin(&t.dt_min_enc, e);
 }
 
 // rho, Omega, P, c_s of particle i at its converged h (Sect. 2.2 and the
@@ -2137,13 +2142,14 @@ __global__ __launch_bounds__(64) void k_density(KParams kp, Parts p,
   }
   sums = sm;
   if (lane == 0) {
+    WaveTally& tally = my_tally(ds);
     if (b) atomicOr(&ds->err, eall);
-    if (it_max > 0) atomicMax(&ds->max_iter, it_max);
-    if (pf) atomicAdd(&ds->n_pairs_density, pf);
-    if (sums) atomicAdd(&ds->n_sums_density, sums);
-    if (sums && !fb) atomicAdd(&ds->tot_sums_density, sums);
-    if (cd) atomicAdd(&ds->n_cand_density, cd);
-    if (walks) atomicAdd(&ds->n_rewalk, walks);
+    if (it_max > 0) atomicMax(&tally.max_iter, it_max);
+    if (pf) atomicAdd(&tally.n_pairs_density, pf);
+    if (sums) atomicAdd(&tally.n_sums_density, sums);
+    if (sums && !fb) atomicAdd(&tally.tot_sums_density, sums);
+    if (cd) atomicAdd(&tally.n_cand_density, cd);
+    if (walks) atomicAdd(&tally.n_rewalk, walks);
     if (ballot_any) atomicMax(&ds->leaf_state, 2);
   }
 }
@@ -2404,11 +2410,12 @@ __global__ __launch_bounds__(64) void k_force(KParams kp, Parts p,
   }
   const double dm = wave_min_f64(dtmin);
   if (lane == 0) {
+    WaveTally& tally = my_tally(ds);
     if (b) atomicOr(&ds->err, eall);
-    if (pf) atomicAdd(&ds->n_pairs_force, pf);
-    if (pf && flag_list == nullptr) atomicAdd(&ds->tot_pairs_force, pf);
-    if (cd) atomicAdd(&ds->n_cand_force, cd);
-    if (dm < SPH_INF) dt_min_update(ds, dm);
+    if (pf) atomicAdd(&tally.n_pairs_force, pf);
+    if (pf && flag_list == nullptr) atomicAdd(&tally.tot_pairs_force, pf);
+    if (cd) atomicAdd(&tally.n_cand_force, cd);
+    if (dm < SPH_INF) dt_min_update(tally, dm);
   }
 }
 
@@ -2834,9 +2841,10 @@ void k_lists(KParams kp, Parts p, const WalkNode* __restrict__ nodes,
   unsigned long long cd = cands;
   for (int d = 32; d > 0; d >>= 1) cd += __shfl_xor(cd, d, kWave);
   if (lane == 0) {
-    if (cd) atomicAdd(&ds->n_cand_density, cd);
-    if (cd) atomicAdd(&ds->tot_cand_lists, cd);
-    if (walks) atomicAdd(&ds->n_rewalk, walks);
+    WaveTally& tally = my_tally(ds);
+    if (cd) atomicAdd(&tally.n_cand_density, cd);
+    if (cd) atomicAdd(&tally.tot_cand_lists, cd);
+    if (walks) atomicAdd(&tally.n_rewalk, walks);
     if (flagged) {
       atomicOr(&ds->lists_missing, 1);
       atomicAdd(&ds->n_flag_rows, nflag);
@@ -3123,11 +3131,12 @@ void k_density_lists(KParams kp, Parts p,
   }
   outgrew_any = ballot64(outgrew_any) != 0ull;
   if (lane == 0) {
+    WaveTally& tally = my_tally(ds);
     if (b) atomicOr(&ds->err, eall);
-    if (it_max > 0) atomicMax(&ds->max_iter, it_max);
-    if (pf) atomicAdd(&ds->n_pairs_density, pf);
-    if (sm) atomicAdd(&ds->n_sums_density, sm);
-    if (sm) atomicAdd(&ds->tot_sums_density, sm);
+    if (it_max > 0) atomicMax(&tally.max_iter, it_max);
+    if (pf) atomicAdd(&tally.n_pairs_density, pf);
+    if (sm) atomicAdd(&tally.n_sums_density, sm);
+    if (sm) atomicAdd(&tally.tot_sums_density, sm);
     if (outgrew_any) {
       atomicMax(&ds->leaf_state, 2);
       atomicOr(&ds->lists_missing, 1);
@@ -3338,11 +3347,12 @@ void k_force_lists(KParams kp, Parts p,
   }
   const double dm = wave_min_f64(dtmin);
   if (lane == 0) {
+    WaveTally& tally = my_tally(ds);
     if (b) atomicOr(&ds->err, eall);
-    if (pf) atomicAdd(&ds->n_pairs_force, pf);
-    if (pf) atomicAdd(&ds->tot_pairs_force, pf);
-    if (cd) atomicAdd(&ds->n_cand_force, cd);
-    if (dm < SPH_INF) dt_min_update(ds, dm);
+    if (pf) atomicAdd(&tally.n_pairs_force, pf);
+    if (pf) atomicAdd(&tally.tot_pairs_force, pf);
+    if (cd) atomicAdd(&tally.n_cand_force, cd);
+    if (dm < SPH_INF) dt_min_update(tally, dm);
   }
 }
 
@@ -3475,38 +3485,43 @@ __global__ void k_set_leaf_state(DevState* ds, int v) {
   }
 }
 
+// The tallies, one per lane of the one wavefront that the next kernels run in.
+static_assert(kTallies == kWave, "one lane per tally");
+
 __global__ void k_reset_force_state(DevState* ds) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) ds->dt_min_enc = enc_f64(SPH_INF);
+  ds->tally[threadIdx.x].dt_min_enc = enc_f64(SPH_INF);
 }
 
 __device__ __forceinline__ void clear_counters(DevState* ds) {
-  ds->max_iter = 0;
-  ds->n_pairs_density = 0;
-  ds->n_pairs_force = 0;
-  ds->n_sums_density = 0;
-  ds->n_cand_density = 0;
-  ds->n_cand_force = 0;
-  ds->n_rewalk = 0;
-  ds->leaf_state = 0;
-  ds->lists_missing = 0;
-  ds->n_flag_rows = 0;
-  ds->n_flag_grew = 0;
-  ds->n_flagged = 0;
+  WaveTally& t = ds->tally[threadIdx.x];
+  t.max_iter = 0;
+  t.n_pairs_density = 0;
+  t.n_pairs_force = 0;
+  t.n_sums_density = 0;
+  t.n_cand_density = 0;
+  t.n_cand_force = 0;
+  t.n_rewalk = 0;
+  if (threadIdx.x == 0) {
+    ds->leaf_state = 0;
+    ds->lists_missing = 0;
+    ds->n_flag_rows = 0;
+    ds->n_flag_grew = 0;
+    ds->n_flagged = 0;
+  }
 }
 
-__global__ void k_reset_counters(DevState* ds) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) clear_counters(ds);
-}
+__global__ void k_reset_counters(DevState* ds) { clear_counters(ds); }
 
 // Start of a step: counters cleared; the step's dt (the host's, or the
 // previous force pass's Courant minimum) taken before that minimum is reset
 // for this step's force pass; neighbour lists wanted (leaf_state 1: the tree
 // kernels before the density do not read it).
 __global__ void k_step_begin(DevState* ds, double dt_host) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    ds->dt_cur = (dt_host > 0.0) ? dt_host : dec_f64(ds->dt_min_enc);
-    ds->dt_min_enc = enc_f64(SPH_INF);
-    clear_counters(ds);
+  const double dt = wave_min_f64(dec_f64(ds->tally[threadIdx.x].dt_min_enc));
+  ds->tally[threadIdx.x].dt_min_enc = enc_f64(SPH_INF);
+  clear_counters(ds);
+  if (threadIdx.x == 0) {
+    ds->dt_cur = (dt_host > 0.0) ? dt_host : dt;
     ds->leaf_state = 1;
   }
 }
