@@ -234,8 +234,9 @@ sph_status sph_list_pairs(sph_ctx* ctx, const sph_particles* p, int32_t mode, in
                           int32_t* idx, int64_t cap);
 
 /* Mean duration of the launches of each phase since the previous call, in
-   milliseconds, from HIP events recorded on the library stream around each
-   phase (at most 1024 launches per phase are kept): out[0..11] = {keys+sort,
+   milliseconds, from HIP events that the last kernel before and the last
+   kernel of each phase stamp when they complete (so a phase holds the gap
+   before its first kernel; at most 1024 launches per phase are kept): out[0..11] = {keys+sort,
    permute, tree, density, force, integrate, total step, neighbour lists,
    density of flagged groups, force of flagged groups, adjoint kernels of
    sph_eval_adjoint / sph_step_adjoint, the force-adjoint kernel alone}.
@@ -247,9 +248,10 @@ sph_status sph_timings(sph_ctx* ctx, double out[12]);
 /* Which calls record the phase events of sph_timings: sph_step records them
    on one call in `every` (the first after this call, then every every-th),
    0 records none; every other entry point records them whenever every > 0.
-   The default is 1 (every call).  Each recorded phase boundary leaves the
-   GPU idle for a few microseconds, so a throughput run samples (e.g. every =
-   8) and sph_timings averages over the sampled launches.  Returns SPH_E_ARG
+   The default is 1 (every call).  A stamp costs a fraction of a microsecond
+   per phase; a throughput run may still sample (e.g. every = 8), and
+   sph_timings averages over the sampled launches.  While the stream is being
+   captured nothing is recorded.  Returns SPH_E_ARG
    for every < 0.  Host-only; no GPU work. */
 sph_status sph_set_timing(sph_ctx* ctx, int32_t every);
 

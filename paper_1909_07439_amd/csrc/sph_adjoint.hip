@@ -578,28 +578,24 @@ hipError_t launch_adjoint(sph_ctx* c, const sph_particles* s, const sph_cotangen
   if (part == 0) {
     const int sblocks = (int)std::min<int64_t>((n + 255) / 256, 8 * (int64_t)c->n_cu);
     if (mixed)
-      hipLaunchKernelGGL(k_adj_seed<true>, dim3(sblocks), dim3(256), 0, c->stream, n, p.id, g,
-                         0.5 * dt, step_mode ? 1 : 0, c->adj_abar, &c->ds->err);
+      launch_last(c, k_adj_seed<true>, dim3(sblocks), dim3(256), n, p.id, g, 0.5 * dt,
+                  step_mode ? 1 : 0, c->adj_abar, &c->ds->err);
     else
-      hipLaunchKernelGGL(k_adj_seed<false>, dim3(sblocks), dim3(256), 0, c->stream, n, p.id, g,
-                         0.5 * dt, step_mode ? 1 : 0, c->adj_abar, &c->ds->err);
+      launch_last(c, k_adj_seed<false>, dim3(sblocks), dim3(256), n, p.id, g, 0.5 * dt,
+                  step_mode ? 1 : 0, c->adj_abar, &c->ds->err);
   } else if (part == 1) {
     if (mixed)
-      hipLaunchKernelGGL((k_adj_force<true, LPI>), grid, block, 0, c->stream, c->kp, p, c->frec,
-                         c->adj_abar, c->nl_idx, c->nl_len, c->adj_raw, ns, c->adj_ab,
-                         &c->ds->qf);
+      launch_last(c, k_adj_force<true, LPI>, grid, block, c->kp, p, c->frec, c->adj_abar,
+                  c->nl_idx, c->nl_len, c->adj_raw, ns, c->adj_ab, &c->ds->qf);
     else
-      hipLaunchKernelGGL((k_adj_force<false, LPI>), grid, block, 0, c->stream, c->kp, p, c->frec,
-                         c->adj_abar, c->nl_idx, c->nl_len, c->adj_raw, ns, c->adj_ab,
-                         &c->ds->qf);
+      launch_last(c, k_adj_force<false, LPI>, grid, block, c->kp, p, c->frec, c->adj_abar,
+                  c->nl_idx, c->nl_len, c->adj_raw, ns, c->adj_ab, &c->ds->qf);
   } else if (mixed) {
-    hipLaunchKernelGGL((k_adj_dens2<true, LPI>), dgrid, block, 0, c->stream, c->kp, p, c->frec,
-                       c->nl_idx, c->nl_len, c->adj_raw, ns, c->adj_ab, g, dt,
-                       step_mode ? 1 : 0, &c->ds->qf);
+    launch_last(c, k_adj_dens2<true, LPI>, dgrid, block, c->kp, p, c->frec, c->nl_idx, c->nl_len,
+                c->adj_raw, ns, c->adj_ab, g, dt, step_mode ? 1 : 0, &c->ds->qf);
   } else {
-    hipLaunchKernelGGL((k_adj_dens2<false, LPI>), dgrid, block, 0, c->stream, c->kp, p, c->frec,
-                       c->nl_idx, c->nl_len, c->adj_raw, ns, c->adj_ab, g, dt,
-                       step_mode ? 1 : 0, &c->ds->qf);
+    launch_last(c, k_adj_dens2<false, LPI>, dgrid, block, c->kp, p, c->frec, c->nl_idx, c->nl_len,
+                c->adj_raw, ns, c->adj_ab, g, dt, step_mode ? 1 : 0, &c->ds->qf);
   }
   return hipGetLastError();
 }

@@ -1,6 +1,8 @@
 // sph_ctx.h -- the library context: run parameters, device scratch, events.
 #pragma once
 
+#include <hip/hip_ext.h>
+
 #include <string>
 
 #include "sph_internal.h"
@@ -106,7 +108,8 @@ struct sph_ctx {
   double* red_out = nullptr;   // 12 results
   sph::DevState* ds = nullptr;
   sph::DevState* hs = nullptr;  // pinned host mirror
-  struct sph_timing* tm = nullptr;  // phase event rings (host code)
+  struct sph_timing* tm = nullptr;  // phase events (host code)
+  hipEvent_t mark = nullptr;  // event that the running phase's last kernel stamps (launch_last)
   bool timing = true;      // record phase events for the current call
   int timing_every = 1;    // sph_step records them on one call in this many (0: never)
   int64_t step_calls = 0;  // sph_step calls since sph_set_timing
@@ -116,3 +119,21 @@ struct sph_ctx {
   int64_t lists_launches = 0;    // launches of the neighbour-list kernel so far
   std::string err;
 };
+
+namespace sph {
+// Launch of a phase's last kernel on the library stream: its completion stamps
+// the event the host set for the phase's end, if any.  The stamp rides on the
+// kernel's own completion (0.2 us per kernel); an event recorded behind the
+// kernel is a packet of its own, and a pair of them around every phase idled
+// the GPU for 8 us per phase.
+template <typename... F, typename... A>
+inline void launch_last(sph_ctx* c, void (*kernel)(F...), dim3 grid, dim3 block, A... args) {
+  if (hipEvent_t e = c->mark) {
+    c->mark = nullptr;
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, c->stream, nullptr, e, 0,
+                          static_cast<F>(args)...);
+  } else {
+    hipLaunchKernelGGL(kernel, grid, block, 0, c->stream, static_cast<F>(args)...);
+  }
+}
+}  // namespace sph

@@ -21,7 +21,8 @@ hipError_t launch_leaf_state(sph_ctx* c, int v);
 
 namespace {
 
-constexpr int kRing = 1024;  // timed launches kept per phase
+constexpr int kRing = 1024;        // timed launches kept per phase
+constexpr int kPool = 15 * kRing;  // phase boundaries kept, over all phases
 enum Phase {
   kPhSort = 0,
   kPhPermute,
@@ -40,10 +41,14 @@ enum Phase {
 
 }  // namespace
 
-// Event rings of the phase timings, owned by the context.
+// Events of the phase boundaries, owned by the context.  A boundary's event is
+// stamped by the last kernel before it (launch_last); a phase is the pair of
+// boundaries around it, so consecutive phases share one.
 struct sph_timing {
-  hipEvent_t start[kNPh][kRing];
-  hipEvent_t stop[kNPh][kRing];
+  hipEvent_t ev[kPool];
+  int used = 0;            // events taken since sph_timings
+  int last = -1;           // the latest boundary of the running call (-1: none)
+  int span[kNPh][kRing][2];  // first and last boundary of each timed launch
   int count[kNPh];
   bool ready = false;
 };
@@ -72,20 +77,58 @@ sph_status hip_fail(sph_ctx* c, hipError_t e, const char* where) {
     if (e_ != hipSuccess) return hip_fail((c), e_, #call); \
   } while (0)
 
-void ph_begin(sph_ctx* c, int ph) {
+// Phase boundaries.  timing_begin opens a call: no boundary yet, and none at
+// all while the stream is being captured (a captured event holds no time).
+void timing_begin(sph_ctx* c) {
   sph_timing* x = c->tm;
-  if (!x || !x->ready || !c->timing) return;
-  const int k = x->count[ph];
-  if (k < kRing) (void)hipEventRecord(x->start[ph][k], c->stream);
-}
-void ph_end(sph_ctx* c, int ph) {
-  sph_timing* x = c->tm;
-  if (!x || !x->ready || !c->timing) return;
-  const int k = x->count[ph];
-  if (k < kRing) {
-    (void)hipEventRecord(x->stop[ph][k], c->stream);
-    x->count[ph] = k + 1;
+  c->mark = nullptr;
+  if (!x || !x->ready) {
+    c->timing = false;
+    return;
   }
+  x->last = -1;
+  if (!c->timing) return;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    c->timing = false;
+  }
+}
+// The next event of the pool as the latest boundary; -1 if there is none.
+int next_boundary(sph_ctx* c) {
+  sph_timing* x = c->tm;
+  if (!c->timing || x->used >= kPool) return x ? (x->last = -1) : -1;
+  return x->last = x->used++;
+}
+// The last kernel of the next launcher call stamps a boundary.
+void ph_mark(sph_ctx* c) {
+  const int k = next_boundary(c);
+  c->mark = k >= 0 ? c->tm->ev[k] : nullptr;
+}
+// A boundary of its own on the stream, where no kernel precedes the phase.
+void ph_record(sph_ctx* c) {
+  const int k = next_boundary(c);
+  if (k >= 0) (void)hipEventRecord(c->tm->ev[k], c->stream);
+}
+// Phase `ph` runs from boundary `from` to the latest one.
+void ph_span(sph_ctx* c, int ph, int from) {
+  sph_timing* x = c->tm;
+  if (!c->timing || from < 0 || x->last < 0 || x->count[ph] >= kRing) return;
+  int* sp = x->span[ph][x->count[ph]++];
+  sp[0] = from;
+  sp[1] = x->last;
+}
+int ph_last(const sph_ctx* c) { return c->timing ? c->tm->last : -1; }
+
+// Runs one launcher as phase `ph`, from the latest boundary to one that its
+// last kernel stamps.
+template <typename Fn>
+hipError_t ph_run(sph_ctx* c, int ph, Fn fn) {
+  const int from = ph_last(c);
+  ph_mark(c);
+  const hipError_t e = fn();
+  ph_span(c, ph, from);
+  return e;
 }
 
 sph_status check_parts(sph_ctx* c, const sph_particles* p, bool need_state_out,
@@ -142,6 +185,17 @@ double courant_dt(const sph::DevState& s) {
   for (const sph::WaveTally& t : s.tally) e = std::min(e, t.dt_min_enc);
   return sph::dec_f64(e);
 }
+
+// Phase events of one call, as asked for; afterwards the context's default
+// (every entry point but sph_step records while they are on at all).
+struct TimingScope {
+  sph_ctx* c;
+  TimingScope(sph_ctx* ctx, bool on) : c(ctx) {
+    c->timing = on;
+    timing_begin(c);
+  }
+  ~TimingScope() { c->mark = nullptr; }
+};
 
 template <typename T>
 hipError_t dalloc(T** p, size_t count) {
@@ -320,17 +374,12 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   }
   c->tm = x;
   bool ok = true;
-  // timing-only events: no system-scope fence when one is recorded (the
-  // cache write-back and invalidation would idle the GPU for microseconds at
-  // every phase boundary); sph_timings reads them after a stream synchronise
-  const unsigned evf = hipEventDisableSystemFence;
-  for (int ph = 0; ph < kNPh && ok; ++ph) {
-    x->count[ph] = 0;
-    for (int r = 0; r < kRing && ok; ++r) {
-      ok = hipEventCreateWithFlags(&x->start[ph][r], evf) == hipSuccess &&
-           hipEventCreateWithFlags(&x->stop[ph][r], evf) == hipSuccess;
-    }
-  }
+  // timing-only events: no system-scope fence (the cache write-back and
+  // invalidation would idle the GPU for microseconds at every phase boundary);
+  // sph_timings reads them after a stream synchronise
+  for (int ph = 0; ph < kNPh; ++ph) x->count[ph] = 0;
+  for (int k = 0; k < kPool && ok; ++k)
+    ok = hipEventCreateWithFlags(&x->ev[k], hipEventDisableSystemFence) == hipSuccess;
   x->ready = ok;
   g_create_err.clear();
   *out = c;
@@ -342,11 +391,8 @@ void sph_destroy(sph_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   if (sph_timing* x = c->tm) {
     // events that were created are destroyed; a failed creation left the rest null
-    for (int ph = 0; ph < kNPh; ++ph)
-      for (int r = 0; r < kRing; ++r) {
-        if (x->start[ph][r]) (void)hipEventDestroy(x->start[ph][r]);
-        if (x->stop[ph][r]) (void)hipEventDestroy(x->stop[ph][r]);
-      }
+    for (hipEvent_t e : x->ev)
+      if (e) (void)hipEventDestroy(e);
     delete x;
     c->tm = nullptr;
   }
@@ -367,21 +413,20 @@ void sph_destroy(sph_ctx* c) {
   delete c;
 }
 
+// After a launch that stamped a phase boundary (counters cleared).
 static sph_status do_build(sph_ctx* c, sph_particles* p, bool outputs_too, bool predict) {
   c->n = (int32_t)p->n;
   c->kp.n = c->n;
   c->densities_on_tree = 0;
-  ph_begin(c, kPhSort);
-  HIPCHK(c, sph::launch_predict_keys(c, p, predict, 0.0));
-  HIPCHK(c, sph::launch_sort(c));
-  ph_end(c, kPhSort);
-  ph_begin(c, kPhPermute);
-  HIPCHK(c, sph::launch_permute(c, p, outputs_too));
-  ph_end(c, kPhPermute);
-  ph_begin(c, kPhTree);
-  HIPCHK(c, sph::launch_tree(c));
-  HIPCHK(c, sph::launch_node_boxes(c, p));
-  ph_end(c, kPhTree);
+  HIPCHK(c, ph_run(c, kPhSort, [&] {
+    const hipError_t e = sph::launch_predict_keys(c, p, predict, 0.0);
+    return e == hipSuccess ? sph::launch_sort(c) : e;
+  }));
+  HIPCHK(c, ph_run(c, kPhPermute, [&] { return sph::launch_permute(c, p, outputs_too); }));
+  HIPCHK(c, ph_run(c, kPhTree, [&] {
+    const hipError_t e = sph::launch_tree(c);
+    return e == hipSuccess ? sph::launch_node_boxes(c, p) : e;
+  }));
   return SPH_OK;
 }
 
@@ -389,6 +434,8 @@ sph_status sph_build_tree(sph_ctx* c, sph_particles* p) {
   if (!c) return SPH_E_ARG;
   sph_status st = check_parts(c, p, false, false);
   if (st != SPH_OK) return st;
+  TimingScope scope(c, c->timing_every > 0);
+  ph_mark(c);
   HIPCHK(c, sph::launch_reset_counters(c));
   return do_build(c, p, true, false);
 }
@@ -397,20 +444,12 @@ sph_status sph_build_tree(sph_ctx* c, sph_particles* p) {
 // walking kernel for flagged groups; or the walking kernel for all groups.
 static sph_status run_density(sph_ctx* c, sph_particles* p) {
   if (sph::lists_mode(c)) {
-    ph_begin(c, kPhLists);
-    HIPCHK(c, sph::launch_lists(c, p));
-    ph_end(c, kPhLists);
+    HIPCHK(c, ph_run(c, kPhLists, [&] { return sph::launch_lists(c, p); }));
     ++c->lists_launches;
-    ph_begin(c, kPhDensity);
-    HIPCHK(c, sph::launch_density_lists(c, p));
-    ph_end(c, kPhDensity);
-    ph_begin(c, kPhDensityFb);
-    HIPCHK(c, sph::launch_density(c, p, true));
-    ph_end(c, kPhDensityFb);
+    HIPCHK(c, ph_run(c, kPhDensity, [&] { return sph::launch_density_lists(c, p); }));
+    HIPCHK(c, ph_run(c, kPhDensityFb, [&] { return sph::launch_density(c, p, true); }));
   } else {
-    ph_begin(c, kPhDensity);
-    HIPCHK(c, sph::launch_density(c, p, false));
-    ph_end(c, kPhDensity);
+    HIPCHK(c, ph_run(c, kPhDensity, [&] { return sph::launch_density(c, p, false); }));
   }
   ++c->density_launches;
   ++c->densities_on_tree;
@@ -421,16 +460,10 @@ static sph_status run_density(sph_ctx* c, sph_particles* p) {
 // the rest (or for all groups).
 static sph_status run_force(sph_ctx* c, sph_particles* p, bool step_mode) {
   if (sph::lists_mode(c)) {
-    ph_begin(c, kPhForce);
-    HIPCHK(c, sph::launch_force_lists(c, p, step_mode));
-    ph_end(c, kPhForce);
-    ph_begin(c, kPhForceFb);
-    HIPCHK(c, sph::launch_force(c, p, step_mode, true));
-    ph_end(c, kPhForceFb);
+    HIPCHK(c, ph_run(c, kPhForce, [&] { return sph::launch_force_lists(c, p, step_mode); }));
+    HIPCHK(c, ph_run(c, kPhForceFb, [&] { return sph::launch_force(c, p, step_mode, true); }));
   } else {
-    ph_begin(c, kPhForce);
-    HIPCHK(c, sph::launch_force(c, p, step_mode, false));
-    ph_end(c, kPhForce);
+    HIPCHK(c, ph_run(c, kPhForce, [&] { return sph::launch_force(c, p, step_mode, false); }));
   }
   ++c->force_launches;
   return SPH_OK;
@@ -441,6 +474,7 @@ sph_status sph_density(sph_ctx* c, sph_particles* p, int32_t* iters_out) {
   sph_status st = check_parts(c, p, false, true);
   if (st != SPH_OK) return st;
   if (p->n != c->n) return fail(c, SPH_E_ARG, "n differs from the last sph_build_tree");
+  TimingScope scope(c, c->timing_every > 0);
   // the packed positions and masses the list and density kernels gather are
   // taken from the arrays as they are now (m may have changed since the build;
   // the mixed code records are packed with the h_max refresh below)
@@ -450,6 +484,7 @@ sph_status sph_density(sph_ctx* c, sph_particles* p, int32_t* iters_out) {
   // tree starts from the h the last one converged to), or the list walk
   // could leave out a neighbour whose h grew past its node's h_max
   HIPCHK(c, sph::launch_node_h(c, p, true));
+  ph_mark(c);
   HIPCHK(c, sph::launch_leaf_state(c, 1));
   st = run_density(c, p);
   if (st != SPH_OK) return st;
@@ -470,7 +505,9 @@ sph_status sph_force(sph_ctx* c, sph_particles* p, double* dt_next_out) {
   sph_status st = check_parts(c, p, true, true);
   if (st != SPH_OK) return st;
   if (p->n != c->n) return fail(c, SPH_E_ARG, "n differs from the last sph_build_tree");
+  TimingScope scope(c, c->timing_every > 0);
   HIPCHK(c, sph::launch_node_h(c, p, false));
+  ph_mark(c);
   HIPCHK(c, sph::launch_force_reset(c));
   st = run_force(c, p, false);
   if (st != SPH_OK) return st;
@@ -482,30 +519,32 @@ sph_status sph_force(sph_ctx* c, sph_particles* p, double* dt_next_out) {
   return SPH_OK;
 }
 
+// A step up to the corrector; `begin` is the phase boundary it starts from.
+static sph_status step_to_force(sph_ctx* c, sph_particles* p, double dt, int& begin) {
+  ph_mark(c);
+  begin = ph_last(c);
+  HIPCHK(c, sph::launch_step_begin(c, dt));
+  sph_status st = do_build(c, p, false, true);
+  if (st != SPH_OK) return st;
+  st = run_density(c, p);
+  if (st != SPH_OK) return st;
+  ph_mark(c);
+  HIPCHK(c, sph::launch_node_h(c, p, false));
+  return run_force(c, p, true);
+}
+
 sph_status sph_step(sph_ctx* c, sph_particles* p, double dt, double* dt_next_out) {
   if (!c) return SPH_E_ARG;
   sph_status st = check_parts(c, p, true, true);
   if (st != SPH_OK) return st;
   if (!isfinite(dt)) return fail(c, SPH_E_ARG, "dt is not finite");
   // phase events on one call in timing_every; other entry points always record
-  struct TimingScope {
-    sph_ctx* c;
-    ~TimingScope() { c->timing = c->timing_every > 0; }
-  } scope{c};
-  c->timing = c->timing_every > 0 && (c->step_calls++ % c->timing_every) == 0;
-  ph_begin(c, kPhStep);
-  HIPCHK(c, sph::launch_step_begin(c, dt));
-  st = do_build(c, p, false, true);
+  TimingScope scope(c, c->timing_every > 0 && (c->step_calls++ % c->timing_every) == 0);
+  int begin = -1;
+  st = step_to_force(c, p, dt, begin);
   if (st != SPH_OK) return st;
-  st = run_density(c, p);
-  if (st != SPH_OK) return st;
-  HIPCHK(c, sph::launch_node_h(c, p, false));
-  st = run_force(c, p, true);
-  if (st != SPH_OK) return st;
-  ph_begin(c, kPhIntegrate);
-  HIPCHK(c, sph::launch_correct(c, p));
-  ph_end(c, kPhIntegrate);
-  ph_end(c, kPhStep);
+  HIPCHK(c, ph_run(c, kPhIntegrate, [&] { return sph::launch_correct(c, p); }));
+  ph_span(c, kPhStep, begin);
   if (dt_next_out) {
     st = sync_state(c, true);
     *dt_next_out = courant_dt(*c->hs);
@@ -550,13 +589,14 @@ static sph_status adj_check(sph_ctx* c, const sph_particles* p, const sph_cotang
 // h and must be complete.
 static sph_status adj_launch(sph_ctx* c, const sph_particles* p, sph_cotangents* g, double dt,
                              bool step_mode) {
-  ph_begin(c, kPhAdjoint);
+  ph_record(c);
+  const int from = ph_last(c);
+  ph_mark(c);
   HIPCHK(c, sph::launch_adjoint(c, p, g, dt, step_mode, 0));
-  ph_begin(c, kPhAdjForce);
-  HIPCHK(c, sph::launch_adjoint(c, p, g, dt, step_mode, 1));
-  ph_end(c, kPhAdjForce);
+  HIPCHK(c, ph_run(c, kPhAdjForce, [&] { return sph::launch_adjoint(c, p, g, dt, step_mode, 1); }));
+  ph_mark(c);
   HIPCHK(c, sph::launch_adjoint(c, p, g, dt, step_mode, 2));
-  ph_end(c, kPhAdjoint);
+  ph_span(c, kPhAdjoint, from);
   return SPH_OK;
 }
 
@@ -580,6 +620,7 @@ sph_status sph_eval_adjoint(sph_ctx* c, const sph_particles* p, sph_cotangents* 
   sph_status st = adj_check(c, p, g);
   if (st != SPH_OK) return st;
   if (p->n != c->n) return fail(c, SPH_E_ARG, "n differs from the last sph_build_tree");
+  TimingScope scope(c, c->timing_every > 0);
   st = adj_rows(c, p);
   if (st != SPH_OK) return st;
   return adj_launch(c, p, g, 0.0, false);
@@ -591,24 +632,17 @@ sph_status sph_step_adjoint(sph_ctx* c, sph_particles* p, double dt, sph_cotange
   if (st != SPH_OK) return st;
   if (!(dt > 0.0) || !isfinite(dt)) return fail(c, SPH_E_ARG, "the step adjoint needs dt > 0");
   // the forward step up to the corrector (as sph_step)
-  ph_begin(c, kPhStep);
-  HIPCHK(c, sph::launch_step_begin(c, dt));
-  st = do_build(c, p, false, true);
+  TimingScope scope(c, c->timing_every > 0);
+  int begin = -1;
+  st = step_to_force(c, p, dt, begin);
   if (st != SPH_OK) return st;
-  st = run_density(c, p);
-  if (st != SPH_OK) return st;
-  HIPCHK(c, sph::launch_node_h(c, p, false));
-  st = run_force(c, p, true);
-  if (st != SPH_OK) return st;
-  ph_end(c, kPhStep);
+  ph_span(c, kPhStep, begin);
   // reverse sweep at the predicted state (x1, v_p, u_p, new a in scratch)
   st = adj_rows(c, p);
   if (st != SPH_OK) return st;
   st = adj_launch(c, p, g, dt, true);
   if (st != SPH_OK) return st;
-  ph_begin(c, kPhIntegrate);
-  HIPCHK(c, sph::launch_correct(c, p));
-  ph_end(c, kPhIntegrate);
+  HIPCHK(c, ph_run(c, kPhIntegrate, [&] { return sph::launch_correct(c, p); }));
   return SPH_OK;
 }
 
@@ -811,12 +845,14 @@ sph_status sph_timings(sph_ctx* c, double out[12]) {
     double s = 0.0;
     const int n = x->count[ph];
     for (int r = 0; r < n; ++r) {
+      const int* sp = x->span[ph][r];
       float ms = 0.f;
-      if (hipEventElapsedTime(&ms, x->start[ph][r], x->stop[ph][r]) == hipSuccess) s += ms;
+      if (hipEventElapsedTime(&ms, x->ev[sp[0]], x->ev[sp[1]]) == hipSuccess) s += ms;
     }
     out[map[ph]] = n ? s / n : 0.0;
     x->count[ph] = 0;
   }
+  x->used = 0;
   return SPH_OK;
 }
 

@@ -3692,9 +3692,13 @@ hipError_t launch_sort(sph_ctx* c) {
                      status, ghist);
   for (int pass = 0; pass < 8; ++pass) {
     const int src = pass & 1, dst = src ^ 1;
-    hipLaunchKernelGGL(k_radix_pass, dim3(nblk), dim3(256), 0, c->stream, c->keys[src],
-                       c->vals[src], c->keys[dst], c->vals[dst], n, pass, nblk, status, ghist,
-                       tickets, &c->ds->err);
+    if (pass < 7)
+      hipLaunchKernelGGL(k_radix_pass, dim3(nblk), dim3(256), 0, c->stream, c->keys[src],
+                         c->vals[src], c->keys[dst], c->vals[dst], n, pass, nblk, status, ghist,
+                         tickets, &c->ds->err);
+    else
+      launch_last(c, k_radix_pass, dim3(nblk), dim3(256), c->keys[src], c->vals[src],
+                  c->keys[dst], c->vals[dst], n, pass, nblk, status, ghist, tickets, &c->ds->err);
   }
   return hipGetLastError();  // 8 passes: the result is back in buffer 0
 }
@@ -3717,8 +3721,8 @@ hipError_t launch_permute(sph_ctx* c, const sph_particles* s, bool outputs_too) 
   const int nb = stream_blocks(c->n);
   hipLaunchKernelGGL(k_gather, dim3(nb), dim3(256), 0, c->stream, fs, c->vals[0], c->gtmp,
                      c->gtmp_id, c->n, (int64_t)c->n_max);
-  hipLaunchKernelGGL(k_copy_back, dim3(nb), dim3(256), 0, c->stream, fs, c->gtmp, c->gtmp_id,
-                     c->n, (int64_t)c->n_max);
+  launch_last(c, k_copy_back, dim3(nb), dim3(256), fs, c->gtmp, c->gtmp_id, c->n,
+              (int64_t)c->n_max);
   return hipGetLastError();
 }
 
@@ -3732,8 +3736,8 @@ hipError_t launch_pack_xyzm(sph_ctx* c, const sph_particles* s) {
 }
 
 static void pack_q(sph_ctx* c, const sph_particles* s, int mode) {
-  hipLaunchKernelGGL(k_pack_q, dim3(stream_blocks(c->n)), dim3(256), 0, c->stream, c->kp,
-                     parts_of(s), c->n, c->ds, mode, c->qxyzm, c->qrec);
+  launch_last(c, k_pack_q, dim3(stream_blocks(c->n)), dim3(256), c->kp, parts_of(s), c->n, c->ds,
+              mode, c->qxyzm, c->qrec);
 }
 
 hipError_t launch_tree(sph_ctx* c) {
@@ -3775,21 +3779,31 @@ static hipError_t node_props(sph_ctx* c, const sph_particles* s, int mode) {
   const int nb = (int)std::min<int64_t>(std::max<int64_t>((items / 4 + 15) / 16, 16), 4096);
   const int nbi =
       small ? (int)std::min<int64_t>(std::max<int64_t>((c->node_cap / 8 + 63) / 64, 16), 4096) : 0;
-  hipLaunchKernelGGL(k_range_boxes, dim3(nb + nbi), dim3(256), 0, c->stream, s->x, s->y, s->z,
-                     s->h, c->node_first, c->node_count, c->node_child, c->node_nchild, c->wnode,
-                     c->grp_first, c->grp_count, c->ginfo, c->ds, mode, nb, n, c->chunk_box,
-                     c->node_parent);
+  // the last launch of an h_max refresh stamps a phase boundary
+  const bool mixed = c->kp.precision == SPH_PREC_MIXED;
+  const hipEvent_t mark = c->mark;
+  c->mark = mode != 1 && small && !mixed ? mark : nullptr;
+  launch_last(c, k_range_boxes, dim3(nb + nbi), dim3(256), s->x, s->y, s->z, s->h, c->node_first,
+              c->node_count, c->node_child, c->node_nchild, c->wnode, c->grp_first, c->grp_count,
+              c->ginfo, c->ds, mode, nb, n, c->chunk_box, c->node_parent);
   if (!small) {
     const int nblk = (n + kTreeTile - 1) / kTreeTile;
     const int lb =
         (int)std::min<int64_t>(std::max<int64_t>((c->node_cap / 4 + 255) / 256, 1), 1024);
-    for (int l = kLevels - 2; l >= 0; --l)
-      hipLaunchKernelGGL(k_level_boxes, dim3(lb), dim3(256), 0, c->stream, l, c->tree_cnt, nblk,
-                         c->node_first, c->node_child, c->node_nchild, c->wnode, c->ds, mode);
+    for (int l = kLevels - 2; l >= 0; --l) {
+      c->mark = mode != 1 && l == 0 && !mixed ? mark : nullptr;
+      launch_last(c, k_level_boxes, dim3(lb), dim3(256), l, c->tree_cnt, nblk, c->node_first,
+                  c->node_child, c->node_nchild, c->wnode, c->ds, mode);
+    }
   }
   // mixed: the code records with the current h and m (a new tree's after its
   // frame, below)
-  if (mode != 1 && c->kp.precision == SPH_PREC_MIXED) pack_q(c, s, mode);
+  if (mode != 1 && mixed) {
+    c->mark = mark;
+    pack_q(c, s, mode);
+  } else if (mode == 1) {
+    c->mark = mark;  // the caller's last launch stamps it
+  }
   return hipGetLastError();
 }
 
@@ -3799,10 +3813,14 @@ hipError_t launch_node_h(sph_ctx* c, const sph_particles* s, bool always) {
 hipError_t launch_node_boxes(sph_ctx* c, const sph_particles* s) {
   const hipError_t e = node_props(c, s, 1);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_qframe, dim3(1), dim3(64), 0, c->stream, c->kp, c->wnode, c->ds);
   // the mixed code records need the frame (the FP64 packed positions come
   // from the permute)
-  if (c->kp.precision == SPH_PREC_MIXED) pack_q(c, s, 1);
+  if (c->kp.precision == SPH_PREC_MIXED) {
+    hipLaunchKernelGGL(k_qframe, dim3(1), dim3(64), 0, c->stream, c->kp, c->wnode, c->ds);
+    pack_q(c, s, 1);
+  } else {
+    launch_last(c, k_qframe, dim3(1), dim3(64), c->kp, c->wnode, c->ds);
+  }
   return hipGetLastError();
 }
 
@@ -3849,9 +3867,9 @@ static hipError_t density_dispatch(sph_ctx* c, const sph_particles* s, const int
   // over a quarter of the walk grid: an empty launch then costs less
   const dim3 grid(gflag ? std::max(c->walk_blocks / 4, 8) : c->walk_blocks), block(64);
   SPH_LPI_SWITCH(c->kp.n_group,
-                 hipLaunchKernelGGL((k_density<MIXED, LPI>), grid, block, 0, c->stream, c->kp, p,
-                                    c->wnode, c->ginfo, c->frec, c->leaf_pool, c->pool_cap,
-                                    c->gl_off, c->gl_cnt, gflag, c->walk_spill, c->ds));
+                 launch_last(c, (k_density<MIXED, LPI>), grid, block, c->kp, p, c->wnode, c->ginfo,
+                             c->frec, c->leaf_pool, c->pool_cap, c->gl_off, c->gl_cnt, gflag,
+                             c->walk_spill, c->ds));
   return hipGetLastError();
 }
 
@@ -3868,16 +3886,14 @@ hipError_t launch_lists(sph_ctx* c, const sph_particles* s) {
   const dim3 grid(c->walk_blocks), block(64);
   if (c->kp.precision == SPH_PREC_MIXED) {
     SPH_LPI_SWITCH_LISTS(c->kp.n_group,
-                         hipLaunchKernelGGL((k_lists<true, LPI>), grid, block, 0, c->stream,
-                                            c->kp, p, c->wnode, c->ginfo, c->nl_idx, c->nl_len,
-                                            c->gflag, c->flag_list, c->grp_of, c->qrec,
-                                            c->walk_spill, c->ds));
+                         launch_last(c, (k_lists<true, LPI>), grid, block, c->kp, p, c->wnode,
+                                     c->ginfo, c->nl_idx, c->nl_len, c->gflag, c->flag_list,
+                                     c->grp_of, c->qrec, c->walk_spill, c->ds));
   } else {
     SPH_LPI_SWITCH_LISTS(c->kp.n_group,
-                         hipLaunchKernelGGL((k_lists<false, LPI>), grid, block, 0, c->stream,
-                                            c->kp, p, c->wnode, c->ginfo, c->nl_idx, c->nl_len,
-                                            c->gflag, c->flag_list, c->grp_of, c->qrec,
-                                            c->walk_spill, c->ds));
+                         launch_last(c, (k_lists<false, LPI>), grid, block, c->kp, p, c->wnode,
+                                     c->ginfo, c->nl_idx, c->nl_len, c->gflag, c->flag_list,
+                                     c->grp_of, c->qrec, c->walk_spill, c->ds));
   }
   return hipGetLastError();
 }
@@ -3903,11 +3919,11 @@ template <bool MIXED, int CAP, int KIND>
 static void density_lists_kind(sph_ctx* c, const Parts& p) {
   const dim3 grid(c->walk_blocks), block(64);
   SPH_LPI_SWITCH_LISTS(c->kp.n_group,
-                       hipLaunchKernelGGL((k_density_lists<MIXED, LPI, CAP, KIND>), grid, block,
-                                          0, c->stream, c->kp, p, c->ginfo, c->nl_idx, c->nl_len,
-                                          c->gflag, c->flag_list, c->grp_of,
-                                          MIXED ? (const void*)c->qxyzm : (const void*)c->xyzm,
-                                          c->frec, c->ds));
+                       launch_last(c, (k_density_lists<MIXED, LPI, CAP, KIND>), grid, block,
+                                   c->kp, p, c->ginfo, c->nl_idx, c->nl_len, c->gflag,
+                                   c->flag_list, c->grp_of,
+                                   MIXED ? (const void*)c->qxyzm : (const void*)c->xyzm, c->frec,
+                                   c->ds));
 }
 
 template <bool MIXED, int CAP>
@@ -3939,9 +3955,9 @@ static hipError_t force_dispatch(sph_ctx* c, const sph_particles* s, double* oax
   const Parts p = parts_of(s);
   const dim3 grid(c->walk_blocks), block(64);
   SPH_LPI_SWITCH(c->kp.n_group,
-                 hipLaunchKernelGGL((k_force<MIXED, LPI>), grid, block, 0, c->stream, c->kp, p,
-                                    c->wnode, c->ginfo, c->frec, c->leaf_pool, c->gl_off,
-                                    c->gl_cnt, oax, oay, oaz, odu, gflag, c->walk_spill, c->ds));
+                 launch_last(c, (k_force<MIXED, LPI>), grid, block, c->kp, p, c->wnode, c->ginfo,
+                             c->frec, c->leaf_pool, c->gl_off, c->gl_cnt, oax, oay, oaz, odu, gflag,
+                             c->walk_spill, c->ds));
   return hipGetLastError();
 }
 
@@ -3965,10 +3981,9 @@ template <bool MIXED, int KIND>
 static void force_lists_kind(sph_ctx* c, const Parts& p, double* const* o) {
   const dim3 grid(c->walk_blocks), block(64);
   SPH_LPI_SWITCH_LISTS(c->kp.n_group,
-                       hipLaunchKernelGGL((k_force_lists<MIXED, LPI, KIND>), grid, block, 0,
-                                          c->stream, c->kp, p, c->ginfo, c->frec, c->nl_idx,
-                                          c->nl_len, c->gflag, c->grp_of, o[0], o[1], o[2], o[3],
-                                          c->ds));
+                       launch_last(c, (k_force_lists<MIXED, LPI, KIND>), grid, block, c->kp, p,
+                                   c->ginfo, c->frec, c->nl_idx, c->nl_len, c->gflag, c->grp_of,
+                                   o[0], o[1], o[2], o[3], c->ds));
 }
 
 hipError_t launch_force_lists(sph_ctx* c, const sph_particles* s, bool step_mode) {
@@ -4000,18 +4015,18 @@ hipError_t launch_row_sets(sph_ctx* c, const sph_particles* s, int mode, int32_t
 }
 
 hipError_t launch_leaf_state(sph_ctx* c, int v) {
-  hipLaunchKernelGGL(k_set_leaf_state, dim3(1), dim3(64), 0, c->stream, c->ds, v);
+  launch_last(c, k_set_leaf_state, dim3(1), dim3(64), c->ds, v);
   return hipGetLastError();
 }
 
 hipError_t launch_force_reset(sph_ctx* c) {
-  hipLaunchKernelGGL(k_reset_force_state, dim3(1), dim3(64), 0, c->stream, c->ds);
+  launch_last(c, k_reset_force_state, dim3(1), dim3(64), c->ds);
   return hipGetLastError();
 }
 
 hipError_t launch_correct(sph_ctx* c, const sph_particles* s) {
-  hipLaunchKernelGGL(k_correct, dim3(stream_blocks(c->n)), dim3(256), 0, c->stream, parts_of(s),
-                     c->n, c->a1, (int64_t)c->n_max, c->ds);
+  launch_last(c, k_correct, dim3(stream_blocks(c->n)), dim3(256), parts_of(s), c->n, c->a1,
+              (int64_t)c->n_max, c->ds);
   return hipGetLastError();
 }
 
@@ -4041,12 +4056,12 @@ hipError_t launch_reduce(sph_ctx* c, const sph_particles* s, double* dev_out) {
 }
 
 hipError_t launch_step_begin(sph_ctx* c, double dt_host) {
-  hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, c->stream, c->ds, dt_host);
+  launch_last(c, k_step_begin, dim3(1), dim3(64), c->ds, dt_host);
   return hipGetLastError();
 }
 
 hipError_t launch_reset_counters(sph_ctx* c) {
-  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, c->stream, c->ds);
+  launch_last(c, k_reset_counters, dim3(1), dim3(64), c->ds);
   return hipGetLastError();
 }
 
