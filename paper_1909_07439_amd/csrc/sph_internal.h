@@ -84,7 +84,7 @@ struct DevState {
   int32_t n_flag_rows;    // groups whose neighbour-list rows overflowed (walking kernels)
   int32_t n_flag_grew;    // groups in which some h outgrew the rows (walking kernels)
   int32_t n_flagged;      // entries of the flagged-group list (both kinds)
-  int32_t pad1;
+  int32_t pool_used;      // entries taken from the pool of single groups' leaf lists
   double dt_cur;          // step used by the running sph_step
   alignas(256) uint32_t err;
   alignas(256) QFrame qf;  // frame of the mixed force records (set with each tree's node boxes)
@@ -144,6 +144,14 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 }
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
 __device__ __forceinline__ int popc64(uint64_t x) { return __popcll(x); }
+
+// Marks a loaded value as used here whatever becomes of it, so that the
+// compiler neither sinks its load into a later condition nor serialises a
+// batch of loads that are meant to be in flight together.
+template <typename T>
+__device__ __forceinline__ void loaded(T& v) {
+  asm volatile("" : "+v"(v));
+}
 
 // v of lane (l ^ D).  Distances below 16 stay within a row of 16 lanes and go
 // by DPP (a VALU move, no LDS round trip): quad permutations for 1 and 2, the

@@ -2419,439 +2419,6 @@ __global__ __launch_bounds__(64) void k_force(KParams kp, Parts p,
   }
 }
 
-// ============================================================================
-// Neighbour lists (Sect. 3.2).  k_lists: one wavefront per super-group of
-// kSGL consecutive groups (aligned runs of the curve, hence compact).  Each
-// XCD's super-groups go round its wavefronts; those left over after the last
-// full round are cut into aligned units of 4, 2 or 1 groups, the largest size
-// that still gives every wavefront at most one unit, so that the last round
-// costs a fraction of a super-group.  The super-group's particles are loaded
-// once, one per lane.  The super-group walk collects every leaf any of its
-// groups can need; one pass over that list then tests each leaf against the
-// box of every group of the super-group (one bit per group), so a node is
-// read once per super-group.  Each group then loads the particles of its
-// leaves, one candidate per lane, and for each of its particles i in turn
-// appends the indices j of every candidate with
-//     r_ij < 2 max(hl_i, hl_j),   hl = h_margin * (h at the start),
-// to the fixed-capacity row i of nl_idx (self included): one ballot and one
-// coalesced store per particle and 64 candidates, in candidate order.  As
-// long as no h grows past its hl, a row is a superset of the density
-// neighbours (r < 2 h_i) and of the force pairs (r < 2 max(h_i, h_j)); the
-// density and force list kernels apply the exact predicates.  A group with
-// an overflowing row or a failed walk is flagged (gflag = 1) and left to the
-// walking kernels.  The group of every particle is kept (grp_of) for the list
-// kernels, which work on chunks of consecutive particles instead of groups.
-// ============================================================================
-
-constexpr int kSGL = 8;       // groups per super-group of the list kernel
-constexpr int kSLCapL = 512;  // leaves a list-kernel super-group walk may collect
-constexpr int kListPer = 4;   // candidates each lane loads per list-kernel tile
-
-// The value a wave-uniform lane `l` holds, as a wave-uniform scalar.
-__device__ __forceinline__ float lane_val(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ double lane_val(double v, int l) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// base + the number of set bits of m below this lane (mbcnt: two VALU ops)
-__device__ __forceinline__ int rank_below(uint64_t m, int base) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
-}
-
-// Squared search radius (support * x)^2 of the list predicate, with a
-// relative slack of 1e-5 in FP32.  Every step rounds monotonically, so the
-// value at max(a, b) is the larger of the values at a and at b: the pair test
-// compares r^2 with the larger of the particle's and the candidate's value.
-__device__ __forceinline__ float list_thr(float support, float x) {
-  const float s = support * x;
-  return s * s * 1.00001f;
-}
-__device__ __forceinline__ double list_thr(double support, double x) {
-  const double s = support * x;
-  return s * s;
-}
-
-template <bool MIXED, int LPI>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
-void k_lists(KParams kp, Parts p, const WalkNode* __restrict__ nodes,
-             const GroupInfo* __restrict__ groups, int32_t* __restrict__ nl_idx,
-             int32_t* __restrict__ nl_len, int32_t* __restrict__ gflag,
-             int32_t* __restrict__ flag_list, int32_t* __restrict__ grp_of,
-             const int4* __restrict__ qrec, int32_t* __restrict__ walk_spill,
-             DevState* __restrict__ ds) {
-  int* __restrict__ spill = walk_spill + (int64_t)blockIdx.x * 2 * kSpill;
-  using R = typename std::conditional<MIXED, float, double>::type;
-  constexpr int GS = kWave / LPI;  // particles per group at most
-  constexpr int PER = kListPer;  // candidates per lane per tile
-  static_assert(kSGL * GS <= kWave, "one lane per particle of a super-group");
-  __shared__ WalkLds L;
-  // the frontier is live only during walks, the leaf ranges of the
-  // super-group only after its walk; a group that walks on its own (the
-  // super-group's list overflowed) takes the node ids instead
-  __shared__ union {
-    int front[2][kFCap];
-    struct {
-      int first[kSLCapL];
-      int cntbits[kSLCapL];  // particle count | (one bit per group) << 24
-    } sl;
-  } U;
-  __shared__ int s_sl[kSLCapL];  // leaf node ids of the walk
-  __shared__ double s_hm[kSGL];  // largest hl of each group
-  // one flag per candidate of a tile: a flushed leaf's range starts there
-  __shared__ alignas(4) uint8_t s_start[PER * kWave];
-  const int lane = threadIdx.x;
-  const int ng = ds->n_groups;
-  const int nsg = (ng + kSGL - 1) / kSGL;
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, nloc = gridDim.x >> 3;
-  const int chunk = (nsg + 7) >> 3;
-  const int sbeg = xcd * chunk, send = min(sbeg + chunk, nsg);
-  // full rounds of super-groups, then the tail [gt0, gx1) in units of tsz groups
-  const int nfull = (max(send - sbeg, 0) / nloc) * nloc;
-  const int gt0 = min((sbeg + nfull) * kSGL, ng), gx1 = min(send * kSGL, ng);
-  int tsz = 1;
-  while (tsz < kSGL && (gx1 - gt0 + tsz - 1) / tsz > nloc) tsz *= 2;
-  const int nunits = nfull + (gx1 - gt0 + tsz - 1) / tsz;
-  const double margin = kp.h_margin;
-  const R supr = (R)kp.support, marginr = (R)margin;
-  const int cap = kp.nl_cap;
-  float lpf[3], ilpf[3];  // periodic lengths and their inverses in FP32 (0 on open axes)
-  for (int a = 0; a < 3; ++a) {
-    lpf[a] = kp.periodic[a] ? (float)kp.len[a] : 0.f;
-    ilpf[a] = kp.periodic[a] ? (float)kp.inv_len[a] : 0.f;
-  }
-  // FP32 path: positions are code differences (the tree's fixed-point frame)
-  // from the group's centre; reach bounds the list radius of every pair
-  const QFrame& qf = ds->qf;
-  const double reach =
-      kp.support * margin * (ds->n_nodes > 0 ? (double)nodes[0].hmax : 0.0) * (1.0 + 1e-4);
-  bool flagged = false;
-  int nflag = 0;
-  unsigned long long cands = 0;
-  int walks = 0;
-
-  for (int u = local; u < nunits; u += nloc) {
-    int g0, g1;
-    if (u < nfull) {
-      g0 = (sbeg + u) * kSGL;
-      g1 = min(g0 + kSGL, ng);
-    } else {
-      g0 = gt0 + (u - nfull) * tsz;
-      g1 = min(g0 + tsz, gx1);
-    }
-    const int ngs = g1 - g0;
-    GroupInfo SG;
-    {
-      const bool v = lane < ngs;
-      GroupInfo Gk;
-      if (v) Gk = groups[g0 + lane];
-      for (int a = 0; a < 3; ++a) {
-        const double lo = wave_min_f64(v ? Gk.c[a] - Gk.w[a] : SPH_INF);
-        const double hi = wave_max_f64(v ? Gk.c[a] + Gk.w[a] : -SPH_INF);
-        SG.c[a] = 0.5 * (lo + hi);
-        SG.w[a] = fmax(hi - SG.c[a], SG.c[a] - lo);
-      }
-      SG.hmax = wave_max_f64(v ? Gk.hmax : 0.0);
-      SG.first = 0;
-      SG.count = 0;
-    }
-    // one particle per lane for the whole super-group (lane = group * GS +
-    // slot): position (FP32 path: relative to its group's centre, folded) and
-    // squared search radius, read as scalars by the pair loop; the largest
-    // hl of each group
-    const int pgk = lane / GS, psl = lane % GS;
-    bool pact = false;
-    int pi = 0;
-    R xq = R(0), yq = R(0), zq = R(0), tq = R(0);
-    {
-      double hl = 0.0;
-      if (pgk < ngs) {
-        const GroupInfo& Gp = groups[g0 + pgk];
-        pact = psl < Gp.count;
-        pi = Gp.first + (pact ? psl : 0);
-        const double xi = p.x[pi], yi = p.y[pi], zi = p.z[pi], hi = p.h[pi];
-        if constexpr (MIXED) {
-          xq = qsep(qcode(xi, qf, 0, kp.periodic[0]), qcode(Gp.c[0], qf, 0, kp.periodic[0]),
-                    qf.step[0]);
-          yq = qsep(qcode(yi, qf, 1, kp.periodic[1]), qcode(Gp.c[1], qf, 1, kp.periodic[1]),
-                    qf.step[1]);
-          zq = qsep(qcode(zi, qf, 2, kp.periodic[2]), qcode(Gp.c[2], qf, 2, kp.periodic[2]),
-                    qf.step[2]);
-        } else {
-          xq = xi;
-          yq = yi;
-          zq = zi;
-        }
-        tq = list_thr(supr, (R)(margin * hi));
-        if (pact) hl = margin * hi;
-      }
-      hl = seg_max<GS>(hl);
-      if (psl == 0 && pgk < ngs) s_hm[pgk] = hl;
-    }
-    __syncthreads();
-    int npv = 0;  // entries appended to this lane's particle's row so far
-    int nsl = 0;
-    bool sok = true;
-    {
-      const double hs = margin * SG.hmax;
-      auto sradius = [&](const WalkNode& nd) {
-        return kp.support * fmax(hs, margin * (double)nd.hmax) * (1.0 + 4e-9);
-      };
-      auto sflush = [&](int nleaf) {
-        if (nsl + nleaf <= kSLCapL) {
-          for (int q = lane; q < nleaf; q += kWave) s_sl[nsl + q] = L.lnode[q];
-        } else {
-          sok = false;
-        }
-        nsl += nleaf;
-        __syncthreads();
-      };
-      if (!group_walk<!MIXED>(nodes, SG, kp, L, U.front, spill, sradius, sflush)) sok = false;
-      __syncthreads();  // the frontier's LDS becomes the leaf ranges
-      ++walks;
-    }
-    if (sok) {
-      // each leaf against every group's box, with that group's radius; a
-      // range of 2^24 particles or more (coincident keys, or a whole inner
-      // node) does not fit beside the bits: the groups then walk on their own
-      // two leaves per lane per trip, their node loads in flight together
-      for (int base = 0; base < nsl; base += 2 * kWave) {
-        const int ka = base + lane, kb = base + kWave + lane;
-        const WalkNode na = nodes[s_sl[ka < nsl ? ka : 0]];
-        const WalkNode nb = nodes[s_sl[kb < nsl ? kb : 0]];
-        bool big = false;
-        auto leaf_bits = [&](const WalkNode& nd, int k) {
-          int bits = 0;
-          for (int gk = 0; gk < ngs; ++gk) {
-            const double rg = kp.support * fmax(s_hm[gk], margin * (double)nd.hmax) * (1.0 + 4e-9);
-            if (box_gap2(nd, groups[g0 + gk], kp) < rg * rg) bits |= 1 << gk;
-          }
-          big = big || nd.count >= (1 << 24);
-          U.sl.first[k] = nd.first;
-          U.sl.cntbits[k] = (nd.count & 0xffffff) | (bits << 24);
-        };
-        if (ka < nsl) leaf_bits(na, ka);
-        if (kb < nsl) leaf_bits(nb, kb);
-        if (ballot64(big) != 0ull) sok = false;
-      }
-      __syncthreads();
-    }
-    for (int g = g0; g < g1; ++g) {
-      const int gk = g - g0;
-      const GroupInfo G = groups[g];
-      const int cnt = G.count;
-      const int l0 = gk * GS;  // lane of the group's first particle
-      const double hm = s_hm[gk];
-      auto radius = [&](const WalkNode& nd) {
-        return kp.support * fmax(hm, margin * (double)nd.hmax) * (1.0 + 4e-9);
-      };
-      // FP32 path: the group centre's codes; a candidate's offset from the
-      // centre is the wrapped code difference, its nearest image.  A pair's
-      // difference of offsets is then the pair's nearest image whenever it
-      // lies within reach, unless the group's half-width and the reach
-      // together come to half a periodic length on some axis (tiny periodic
-      // boxes): that group folds every pair separation instead.
-      int32_t qgx = 0, qgy = 0, qgz = 0;
-      bool amb = false;
-      if constexpr (MIXED) {
-        qgx = qcode(G.c[0], qf, 0, kp.periodic[0]);
-        qgy = qcode(G.c[1], qf, 1, kp.periodic[1]);
-        qgz = qcode(G.c[2], qf, 2, kp.periodic[2]);
-        for (int a = 0; a < 3; ++a)
-          if (kp.periodic[a] && G.w[a] + reach >= kp.half[a]) amb = true;
-      }
-      auto flush = [&](int nleaf) {
-        const int total = leaf_offsets(L, nleaf);
-        if (lane == 0) cands += (unsigned long long)total * (unsigned)cnt;
-        // leaves hold at least one particle each (tree cells are cut from
-        // the sorted keys), so the leaf of candidate c is the number of leaf
-        // ranges starting at or before c, less one
-        int lt = -1;  // leaf of the candidate before the tile
-        for (int c0 = 0; c0 < total; c0 += PER * kWave) {
-          const int cn = min(PER * kWave, total - c0);
-          // flag the starts of the leaf ranges within the tile
-          static_assert(PER * kWave % (4 * kWave) == 0, "whole dwords per lane");
-#pragma unroll
-          for (int w = 0; w < PER / 4; ++w) reinterpret_cast<int*>(s_start)[lane + w * kWave] = 0;
-          __syncthreads();
-          for (int l = lt + 1 + lane;; l += kWave) {
-            const int o = l < nleaf ? L.loff[l] - c0 : cn;
-            const bool in = o < cn;
-            if (in && o >= 0) s_start[o] = 1;
-            if (ballot64(in) != ~0ull) break;
-          }
-          __syncthreads();
-          // resolve this lane's candidates, then issue all their loads
-          int jj[PER];
-#pragma unroll
-          for (int q = 0; q < PER; ++q) {
-            const int t = lane + q * kWave;
-            const int st = t < cn ? (int)s_start[t] : 0;
-            const uint64_t b = ballot64(st != 0);
-            const int lo = rank_below(b, lt + st);
-            lt += popc64(b);
-            jj[q] = t < cn ? L.lfirst[lo] + (c0 + t - L.loff[lo]) : -1;
-          }
-          R cx[PER], cy[PER], cz[PER], ct[PER];
-          if constexpr (MIXED) {
-            // one 16-byte load per candidate: its position codes and its h
-            int4 v[PER];
-#pragma unroll
-            for (int q = 0; q < PER; ++q) v[q] = qrec[jj[q] >= 0 ? jj[q] : 0];
-#pragma unroll
-            for (int q = 0; q < PER; ++q) {
-              cx[q] = qsep(v[q].x, qgx, qf.step[0]);
-              cy[q] = qsep(v[q].y, qgy, qf.step[1]);
-              cz[q] = qsep(v[q].z, qgz, qf.step[2]);
-              ct[q] = list_thr(supr, marginr * __int_as_float(v[q].w));
-            }
-          } else {
-            double vx[PER], vy[PER], vz[PER], vh[PER];
-#pragma unroll
-            for (int q = 0; q < PER; ++q) {
-              const int j = jj[q] >= 0 ? jj[q] : 0;
-              vx[q] = p.x[j];
-              vy[q] = p.y[j];
-              vz[q] = p.z[j];
-              vh[q] = p.h[j];
-            }
-#pragma unroll
-            for (int q = 0; q < PER; ++q) {
-              cx[q] = vx[q];
-              cy[q] = vy[q];
-              cz[q] = vz[q];
-              ct[q] = list_thr(supr, marginr * (R)vh[q]);
-            }
-          }
-          uint64_t vm[PER];  // lanes holding a candidate, per quarter of the tile
-#pragma unroll
-          for (int q = 0; q < PER; ++q) vm[q] = ballot64(jj[q] >= 0);
-          // particle-major: each particle's values are read from its lane once
-          // per tile; its row gets the tile's candidates in order
-          auto particles = [&](auto fold_pairs) {
-            constexpr bool FOLD = decltype(fold_pairs)::value;
-            for (int s = 0; s < cnt; ++s) {
-              const int ls = l0 + s;
-              const R px = lane_val(xq, ls), py = lane_val(yq, ls), pz = lane_val(zq, ls);
-              const R pt = lane_val(tq, ls);
-              int32_t* __restrict__ row = nl_idx + (int64_t)(G.first + s) * cap;
-              int n = __builtin_amdgcn_readlane(npv, ls);
-#pragma unroll
-              for (int q = 0; q < PER; ++q) {
-                if (q * kWave < cn) {
-                  // one compare per ballot; candidates past the tile's end
-                  // are masked out afterwards (scalar AND)
-                  bool hit;
-                  if constexpr (MIXED) {
-                    float dx = px - cx[q], dy = py - cy[q], dz = pz - cz[q];
-                    if constexpr (FOLD) {
-                      dx = fmaf(-lpf[0], rintf(dx * ilpf[0]), dx);
-                      dy = fmaf(-lpf[1], rintf(dy * ilpf[1]), dy);
-                      dz = fmaf(-lpf[2], rintf(dz * ilpf[2]), dz);
-                    }
-                    const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                    // r2 and the radii are >= 0: their bit patterns order
-                    // like their values (an integer max needs no NaN care)
-                    hit = __float_as_int(r2) < max(__float_as_int(pt), __float_as_int(ct[q]));
-                  } else {
-                    const double dx = fold(px - cx[q], kp.len[0], kp.half[0], kp.periodic[0]);
-                    const double dy = fold(py - cy[q], kp.len[1], kp.half[1], kp.periodic[1]);
-                    const double dz = fold(pz - cz[q], kp.len[2], kp.half[2], kp.periodic[2]);
-                    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-                    hit = r2 < fmax(pt, ct[q]);
-                  }
-                  const bool pred = hit & (jj[q] >= 0);
-                  const uint64_t b = ballot64(hit) & vm[q];
-                  const int pos = rank_below(b, n);
-                  if (pred & (pos < cap)) row[(unsigned)pos] = jj[q];
-                  n += popc64(b);
-                }
-              }
-              npv = lane == ls ? n : npv;
-            }
-          };
-          if (MIXED && amb)
-            particles(std::true_type{});
-          else
-            particles(std::false_type{});
-        }
-        __syncthreads();  // L is refilled next
-      };
-      bool gok = sok;
-      if (sok) {
-        int nleaf = 0;
-        for (int base = 0; base < nsl; base += kWave) {
-          const int k = base + lane;
-          const bool open = k < nsl && ((U.sl.cntbits[k] >> (24 + gk)) & 1);
-          const uint64_t lb = ballot64(open);
-          const int nl = popc64(lb);
-          if (nleaf + nl > kLCap) {
-            flush(nleaf);
-            nleaf = 0;
-          }
-          if (open) {
-            const int pos = nleaf + popc64(lb & lanemask_lt());
-            L.lfirst[pos] = U.sl.first[k];
-            L.lcnt[pos] = U.sl.cntbits[k] & 0xffffff;
-            L.lnode[pos] = s_sl[k];
-          }
-          nleaf += nl;
-          __syncthreads();
-        }
-        if (nleaf > 0) flush(nleaf);
-      } else {
-        // the super-group's leaf list overflowed: the group walks for its
-        // own leaf list; a group whose list overflows too is left to the
-        // walking kernels
-        int ngl = 0;
-        gok = true;
-        auto gflush = [&](int nleaf) {
-          if (ngl + nleaf <= kSLCapL) {
-            for (int q = lane; q < nleaf; q += kWave) s_sl[ngl + q] = L.lnode[q];
-          } else {
-            gok = false;
-          }
-          ngl += nleaf;
-          __syncthreads();
-        };
-        if (!group_walk<!MIXED>(nodes, G, kp, L, U.front, spill, radius, gflush)) gok = false;
-        __syncthreads();
-        ++walks;
-        if (gok) list_walk(nodes, s_sl, ngl, G, kp, L, radius, flush);
-      }
-      const bool mine = lane >= l0 && lane < l0 + cnt;
-      const bool bad = !gok || ballot64(mine && npv > cap) != 0ull;
-      if (lane == 0) {
-        gflag[g] = bad ? 1 : 0;
-        if (bad) flag_list[atomicAdd(&ds->n_flagged, 1)] = g;
-      }
-      flagged |= bad;
-      nflag += bad ? 1 : 0;
-    }
-    if (pact) {
-      nl_len[pi] = npv;
-      grp_of[pi] = g0 + pgk;
-    }
-  }
-  unsigned long long cd = cands;
-  for (int d = 32; d > 0; d >>= 1) cd += __shfl_xor(cd, d, kWave);
-  if (lane == 0) {
-    WaveTally& tally = my_tally(ds);
-    if (cd) atomicAdd(&tally.n_cand_density, cd);
-    if (cd) atomicAdd(&tally.tot_cand_lists, cd);
-    if (walks) atomicAdd(&tally.n_rewalk, walks);
-    if (flagged) {
-      atomicOr(&ds->lists_missing, 1);
-      atomicAdd(&ds->n_flag_rows, nflag);
-    }
-  }
-}
-
 // Groups of this wave under the XCD-aware static schedule: block b works on
 // the contiguous eighth of the groups that belongs to XCD b mod 8.
 struct GroupRange {
@@ -2862,6 +2429,634 @@ __device__ __forceinline__ GroupRange xcd_groups(int ng) {
   const int chunk = (ng + 7) >> 3;
   const int gbeg = xcd * chunk;
   return GroupRange{gbeg + local, min(gbeg + chunk, ng), nloc};
+}
+
+// ============================================================================
+// Neighbour lists (Sect. 3.2), in two kernels.
+//
+// k_leaves: one wavefront per super-group of kSGL consecutive groups (aligned
+// runs of the curve, hence compact) walks the tree once for all of them and
+// writes every leaf that any of the groups can need to the super-group's leaf
+// list, with one bit per group whose box and radius reach the leaf.  The walk
+// starts from all nodes of levels 0 to 2 (at most 73) at once.  A super-group
+// whose list or frontier overflows lets each of its groups walk on its own,
+// into a list from the pool.
+//
+// k_rows: one wavefront per group takes the leaves that carry its bit, loads
+// their particles, one candidate per lane, and for each of its particles i in
+// turn appends the indices j of every candidate with
+//     r_ij < S max(hl_i, hl_j),   hl = h_margin * (h at the start),
+// to the fixed-capacity row i of nl_idx (self included): one ballot and one
+// coalesced store per particle and 64 candidates, in candidate order (leaves
+// by level, then along the curve).  As long as no h grows past its hl, a row
+// is a superset of the density neighbours (r < S h_i) and of the force pairs
+// (r < S max(h_i, h_j)); the density and force list kernels apply the exact
+// predicates.  A group with an overflowing row or a failed walk is flagged
+// (gflag = 1) and left to the walking kernels.  The group of every particle is
+// kept (grp_of) for the list kernels, which work on chunks of consecutive
+// particles instead of groups.
+//
+// Why two kernels: the walk is a chain of dependent loads (one level after
+// another) and the row tests are VALU work; in one kernel the frontier, the
+// leaf lists and the candidate tiles of both took 8.5 KB of LDS and 121
+// registers per wavefront, and its 4 wavefronts per SIMD kept the VALU half
+// idle.  k_leaves is bound by its loads' latency, k_rows by VALU and scalar
+// issue.  One kernel -> k_leaves + k_rows: 16.8M mixed 11.2 -> 2.2 + 5.7 ms,
+// 10^6 mixed 819 -> 150 + 316 us, 10^6 FP64 1322 -> 150 + 456, 294,912 mixed
+// 176 -> 61 + 70, 32^3 FP64 65 -> 20 + 19 us.
+// ============================================================================
+constexpr int kSGLShift = 3;
+constexpr int kSGL = 1 << kSGLShift;  // groups per super-group of the list kernels
+constexpr int kSLCapL = 512;  // leaves a list-kernel walk may collect
+constexpr int kLeafPart = 64; // particles per leaf-list entry at most (>= the largest n_leaf)
+constexpr int kLeafWaves = 6; // wavefronts per SIMD of k_leaves
+constexpr int kRowWaves = 8;  // and of k_rows
+constexpr int kNoLeaves = -0x7fffffff;  // ll_cnt of a group whose walk failed
+
+// The value a wave-uniform lane `l` holds, as a wave-uniform scalar.
+__device__ __forceinline__ float lane_val(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// Whether this lane's bit of a wave-uniform mask is set.
+__device__ __forceinline__ bool lane_in(uint64_t m) {
+  return __builtin_amdgcn_inverse_ballot_w64(m);
+}
+
+// Largest value of each aligned run of 8 lanes.
+__device__ __forceinline__ float seg_max8(float v) {
+  v = fmaxf(v, __uint_as_float(xor_lane_u32<4>(__float_as_uint(v))));
+  v = fmaxf(v, __uint_as_float(xor_lane_u32<2>(__float_as_uint(v))));
+  return fmaxf(v, __uint_as_float(xor_lane_u32<1>(__float_as_uint(v))));
+}
+
+// base + the number of set bits of m below this lane (mbcnt: two VALU ops)
+__device__ __forceinline__ int rank_below(uint64_t m, int base) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
+}
+
+// Squared search radius (support * x)^2 of the list predicate with the slack
+// of its FP32 test: 1e-5 relative, and 2e-6 w (support * x) for offsets that
+// were rounded to FP32 at a distance of up to w (0 for position codes) beyond
+// the radius from the group's centre.  Every step rounds monotonically, so
+// the value at max(a, b) is the larger of the values at a and at b: the pair
+// test compares r^2 with the larger of the particle's and the candidate's.
+__device__ __forceinline__ float list_thr(float support, float x, float w) {
+  const float s = support * x;
+  return fmaf(2e-6f * w, s, s * s * 1.00001f);
+}
+
+// Groups per unit of k_leaves (its log2): kSGL, or fewer on sets too small to
+// give every fourth wavefront a unit of that size.
+__device__ __forceinline__ int unit_shift(int ng, int nwaves) {
+  int u = kSGLShift;
+  while (u > 0 && (ng >> u) < nwaves / 4) --u;
+  return u;
+}
+// Entries of a unit's leaf list: an equal share of the list space.
+__device__ __forceinline__ int leaf_list_cap(int64_t entries, int nu) {
+  return (int)min((int64_t)kSLCapL, entries / max(nu, 1));
+}
+
+// Separation of a node's centre from c along the nearest periodic image, and
+// the squared gap between the node's box and the box (c, w).
+__device__ __forceinline__ double node_gap2(const WalkNode& nd, const double (&c)[3],
+                                            const double (&w)[3], const KParams& kp,
+                                            double (&dc)[3]) {
+  double d2 = 0.0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    double d = nd.c[a] - c[a];
+    if (kp.periodic[a]) d = d - kp.len[a] * rint(d * kp.inv_len[a]);
+    dc[a] = d;
+    double gap = fabs(d) - (double)nd.w[a] - w[a];
+    gap = gap > 0.0 ? gap : 0.0;
+    d2 = d2 + gap * gap;
+  }
+  return d2;
+}
+
+// Breadth-first walk for the region within S max(hl, margin h_max(node)) of
+// the box (c, w): visit(leaf, node, dc) is called by all lanes for every batch
+// of up to 64 nodes, with leaf set in the lanes that hold an opened leaf, and
+// ends the walk by returning false.  A level's frontier holds kFCap entries in
+// LDS and continues in this wavefront's region of global memory (spill_cap
+// entries per level).  Returns false if the walk ended early or its frontier
+// overflowed.
+template <typename Visit>
+__device__ __forceinline__ bool leaf_walk(const WalkNode* __restrict__ nodes, int n01, int n012,
+                                          const double (&c)[3], const double (&w)[3], double hl,
+                                          const KParams& kp, int (&front)[2][kFCap],
+                                          int* __restrict__ spill, int spill_cap, Visit visit) {
+  const int lane = threadIdx.x;
+  const int cap = kFCap + spill_cap;
+  auto fget = [&](int lvl, int k) -> int {
+    return k < kFCap ? front[lvl][k]
+                     : __hip_atomic_load(&spill[lvl * spill_cap + (k - kFCap)], __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto fput = [&](int lvl, int k, int v) {
+    if (k < kFCap)
+      front[lvl][k] = v;
+    else
+      __hip_atomic_store(&spill[lvl * spill_cap + (k - kFCap)], v, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+  };
+  // the first frontier: nodes 0 .. n012 - 1, of which the first n01 (levels 0
+  // and 1) have their children in it already
+  for (int k = lane; k < n012; k += kWave) front[0][k] = k;
+  int nf = n012, cur = 0, no_push = n01;
+  __syncthreads();
+  while (nf > 0) {
+    int nn = 0;
+    for (int base = 0; base < nf; base += kWave) {
+      const int k = base + lane;
+      WalkNode nd;
+      nd.nchild = 0;
+      bool open = false;
+      int id = 0;
+      double dc[3] = {0.0, 0.0, 0.0};
+      if (k < nf) {
+        id = fget(cur, k);
+        nd = nodes[id];
+        const double R =
+            kp.support * fmax(hl, kp.h_margin * (double)nd.hmax) * (1.0 + 4e-9);
+        open = node_gap2(nd, c, w, kp, dc) < R * R;
+      }
+      if (!visit(open && nd.nchild == 0, nd, dc)) return false;
+      const uint32_t nc = open && id >= no_push ? (uint32_t)nd.nchild : 0u;
+      const uint32_t inc = wave_incl_scan_u32(nc);
+      const int tot = __builtin_amdgcn_readlane((int)inc, kWave - 1);
+      if (nn + tot > cap) return false;
+      const int o = nn + (int)(inc - nc);
+      for (uint32_t q = 0; q < nc; ++q) fput(cur ^ 1, o + (int)q, nd.child + (int)q);
+      nn += tot;
+      __syncthreads();
+    }
+    nf = nn;
+    cur ^= 1;
+    no_push = 0;
+  }
+  return true;
+}
+
+// sg_list: the units' leaf lists, `sg_entries` entries in all; entry: (first
+// particle, particle count | group bits << 24), of at most kLeafPart
+// particles (a level-21 leaf of more takes several).  pool: lists of groups
+// that walked on their own; entry: (first particle, particle count).  Per group:
+// ll_off, ll_cnt = its list's first entry and length (>= 0) in sg_list, or
+// ll_cnt = ~length (< 0) in the pool, or kNoLeaves.
+//
+// A unit's groups are walked together unless they lie apart: where the curve
+// jumps between two of them by more than their two search regions (an octant
+// boundary of a high level), or where their list overflows, the run is cut,
+// and the parts walk one after the other.  (Walked whole, such a unit's box
+// spans the domain: its walk alone took 150 us at 294,912 particles, longer
+// than all others together.)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kLeafWaves)))
+void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
+              const GroupInfo* __restrict__ groups, const uint32_t* __restrict__ level_off,
+              int nblk, int2* __restrict__ sg_list, int64_t sg_entries, int2* __restrict__ pool,
+              int pool_cap, int32_t* __restrict__ ll_off, int32_t* __restrict__ ll_cnt,
+              int32_t* __restrict__ gflag, int32_t* __restrict__ walk_spill, int spill_cap,
+              DevState* __restrict__ ds) {
+  int* __restrict__ spill = walk_spill + (int64_t)blockIdx.x * 2 * spill_cap;
+  __shared__ int front[2][kFCap];
+  __shared__ float4 s_g[kSGL][2];  // per group: box centre from the part's, h_l; half-widths
+  const int lane = threadIdx.x;
+  const int ng = ds->n_groups;
+  const int ush = unit_shift(ng, (int)gridDim.x), usz = 1 << ush;
+  const int nu = (ng + usz - 1) >> ush;
+  const int cap = leaf_list_cap(sg_entries, nu);
+  const int n01 = (int)level_off[2 * nblk], n012 = (int)level_off[3 * nblk];
+  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, nloc = gridDim.x >> 3;
+  const int chunk = (nu + 7) >> 3;
+  const int uend = min((xcd + 1) * chunk, nu);
+  const float S = (float)kp.support, margin = (float)kp.h_margin;
+  int walks = 0;
+
+  for (int u = xcd * chunk + local; u < uend; u += nloc) {
+    const int g0 = u * usz, ngs = min(usz, ng - g0);
+    const bool isg = lane < ngs;
+    const int glane = g0 + (isg ? lane : 0);
+    if (isg) gflag[glane] = 0;
+    // bit k: the search regions of groups k - 1 and k do not meet
+    uint64_t jumps;
+    {
+      const GroupInfo Gk = groups[glane];
+      const double reach = kp.support * kp.h_margin * Gk.hmax;
+      const double before = __shfl_up(reach, 1, kWave);
+      bool apart = false;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const double cb = __shfl_up(Gk.c[a], 1, kWave), wb = __shfl_up(Gk.w[a], 1, kWave);
+        apart |= fabs(Gk.c[a] - cb) - Gk.w[a] - wb > reach + before;
+      }
+      jumps = ballot64(apart && isg && lane > 0);
+    }
+    const int64_t base = (int64_t)u * cap;
+    int used = 0;  // entries of the unit's space written so far
+    for (int a0 = 0; a0 < ngs;) {
+      const uint64_t ahead = jumps & (~0ull << (a0 + 1));
+      int a1 = ahead ? min(__builtin_ctzll(ahead), ngs) : ngs;
+      // The part [a0, a1) into the unit's list, halved until it fits (kUnit);
+      // a single group that still does not fit counts its leaves (kCount) and
+      // then writes them to space taken from the pool (kPool).
+      enum { kUnit, kCount, kPool };
+      int mode = kUnit, off = 0, room = cap - used;
+      int2* __restrict__ list = sg_list + base + used;
+      while (true) {
+        const bool in = lane >= a0 && lane < a1;
+        const GroupInfo Gk = groups[glane];
+        double c[3], w[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const double lo = wave_min_f64(in ? Gk.c[a] - Gk.w[a] : SPH_INF);
+          const double hi = wave_max_f64(in ? Gk.c[a] + Gk.w[a] : -SPH_INF);
+          c[a] = 0.5 * (lo + hi);
+          w[a] = fmax(hi - c[a], c[a] - lo);
+        }
+        const double hl = kp.h_margin * wave_max_f64(in ? Gk.hmax : 0.0);
+        __syncthreads();
+        if (in) {
+          // FP32 offsets from the part's centre
+          s_g[lane][0] = make_float4((float)(Gk.c[0] - c[0]), (float)(Gk.c[1] - c[1]),
+                                     (float)(Gk.c[2] - c[2]), (float)(kp.h_margin * Gk.hmax));
+          s_g[lane][1] = make_float4((float)Gk.w[0], (float)Gk.w[1], (float)Gk.w[2], 0.f);
+        }
+        // bound of the FP32 offsets' rounding within the part's reach
+        const float eps = (float)(1e-6 * (fmax(w[0], fmax(w[1], w[2])) + kp.support * hl));
+        __syncthreads();
+        int n = 0;
+        const bool fits =
+            leaf_walk(nodes, n01, n012, c, w, hl, kp, front, spill, spill_cap,
+                      [&](bool leaf, const WalkNode& nd, const double (&dc)[3]) {
+          if (ballot64(leaf) == 0ull) return true;
+          uint32_t bits = 0;
+          if (mode == kUnit) {
+            // FP32 on offsets from the part's centre, settled in FP64 within
+            // its rounding of the boundary, and near half a periodic length,
+            // where a group's nearest image may be another than the part's:
+            // the leaves a group takes, and so the rows, do not depend on the
+            // part it walks with
+            bool amb = false;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) amb |= kp.periodic[a] && fabs(dc[a]) + w[a] > kp.half[a];
+            const float x = (float)dc[0], y = (float)dc[1], z = (float)dc[2];
+            const float e4 = 4.f * fmaf(1e-6f, fmaxf(nd.w[0], fmaxf(nd.w[1], nd.w[2])), eps);
+            uint32_t border = 0;
+            for (int gk = a0; gk < a1; ++gk) {
+              const float4 gc = s_g[gk][0], gw = s_g[gk][1];
+              const float dx = fmaxf(fabsf(x - gc.x) - (nd.w[0] + gw.x), 0.f);
+              const float dy = fmaxf(fabsf(y - gc.y) - (nd.w[1] + gw.y), 0.f);
+              const float dz = fmaxf(fabsf(z - gc.z) - (nd.w[2] + gw.z), 0.f);
+              const float R = S * fmaxf(gc.w, margin * nd.hmax);
+              const float t = fmaf(dz, dz, fmaf(dy, dy, dx * dx)) - R * R;
+              const float tol = R * fmaf(4e-5f, R, e4);
+              bits |= t < 0.f ? 1u << (24 + gk) : 0u;
+              border |= fabsf(t) <= tol ? 1u << gk : 0u;
+            }
+            if (amb) border = (1u << a1) - (1u << a0);
+            if (!leaf) border = 0u;
+            while (ballot64(border != 0u) != 0ull) {
+              if (border != 0u) {
+                const int gk = __builtin_ctz(border);
+                const GroupInfo G = groups[g0 + gk];
+                const double rg = kp.support *
+                                  fmax(kp.h_margin * G.hmax, kp.h_margin * (double)nd.hmax) *
+                                  (1.0 + 4e-9);
+                bits &= ~(1u << (24 + gk));
+                if (box_gap2(nd, G, kp) < rg * rg) bits |= 1u << (24 + gk);
+                border &= border - 1u;
+              }
+            }
+            leaf = leaf && bits != 0u;
+          }
+          const uint64_t lb = ballot64(leaf);
+          if (ballot64(leaf && nd.count > kLeafPart) == 0ull) {
+            const int pos = rank_below(lb, n);
+            if (leaf && pos < room && mode != kCount)
+              list[pos] = make_int2(nd.first, (int)((uint32_t)nd.count | bits));
+            n += popc64(lb);
+          } else {  // leaves of coincident keys, in parts
+            const uint32_t np = leaf ? (uint32_t)((nd.count + kLeafPart - 1) / kLeafPart) : 0u;
+            const uint32_t inc = wave_incl_scan_u32(np);
+            int pos = n + (int)(inc - np);
+            if (mode != kCount)
+              for (int f = 0; f < (int)np * kLeafPart && pos < room; f += kLeafPart, ++pos)
+                list[pos] = make_int2(
+                    nd.first + f, (int)((uint32_t)min(kLeafPart, nd.count - f) | bits));
+            n += __builtin_amdgcn_readlane((int)inc, kWave - 1);
+          }
+          return n <= room;
+        });
+        ++walks;
+        if (mode == kCount && fits) {
+          // not past a full pool, so that the counter cannot wrap round
+          if (lane == 0) {
+            const int taken =
+                __hip_atomic_load(&ds->pool_used, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            off = (uint32_t)taken < (uint32_t)pool_cap ? atomicAdd(&ds->pool_used, n) : -1;
+          }
+          off = __builtin_amdgcn_readfirstlane(off);
+          if (off >= 0 && off <= pool_cap - n) {
+            list = pool + off;
+            room = n;
+            mode = kPool;
+            continue;
+          }
+        } else if (mode == kUnit && !fits) {
+          if (a1 - a0 > 1) {
+            a1 = a0 + (a1 - a0) / 2;
+          } else {
+            mode = kCount;
+            room = kSLCapL;
+          }
+          continue;
+        }
+        if (in) {
+          ll_off[glane] = mode == kUnit ? used : off;
+          ll_cnt[glane] = mode == kUnit ? n : mode == kPool && fits ? ~n : kNoLeaves;
+        }
+        if (mode == kUnit) used += n;
+        break;
+      }
+      a0 = a1;
+    }
+    __syncthreads();  // s_g and the frontier are refilled next
+  }
+  if (lane == 0 && walks) atomicAdd(&my_tally(ds).n_rewalk, walks);
+}
+
+// Candidates of a group are first tested against its box (with the largest
+// radius of its particles); those that pass are packed in LDS, and every 128 of
+// them meet the group's particles.  (Leaves bring in about twice the
+// candidates that lie within reach of the group.)  2^psh wavefronts share a
+// group, each with its share of the particles, where there are fewer groups
+// than wavefronts.
+template <bool MIXED>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kRowWaves)))
+void k_rows(KParams kp, const double* __restrict__ hp, const WalkNode* __restrict__ nodes,
+            const GroupInfo* __restrict__ groups, const int2* __restrict__ sg_list,
+            int64_t sg_entries, int leaf_grid, const int2* __restrict__ pool,
+            const int32_t* __restrict__ ll_off, const int32_t* __restrict__ ll_cnt,
+            int32_t* __restrict__ nl_idx, int32_t* __restrict__ nl_len,
+            int32_t* __restrict__ gflag, int32_t* __restrict__ flag_list,
+            int32_t* __restrict__ grp_of, const int4* __restrict__ qrec,
+            const double4* __restrict__ xyzm, DevState* __restrict__ ds) {
+  constexpr int PT = 2;                   // sets of 64 packed candidates per test
+  constexpr int NPK = (PT + 1) * kWave;   // fewer than PT sets wait when the next is packed
+  constexpr int NM = kWave * kLeafPart / kWave;
+  __shared__ float4 s_c[NPK];  // packed candidates: offset from the centre, squared radius
+  __shared__ int s_j[NPK];
+  __shared__ int s_j0[kWave];  // first particle of each selected leaf less its first candidate
+  __shared__ unsigned long long s_start[NM];  // bit c: a leaf's candidates start at c
+  const int lane = threadIdx.x;
+  const int ng = ds->n_groups;
+  const int ush = unit_shift(ng, leaf_grid);
+  const int ucap = leaf_list_cap(sg_entries, (ng + (1 << ush) - 1) >> ush);
+  int psh = 0;
+  while (psh < 2 && (ng << (psh + 1)) <= (int)gridDim.x) ++psh;
+  const GroupRange gr = xcd_groups(ng << psh);
+  const float S = (float)kp.support, marginf = (float)kp.h_margin;
+  const int cap = kp.nl_cap;
+  const float stx = ds->qf.step[0], sty = ds->qf.step[1], stz = ds->qf.step[2];
+  // reach bounds the list radius of every pair
+  const double reach =
+      kp.support * kp.h_margin * (ds->n_nodes > 0 ? (double)nodes[0].hmax : 0.0) * (1.0 + 1e-4);
+  int nflag = 0;
+  unsigned long long cands = 0;
+
+  for (int it = gr.beg; it < gr.end; it += gr.step) {
+    const int g = it >> psh, part = it & ((1 << psh) - 1);
+    const double gcx = groups[g].c[0], gcy = groups[g].c[1], gcz = groups[g].c[2];
+    const double gwx = groups[g].w[0], gwy = groups[g].w[1], gwz = groups[g].w[2];
+    const int gcount = groups[g].count;
+    // this wavefront's particles of the group
+    const int s0 = (gcount * part) >> psh, cnt = ((gcount * (part + 1)) >> psh) - s0;
+    const int gfirst = groups[g].first + s0;
+    const int nl = ll_cnt[g];
+    const bool own = nl < 0;
+    const bool gok = nl != kNoLeaves;
+    const int nlist = !gok ? 0 : own ? ~nl : nl;
+    const int2* __restrict__ list =
+        own ? pool + ll_off[g] : sg_list + ((int64_t)(g >> ush) * ucap + ll_off[g]);
+    const uint32_t mybit = own ? ~0u : 1u << (24 + (g & ((1 << ush) - 1)));
+    const uint32_t cmask = own ? ~0u : 0xffffffu;
+    // Positions relative to the group's centre along the nearest image: code
+    // differences in the tree's fixed-point frame (mixed), or rounded FP64
+    // differences.  A pair's difference of offsets is then the pair's nearest
+    // image whenever it lies within reach, unless the group's half-width and
+    // the reach together come to half a periodic length on some axis (tiny
+    // periodic boxes): that group folds every pair separation instead.
+    const bool farx = kp.periodic[0] && gwx + reach >= kp.half[0];
+    const bool fary = kp.periodic[1] && gwy + reach >= kp.half[1];
+    const bool farz = kp.periodic[2] && gwz + reach >= kp.half[2];
+    const bool amb = farx || fary || farz;
+    float wr = 0.f;  // distance at which FP64 offsets may have been rounded
+    int32_t qgx = 0, qgy = 0, qgz = 0;
+    if constexpr (MIXED) {
+      const QFrame& qf = ds->qf;
+      qgx = qcode(gcx, qf, 0, kp.periodic[0]);
+      qgy = qcode(gcy, qf, 1, kp.periodic[1]);
+      qgz = qcode(gcz, qf, 2, kp.periodic[2]);
+    } else {
+      wr = (float)fmax(gwx + (farx ? kp.len[0] : 0.0),
+                       fmax(gwy + (fary ? kp.len[1] : 0.0), gwz + (farz ? kp.len[2] : 0.0)));
+    }
+    // a particle as the tests take it: its offset and its squared radius
+    struct Raw {
+      int4 q;     // mixed
+      double4 d;  // FP64
+      double h;
+    };
+    auto load = [&](int j) {
+      Raw r;
+      if constexpr (MIXED) {
+        r.q = qrec[j];
+      } else {
+        r.d = xyzm[j];
+        r.h = hp[j];
+      }
+      return r;
+    };
+    auto offsets = [&](const Raw& r) {
+      float4 c;
+      if constexpr (MIXED) {
+        c.x = qsep(r.q.x, qgx, stx);
+        c.y = qsep(r.q.y, qgy, sty);
+        c.z = qsep(r.q.z, qgz, stz);
+        c.w = list_thr(S, marginf * __int_as_float(r.q.w), 0.f);
+      } else {
+        c.x = (float)fold(r.d.x - gcx, kp.len[0], kp.half[0], kp.periodic[0]);
+        c.y = (float)fold(r.d.y - gcy, kp.len[1], kp.half[1], kp.periodic[1]);
+        c.z = (float)fold(r.d.z - gcz, kp.len[2], kp.half[2], kp.periodic[2]);
+        c.w = list_thr(S, (float)(kp.h_margin * r.h), wr);
+      }
+      return c;
+    };
+    // one particle per lane, read as scalars by the tests; the next entry of
+    // its row, counted from the first particle's row
+    const int pi = gfirst + (lane < cnt ? lane : 0);
+    float4 me = offsets(load(pi));
+    if constexpr (MIXED) me.w = list_thr(S, (float)(kp.h_margin * hp[pi]), 0.f);
+    int npv = lane * cap;
+    int32_t* __restrict__ rows = nl_idx + (int64_t)gfirst * cap;
+    // the box of the particles about the group's centre with its test's own
+    // rounding, and their largest squared radius (lanes 0 to 7 hold them all)
+    float bx = seg_max8(fabsf(me.x)), by = seg_max8(fabsf(me.y)), bz = seg_max8(fabsf(me.z));
+    float tmax = seg_max8(me.w);
+    {
+      const float e = 1e-6f * (bx + by + bz + fast_sqrt(tmax));
+      bx = lane_val(bx + e, 0);
+      by = lane_val(by + e, 0);
+      bz = lane_val(bz + e, 0);
+      tmax = amb ? (float)SPH_INF : lane_val(tmax, 0);  // folded pairs: no box test
+    }
+    int npk = 0;  // packed candidates waiting
+
+    // the first PT sets of 64 packed candidates (or what is left of them)
+    // against the particles: every particle's row gets the hits in order
+    auto test = [&]() {
+      float4 c[PT];
+      int j[PT];
+      uint64_t vm[PT];  // lanes that hold a candidate
+#pragma unroll
+      for (int q = 0; q < PT; ++q) {
+        c[q] = s_c[q * kWave + lane];
+        j[q] = s_j[q * kWave + lane];
+        const int left = npk - q * kWave;
+        vm[q] = left >= kWave ? ~0ull : left > 0 ? ~0ull >> (kWave - left) : 0ull;
+      }
+      auto pairs = [&](auto fold_pairs) {
+        constexpr bool FOLD = decltype(fold_pairs)::value;
+        int end = 0;  // of the particle's row
+        for (int s = 0; s < cnt; ++s) {
+          const float px = lane_val(me.x, s), py = lane_val(me.y, s), pz = lane_val(me.z, s);
+          const float pt = lane_val(me.w, s);
+          int n = __builtin_amdgcn_readlane(npv, s);
+          end += cap;
+#pragma unroll
+          for (int q = 0; q < PT; ++q) {
+            if (q > 0 && vm[q] == 0ull) break;
+            float dx = px - c[q].x, dy = py - c[q].y, dz = pz - c[q].z;
+            if constexpr (FOLD) {
+              auto nearest = [&](float d, int a) {
+                return kp.periodic[a]
+                           ? fmaf(-(float)kp.len[a], rintf(d * (float)kp.inv_len[a]), d)
+                           : d;
+              };
+              dx = nearest(dx, 0);
+              dy = nearest(dy, 1);
+              dz = nearest(dz, 2);
+            }
+            const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+            // r2 and the radii are >= 0: their bit patterns order like their
+            // values (an integer max needs no NaN care)
+            const uint64_t b =
+                ballot64(__float_as_int(r2) < max(__float_as_int(pt), __float_as_int(c[q].w))) &
+                vm[q];
+            const int pos = rank_below(b, n);
+            const uint64_t st = b & ballot64(pos < end);
+            if (lane_in(st))
+              *reinterpret_cast<int*>(reinterpret_cast<char*>(rows) + ((unsigned)pos << 2)) = j[q];
+            n += popc64(b);
+          }
+          npv = lane_in(1ull << s) ? n : npv;
+        }
+      };
+      if (amb)
+        pairs(std::true_type{});
+      else
+        pairs(std::false_type{});
+    };
+
+    // 64 leaves at a time: those with this group's bit, their first candidate
+    // in s_j0 and s_start; then their candidates, 64 at a time
+    for (int base = 0; base < nlist || npk > 0; base += kWave) {
+      int total = 0;
+      if (base < nlist) {
+        const int k = base + lane;
+        const int2 e = list[min(k, nlist - 1)];
+        const bool open = k < nlist && ((uint32_t)e.y & mybit) != 0u;
+        const uint32_t c = open ? (uint32_t)e.y & cmask : 0u;
+        const uint32_t inc = wave_incl_scan_u32(c);
+        total = __builtin_amdgcn_readlane((int)inc, kWave - 1);
+        __syncthreads();
+        for (int m = lane; m * kWave < total; m += kWave) s_start[m] = 0ull;
+        __syncthreads();
+        if (open) {
+          const int o = (int)(inc - c);
+          s_j0[rank_below(ballot64(open), 0)] = e.x - o;
+          atomicOr(&s_start[o >> 6], 1ull << (o & 63));
+        }
+        __syncthreads();
+        if (part == 0) cands += (unsigned long long)total * (unsigned)gcount;
+      }
+      // leaves hold at least one particle each, so the leaf of candidate c is
+      // the number of starts at or before c, less one
+      int lt = -1;  // leaf of the candidate before the set
+      for (int c0 = 0; c0 < total; c0 += kWave) {
+        const unsigned long long starts = s_start[c0 >> 6];
+        const uint64_t st =
+            (uint64_t)__builtin_amdgcn_readfirstlane((int)starts) & 0xffffffffull |
+            (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(starts >> 32)) << 32;
+        const int left = total - c0;
+        const uint64_t vm = left >= kWave ? ~0ull : ~0ull >> (kWave - left);
+        const int lo = rank_below(st, lt) + (lane_in(st) ? 1 : 0);
+        lt += popc64(st);
+        const int j = lane_in(vm) ? s_j0[lo] + c0 + lane : gfirst;
+        const float4 c = offsets(load(j));
+        const float dx = fmaxf(fabsf(c.x) - bx, 0.f), dy = fmaxf(fabsf(c.y) - by, 0.f),
+                    dz = fmaxf(fabsf(c.z) - bz, 0.f);
+        const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+        const uint64_t near =
+            ballot64(__float_as_int(d2) < max(__float_as_int(tmax), __float_as_int(c.w))) & vm;
+        if (lane_in(near)) {
+          const int pos = rank_below(near, npk);
+          s_c[pos] = c;
+          s_j[pos] = j;
+        }
+        npk += popc64(near);
+        __syncthreads();
+        if (npk >= PT * kWave) {
+          test();
+          const float4 rc = s_c[PT * kWave + lane];  // the rest moves to the front
+          const int rj = s_j[PT * kWave + lane];
+          __syncthreads();
+          s_c[lane] = rc;
+          s_j[lane] = rj;
+          npk -= PT * kWave;
+          __syncthreads();
+        }
+      }
+      if (base + kWave >= nlist && npk > 0) {
+        test();
+        npk = 0;
+      }
+    }
+    const int len = npv - lane * cap;
+    const bool bad = !gok || ballot64(lane < cnt && len > cap) != 0ull;
+    if (lane < cnt) {
+      nl_len[pi] = len;
+      grp_of[pi] = g;
+    }
+    if (bad && lane == 0 && atomicCAS(&gflag[g], 0, 1) == 0) {
+      flag_list[atomicAdd(&ds->n_flagged, 1)] = g;
+      ++nflag;
+    }
+    __syncthreads();  // the packed candidates are refilled next
+  }
+  if (lane == 0) {
+    WaveTally& tally = my_tally(ds);
+    if (cands) atomicAdd(&tally.n_cand_density, cands);
+    if (cands) atomicAdd(&tally.tot_cand_lists, cands);
+    if (nflag) {
+      atomicOr(&ds->lists_missing, 1);
+      atomicAdd(&ds->n_flag_rows, nflag);
+    }
+  }
 }
 
 // ============================================================================
@@ -2882,14 +3077,6 @@ __device__ __forceinline__ GroupRange xcd_groups(int ng) {
 // 294,912 292 -> 216 us, FP64 M4 10^6 945 -> 654 us, mixed M4 16.8M 6657 ->
 // 5907 us.
 // ============================================================================
-// Marks a loaded value as used here whatever becomes of it, so that the
-// compiler neither sinks its load into a later condition nor serialises a
-// batch of loads that are meant to be in flight together.
-template <typename T>
-__device__ __forceinline__ void loaded(T& v) {
-  asm volatile("" : "+v"(v));
-}
-
 // Wavefronts per SIMD the list density kernel is compiled for.
 constexpr int density_waves(bool mixed, int entries) { return mixed ? (entries > 16 ? 3 : 4) : (entries > 16 ? 2 : 3); }
 
@@ -3482,6 +3669,7 @@ __global__ void k_set_leaf_state(DevState* ds, int v) {
     ds->n_flag_rows = 0;
     ds->n_flag_grew = 0;
     ds->n_flagged = 0;
+    ds->pool_used = 0;
   }
 }
 
@@ -3507,6 +3695,7 @@ __device__ __forceinline__ void clear_counters(DevState* ds) {
     ds->n_flag_rows = 0;
     ds->n_flag_grew = 0;
     ds->n_flagged = 0;
+    ds->pool_used = 0;
   }
 }
 
@@ -3882,19 +4071,31 @@ hipError_t launch_density(sph_ctx* c, const sph_particles* s, bool flagged_only)
 
 hipError_t launch_lists(sph_ctx* c, const sph_particles* s) {
   c->kp.n = c->n;
-  const Parts p = parts_of(s);
-  const dim3 grid(c->walk_blocks), block(64);
-  if (c->kp.precision == SPH_PREC_MIXED) {
-    SPH_LPI_SWITCH_LISTS(c->kp.n_group,
-                         launch_last(c, (k_lists<true, LPI>), grid, block, c->kp, p, c->wnode,
-                                     c->ginfo, c->nl_idx, c->nl_len, c->gflag, c->flag_list,
-                                     c->grp_of, c->qrec, c->walk_spill, c->ds));
-  } else {
-    SPH_LPI_SWITCH_LISTS(c->kp.n_group,
-                         launch_last(c, (k_lists<false, LPI>), grid, block, c->kp, p, c->wnode,
-                                     c->ginfo, c->nl_idx, c->nl_len, c->gflag, c->flag_list,
-                                     c->grp_of, c->qrec, c->walk_spill, c->ds));
-  }
+  const int nblk = (c->n + kTreeTile - 1) / kTreeTile;
+  // the units' leaf lists take the walking density's leaf-list pool, which that
+  // kernel fills only later; single groups' lists the permute's staging space,
+  // which is free between two tree builds
+  int2* sg_list = c->leaf_pool;
+  const int64_t sg_entries = c->pool_cap;
+  int2* pool = reinterpret_cast<int2*>(c->gtmp);
+  // and the groups' offsets and lengths the sort's second buffers
+  int32_t* ll_off = reinterpret_cast<int32_t*>(c->keys[1]);
+  int32_t* ll_cnt = reinterpret_cast<int32_t*>(c->vals[1]);
+  const int pool_cap = (int)std::min<int64_t>((int64_t)kMaxFields * c->n_max, 0x7fffffff);
+  // As many wavefronts as are resident at once: the items go round them, and a
+  // second generation of wavefronts would run alone at the end (k_rows asked
+  // for 8 per SIMD with 6 resident: 428 us instead of 362 at 10^6 particles).
+  // The walk wavefronts' spill space is shared out over k_leaves' wavefronts.
+  const int grid = kLeafWaves * 4 * c->n_cu / 8 * 8;
+  const int row_grid = kRowWaves * 4 * c->n_cu / 8 * 8;
+  const int spill_cap = (int)((int64_t)kSpill * c->walk_blocks / grid);
+  hipLaunchKernelGGL(k_leaves, dim3(grid), dim3(64), 0, c->stream, c->kp, c->wnode, c->ginfo,
+                     c->tree_cnt, nblk, sg_list, sg_entries, pool, pool_cap, ll_off, ll_cnt,
+                     c->gflag, c->walk_spill, spill_cap, c->ds);
+  const auto rows = c->kp.precision == SPH_PREC_MIXED ? k_rows<true> : k_rows<false>;
+  launch_last(c, rows, dim3(row_grid), dim3(64), c->kp, s->h, c->wnode, c->ginfo, sg_list,
+              sg_entries, grid, pool, ll_off, ll_cnt, c->nl_idx, c->nl_len, c->gflag,
+              c->flag_list, c->grp_of, c->qrec, c->xyzm, c->ds);
   return hipGetLastError();
 }
 

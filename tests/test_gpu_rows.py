@@ -50,3 +50,45 @@ def test_density_of_ragged_rows(n, kernel, n_group, precision):
         e = float(rel_err(out[k], o[k]).max())
         say(f"  {k}: {e:.2e}")
         assert e <= t, (k, e)
+
+
+def blobs(n, seed, clump=0):
+    """Two jittered blobs in opposite corners of an open box (the curve jumps
+    between them), with `clump` particles of one at one point: coincident
+    keys, so a level-21 leaf of that many particles."""
+    cfg = cloud(n, "m4", seed)
+    rng = np.random.default_rng(seed)
+    for k in "xyz":
+        x = 0.2 + 0.2 * (cfg[k] - 0.25)
+        x[n // 2:] += 0.6
+        cfg[k] = np.ascontiguousarray(x)
+    cfg["h"] = 0.2 * cfg["h"]
+    if clump:
+        at = rng.integers(0, n // 2)
+        for k in "xyz":
+            cfg[k][:clump] = cfg[k][at]
+    return cfg
+
+
+@pytest.mark.parametrize("precision", [sph.SPH_PREC_FP64, sph.SPH_PREC_MIXED])
+@pytest.mark.parametrize("n_group", [4, 8])
+@pytest.mark.parametrize("n,clump", [(1, 0), (8, 0), (70, 0), (1500, 0), (1500, 65), (1500, 110)])
+def test_rows_hold_the_walks_sets(n, clump, n_group, precision):
+    """The pairs the rows give are the exact sets of the group walk: one group,
+    several wavefronts per group, units cut at a jump of the curve, and leaves
+    of more than 64 coincident particles (clump 110: more than a row holds with
+    its other neighbours, so flagged groups)."""
+    cfg = blobs(n, 3 + n, clump)
+    cfg["n_group"] = n_group
+    say(f"[rows] n={n} clump={clump} n_group={n_group} precision={precision}")
+    parts = sph.Particles(cfg)
+    ctx = sph.Context(sph.make_params(cfg, precision, h_tol=-1.0), n)
+    sph.sph_build_tree(ctx, parts)
+    sph.sph_density(ctx, parts)
+    sph.sph_check(ctx)
+    for mode in (0, 1):
+        off, idx = sph.sph_list_pairs(ctx, parts, mode)
+        woff, widx = sph.sph_neighbours(ctx, parts, mode)
+        np.testing.assert_array_equal(off, woff)
+        np.testing.assert_array_equal(idx, widx)
+    ctx.close()
