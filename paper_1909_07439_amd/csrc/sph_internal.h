@@ -221,6 +221,89 @@ __device__ __forceinline__ int wave_max_i32(int v) {
   return v;
 }
 
+// ---- gathers of per-particle records through LDS ------------------------------
+// A wavefront gathers one record of 16 RB bytes per lane.  Loaded by its own
+// lane, a record costs the L1 an access per 16 bytes and lane (each dwordx4 of
+// 64 scattered lanes takes the L1 about 40 cycles); here RB consecutive lanes
+// load one record's bytes together, straight into LDS (64 bytes per access),
+// and each lane then reads its record from there.  The pieces of a record sit
+// permuted (slot = piece ^ key) so that the reads of 8 consecutive lanes fall
+// in distinct banks.
+typedef int Piece __attribute__((ext_vector_type(4)));
+
+template <int RB>
+struct LdsGather {
+  static_assert(RB == 4 || RB == 8, "records of 64 or 128 bytes");
+  static constexpr int kBytes = 64 * 16 * RB;  // LDS of one set of 64 records
+  const char* base;  // the records, at this lane's piece
+  int src;           // ds_bpermute address of the first load's source lane
+  uint32_t at0;      // LDS address of this lane's piece 0
+
+  // lds: this wavefront's buffer of kBytes, aligned to a record
+  __device__ __forceinline__ LdsGather(const void* records, char* lds, int lane) {
+    base = static_cast<const char*>(records) + 16 * ((lane & (RB - 1)) ^ ((lane >> 3) & (RB - 1)));
+    src = 4 * (lane / RB);
+    const uint32_t a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+    const int key = RB == 4 ? (lane >> 1) & 3 : lane & 7;
+    at0 = a + 16u * (uint32_t)(RB * lane + key);
+  }
+
+  // Starts the loads of record j of every lane (none if j < 0) into the buffer
+  // `buf`; every earlier read of it is complete (read() waits).
+  __device__ __forceinline__ void start(char* buf, int j) const {
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      const int je = __builtin_amdgcn_ds_bpermute(src + q * (4 * 64 / RB), j);
+      if (je >= 0)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(base + (int64_t)je * (16 * RB)),
+            (__attribute__((address_space(3))) void*)(buf + q * 1024), 16, 0, 0);
+    }
+  }
+
+  // All loads started so far are in LDS (and all other loads done).
+  static __device__ __forceinline__ void wait() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+
+  // This lane's record.  The reads and their wait are one statement: the next
+  // start() overwrites the buffer.
+  __device__ __forceinline__ void read(Piece (&r)[RB]) const {
+    // piece k sits at slot k ^ key of the (aligned) record: its address is
+    // piece 0's with the bits of 16 k flipped
+    uint32_t at[RB];
+#pragma unroll
+    for (int k = 0; k < RB; ++k) at[k] = at0 ^ (16u * (uint32_t)k);
+    if constexpr (RB == 4) {
+      asm volatile(
+          "ds_read_b128 %0, %4\n\t"
+          "ds_read_b128 %1, %5\n\t"
+          "ds_read_b128 %2, %6\n\t"
+          "ds_read_b128 %3, %7\n\t"
+          "s_waitcnt lgkmcnt(0)"
+          : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+          : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3])
+          : "memory");
+    } else {
+      asm volatile(
+          "ds_read_b128 %0, %8\n\t"
+          "ds_read_b128 %1, %9\n\t"
+          "ds_read_b128 %2, %10\n\t"
+          "ds_read_b128 %3, %11\n\t"
+          "ds_read_b128 %4, %12\n\t"
+          "ds_read_b128 %5, %13\n\t"
+          "ds_read_b128 %6, %14\n\t"
+          "ds_read_b128 %7, %15\n\t"
+          "s_waitcnt lgkmcnt(0)"
+          : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]),
+            "=&v"(r[6]), "=&v"(r[7])
+          : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "v"(at[5]), "v"(at[6]),
+            "v"(at[7])
+          : "memory");
+    }
+  }
+};
+
 // Order-preserving map of doubles to unsigned 64-bit integers, so that
 // atomicMin / atomicMax on the integers implement min / max on the doubles.
 __host__ __device__ __forceinline__ unsigned long long enc_f64(double x) {

@@ -1657,6 +1657,34 @@ __device__ __forceinline__ bool exact_pair(const KParams& kp, const double* __re
   return r2 < sr * sr;
 }
 
+// The same, one axis at a time: a rare test inside a loop whose registers it
+// must not raise.
+__device__ __forceinline__ bool exact_pair_lean(const KParams& kp, const double* __restrict__ x,
+                                                const double* __restrict__ y,
+                                                const double* __restrict__ z,
+                                                const double* __restrict__ h, int i, int j) {
+  loaded(i);  // its addresses are not kept for the loop
+  double r2;
+  {
+    const double d = fold(x[i] - x[j], kp.len[0], kp.half[0], kp.periodic[0]);
+    r2 = d * d;
+    loaded(r2);
+  }
+  {
+    const double d = fold(y[i] - y[j], kp.len[1], kp.half[1], kp.periodic[1]);
+    r2 = fma(d, d, r2);
+    loaded(r2);
+  }
+  {
+    const double d = fold(z[i] - z[j], kp.len[2], kp.half[2], kp.periodic[2]);
+    r2 = fma(d, d, r2);
+    loaded(r2);
+  }
+  const double hi = h[i], hj = h[j];
+  const double sr = kp.support * (hj > hi ? hj : hi);
+  return r2 < sr * sr;
+}
+
 // FP32 pair tests of the mixed mode lie within about 1e-6 (relative) of the
 // FP64 ones; a test this close to the boundary is settled by exact_pair.
 constexpr float kBorder = 4e-5f;
@@ -1673,9 +1701,9 @@ constexpr float kBorder = 4e-5f;
 // and stores the group's leaf list, so that the force pass can replay it.
 // ============================================================================
 
-// This block's set of counters.
+// This wavefront's set of counters.
 __device__ __forceinline__ WaveTally& my_tally(DevState* ds) {
-  return ds->tally[blockIdx.x % kTallies];
+  return ds->tally[(blockIdx.x + gridDim.x * (threadIdx.x / kWave)) % kTallies];
 }
 
 // Courant minimum of a tally: the atomic is skipped when the stored value is
@@ -2429,6 +2457,17 @@ __device__ __forceinline__ GroupRange xcd_groups(int ng) {
   const int chunk = (ng + 7) >> 3;
   const int gbeg = xcd * chunk;
   return GroupRange{gbeg + local, min(gbeg + chunk, ng), nloc};
+}
+
+// The same for blocks of WPB wavefronts, which take WPB consecutive items at a
+// time: what their neighbourhoods share then stays in the CU's L1.
+template <int WPB>
+__device__ __forceinline__ GroupRange xcd_items(int n) {
+  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, nloc = gridDim.x >> 3;
+  const int chunk = (((n + 7) >> 3) + WPB - 1) / WPB * WPB;
+  const int beg = xcd * chunk;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  return GroupRange{beg + local * WPB + wave, min(beg + chunk, n), nloc * WPB};
 }
 
 // ============================================================================
@@ -3339,9 +3378,25 @@ void k_density_lists(KParams kp, Parts p,
 // to every entry; accepted pairs add the pressure, viscosity and conductivity
 // terms.  Runs only while every row is complete (leaf_state 1); flagged
 // groups are left to the walking kernel.
+//
+// Was bound by the L1's access rate (one access per cycle and CU, all cycles
+// taken): each lane loaded its own 64- or 128-byte record, four or eight
+// 16-byte loads of 64 scattered lanes each.  The records now come through LDS,
+// a record's bytes loaded by neighbouring lanes (LdsGather); FP64 10^6 1207 ->
+// 835 us, FP64 Wendland C6 294,912 792 -> 529, mixed 16.8M 7.46 -> 6.65 ms,
+// mixed 10^6 460 -> 401 us, mixed M6 294,912 240 -> 218.  A second buffer per
+// wavefront (the next records in flight during the pair terms) costs FP64 half
+// its wavefronts (835 -> 998 us) and gains the mixed form nothing over a fifth
+// wavefront per SIMD.
 // ============================================================================
+// Blocks of four wavefronts take neighbouring chunks, which share L1 lines
+// (one wavefront per block: 3 % slower).
+constexpr int kForceWpb = 4;
+// Wavefronts per SIMD: what the registers allow without spilling.
+constexpr int force_waves(bool mixed) { return mixed ? 5 : 4; }
+
 template <bool MIXED, int LPI, int KIND>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ __launch_bounds__(kWave * kForceWpb) __attribute__((amdgpu_waves_per_eu(force_waves(MIXED))))
 void k_force_lists(KParams kp, Parts p,
                                                     const GroupInfo* __restrict__ groups,
                                                     const void* __restrict__ frec_in,
@@ -3355,35 +3410,63 @@ void k_force_lists(KParams kp, Parts p,
                                                     double* __restrict__ out_du,
                                                     DevState* __restrict__ ds) {
   if (ds->leaf_state != 1) return;
+  constexpr int RB = MIXED ? 4 : 8;   // 16-byte pieces of a record
+  using Gather = LdsGather<RB>;
+  __shared__ alignas(128) char s_rec[kForceWpb][Gather::kBytes];
   using Rec = typename FRecOf<MIXED>::T;
   const Rec* __restrict__ rec = reinterpret_cast<const Rec*>(frec_in);
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x % kWave;
   const int slot = lane / LPI, sub = lane % LPI;
   constexpr int CS = kWave / LPI;  // particles per chunk
   const int nch = (kp.n + CS - 1) / CS;
-  const GroupRange gr = xcd_groups(nch);
+  const GroupRange gr = xcd_items<kForceWpb>(nch);
   uint32_t err = 0;
-  unsigned long long pairs = 0, cands = 0;
+  uint32_t pairs = 0, cands = 0;  // this lane's: n / (64 wavefronts) rows of at most 256
   double dtmin = SPH_INF;
+  char* const rec_lds = s_rec[__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave)];
+  const Gather gather(rec, rec_lds, lane);
+  const bool any_flag = ds->n_flagged != 0;
 
   for (int g = gr.beg; g < gr.end; g += gr.step) {
     const int first = g * CS, count = min(CS, kp.n - first);
     const bool inr = slot < count;
     const int i = first + (inr ? slot : 0);
     // particles of flagged groups are left to the walking kernel
-    const bool act = inr && gflag[grp_of[i]] == 0;
-    if (ballot64(act) == 0ull) continue;
-    const double xi = p.x[i], yi = p.y[i], zi = p.z[i], hi = p.h[i];
+    const bool act = inr && (!any_flag || gflag[grp_of[i]] == 0);
+    if (any_flag && ballot64(act) == 0ull) continue;
     const Rec ri = rec[i];
-    const int len = act ? nl_len[i] : 0;
-    const int32_t* __restrict__ row = nl_idx + (int64_t)i * kp.nl_cap;
-    int lmax = len;
-    for (int d = 32; d > 0; d >>= 1) lmax = max(lmax, __shfl_xor(lmax, d, kWave));
-    cands += (act && sub == 0) ? (unsigned long long)len : 0ull;
+    int len = nl_len[i];
+    loaded(len);
+    len = act ? len : 0;
+    const int32_t* __restrict__ row = nl_idx + ((int64_t)i * kp.nl_cap + sub);
+    const int lmax = __builtin_amdgcn_readfirstlane(wave_max_i32(len));
+    cands += (act && sub == 0) ? (uint32_t)len : 0u;
     double ax = 0.0, ay = 0.0, az = 0.0, du = 0.0, vmax = 0.0;
+    // body(record, index) for this lane's share of the row (index -1 past its
+    // end), in order, one record per lane at a time; the indices are loaded
+    // one set ahead.
+    auto rows_loop = [&](auto body) {
+      int k = sub;
+      auto index = [&]() {     // of the next entry (within the row's nl_cap entries)
+        const int j = row[0];
+        k += LPI;
+        row += k < kp.nl_cap ? LPI : 0;
+        return j;
+      };
+      int next = index();
+      for (int k0 = 0; k0 < lmax; k0 += LPI) {
+        const int j = k - LPI < len ? next : -1;
+        gather.start(rec_lds, j);
+        next = index();
+        Gather::wait();
+        Piece pc[RB];
+        gather.read(pc);
+        body(__builtin_bit_cast(Rec, pc), j);
+      }
+    };
     if constexpr (MIXED) {
       const float al = (float)kp.alpha, be = (float)kp.beta, hau = (float)(0.5 * kp.alpha_u);
-      const float vxi = ri.vx, vyi = ri.vy, vzi = ri.vz, hif = (float)hi;
+      const float vxi = ri.vx, vyi = ri.vy, vzi = ri.vz, hif = (float)p.h[i];
       const float hinvi = ri.hinv, h4i = ri.hinv4pi, gi = ri.g, ki = ri.k;
       const float Pi = ri.P, rhoi = ri.rho, ui = ri.u;
       const float aci = al * ri.c, nhki = -0.5f * ki, S = (float)kp.support;
@@ -3410,7 +3493,7 @@ void k_force_lists(KParams kp, Parts p,
         bool in = r2 < sr2;
         const bool border = fabsf(r2 - sr2) <= kBorder * sr2;
         if (ballot64(border) != 0ull)
-          if (border) in = exact_pair(kp, p.x, p.y, p.z, p.h, i, j, true);
+          if (border) in = exact_pair_lean(kp, p.x, p.y, p.z, p.h, i, j);
         if (!in) return;
         ++npr;
         const float rinv = __builtin_amdgcn_rsqf(r2);
@@ -3434,23 +3517,9 @@ void k_force_lists(KParams kp, Parts p,
         fdu = fmaf(w, Ai, fmaf(hau * vu * (ui - rj.u), X, fdu));
         fvmax = fmaxf(fvmax, vsi);
       };
-      // row indices one iteration ahead, so that each iteration waits for
-      // one gather of the two records only
-      int j1 = (sub < len) ? row[sub] : i;
-      int j2 = (sub + LPI < len) ? row[sub + LPI] : i;
-      for (int k = sub; k < lmax; k += 2 * LPI) {
-        const bool v1 = k < len, v2 = k + LPI < len;
-        Rec r1, r2;
-        if (v1) r1 = rec[j1];
-        if (v2) r2 = rec[j2];
-        const int kn = k + 2 * LPI;
-        const int jn1 = (kn < len) ? row[kn] : i;
-        const int jn2 = (kn + LPI < len) ? row[kn + LPI] : i;
-        if (v1 && j1 != i) pair(r1, j1);
-        if (v2 && j2 != i) pair(r2, j2);
-        j1 = jn1;
-        j2 = jn2;
-      }
+      rows_loop([&](const Rec& rj, int j) {
+        if (j >= 0 && j != i) pair(rj, j);
+      });
       ax = fax;
       ay = fay;
       az = faz;
@@ -3462,6 +3531,7 @@ void k_force_lists(KParams kp, Parts p,
       const double vxi = ri.vx, vyi = ri.vy, vzi = ri.vz;
       const double hinvi = ri.hinv, h4i = ri.hinv4pi, gi = ri.g, ki = ri.k, ci = ri.c;
       const double Pi = ri.P, rhoi = ri.rho, ui = ri.u;
+      const double xi = ri.x, yi = ri.y, zi = ri.z, hi = p.h[i];
       auto pair = [&](const Rec& rj) {
         const double dx = fold(xi - rj.x, kp.len[0], kp.half[0], kp.periodic[0]);
         const double dy = fold(yi - rj.y, kp.len[1], kp.half[1], kp.periodic[1]);
@@ -3494,16 +3564,9 @@ void k_force_lists(KParams kp, Parts p,
         du += e;
         vmax = fmax(vmax, vsi);
       };
-      // one 128-byte record in flight per lane (registers); row index one
-      // iteration ahead
-      int j = (sub < len) ? row[sub] : i;
-      for (int k = sub; k < lmax; k += LPI) {
-        const bool v = k < len;
-        const Rec rj = rec[j];
-        const int jn = (k + LPI < len) ? row[k + LPI] : i;
-        if (v && j != i) pair(rj);
-        j = jn;
-      }
+      rows_loop([&](const Rec& rj, int j) {
+        if (j >= 0 && j != i) pair(rj);
+      });
     }
     ax = seg_sum<LPI>(ax);
     ay = seg_sum<LPI>(ay);
@@ -3521,7 +3584,7 @@ void k_force_lists(KParams kp, Parts p,
         out_du[i] = du;
         p.vsig[i] = vs;
       }
-      dtmin = fmin(dtmin, kp.c_cour * hi / vs);
+      dtmin = fmin(dtmin, kp.c_cour * p.h[i] / vs);
     }
   }
   const uint64_t b = ballot64(err != 0);
@@ -4180,7 +4243,8 @@ hipError_t launch_force(sph_ctx* c, const sph_particles* s, bool step_mode, bool
 
 template <bool MIXED, int KIND>
 static void force_lists_kind(sph_ctx* c, const Parts& p, double* const* o) {
-  const dim3 grid(c->walk_blocks), block(64);
+  const int waves = force_waves(MIXED) * 4 * c->n_cu;  // resident at once
+  const dim3 grid(std::max(waves / kForceWpb / 8 * 8, 8)), block(kWave * kForceWpb);
   SPH_LPI_SWITCH_LISTS(c->kp.n_group,
                        launch_last(c, (k_force_lists<MIXED, LPI, KIND>), grid, block, c->kp, p,
                                    c->ginfo, c->frec, c->nl_idx, c->nl_len, c->gflag, c->grp_of,
