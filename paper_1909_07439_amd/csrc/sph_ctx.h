@@ -105,7 +105,7 @@ struct sph_ctx {
   int32_t* nb_cnt = nullptr;   // neighbour-export counts
   int64_t* nb_off = nullptr;   // neighbour-export offsets (device)
   double* red_part = nullptr;  // reduction partials
-  double* red_out = nullptr;   // 12 results
+  double* red_out = nullptr;   // 12 results (pinned host memory, behind hs)
   sph::DevState* ds = nullptr;
   sph::DevState* hs = nullptr;  // pinned host mirror
   struct sph_timing* tm = nullptr;  // phase events (host code)

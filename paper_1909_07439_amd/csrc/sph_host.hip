@@ -355,10 +355,12 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   ALLOC(c->nb_cnt, N);
   ALLOC(c->nb_off, N + 1);
   ALLOC(c->red_part, 512 * 12);
-  ALLOC(c->red_out, 16);
   ALLOC(c->ds, 1);
-  e = hipHostMalloc((void**)&c->hs, sizeof(sph::DevState), hipHostMallocDefault);
+  // pinned: the mirror of the device state, then the results of sph_reduce
+  e = hipHostMalloc((void**)&c->hs, sizeof(sph::DevState) + 16 * sizeof(double),
+                    hipHostMallocDefault);
   if (e != hipSuccess) return bail(e, "hipHostMalloc");
+  c->red_out = reinterpret_cast<double*>(c->hs + 1);
   memset(c->hs, 0, sizeof(sph::DevState));
   for (sph::WaveTally& t : c->hs->tally) t.dt_min_enc = sph::enc_f64(__builtin_huge_val());
   e = hipMemcpyAsync(c->ds, c->hs, sizeof(sph::DevState), hipMemcpyHostToDevice, c->stream);
@@ -402,7 +404,7 @@ void sph_destroy(sph_ctx* c) {
                   c->node_level, c->node_first, c->node_count,   c->node_parent, c->node_child,
                   c->node_nchild, c->chunk_box, c->wnode,       c->grp_first,
                   c->grp_count, c->ginfo,       c->frec,         c->a1,          c->nb_cnt,
-                  c->nb_off,    c->red_part,    c->red_out,      c->ds,
+                  c->nb_off,    c->red_part,    c->ds,
                   c->leaf_pool, c->gl_off,      c->gl_cnt,       c->nl_idx,      c->nl_len,
                   c->gflag,     c->flag_list,   c->walk_spill,   c->grp_of,    c->qrec,
                   c->adj_abar,  c->adj_raw,     c->adj_ab,       c->xyzm,
@@ -651,8 +653,8 @@ sph_status sph_reduce(sph_ctx* c, const sph_particles* p, double out[12]) {
   sph_status st = check_parts(c, p, true, false);
   if (st != SPH_OK) return st;
   HIPCHK(c, sph::launch_reduce(c, p, c->red_out));
-  HIPCHK(c, hipMemcpyAsync(out, c->red_out, 12 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  memcpy(out, c->red_out, 12 * sizeof(double));
   return SPH_OK;
 }
 

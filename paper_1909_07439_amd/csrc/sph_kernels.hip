@@ -3830,14 +3830,24 @@ __global__ __launch_bounds__(256) void k_reduce_part(Parts p, int n, double* __r
   if (threadIdx.x < 12) part[blockIdx.x * 12 + threadIdx.x] = s[threadIdx.x][0];
 }
 
-__global__ void k_reduce_final(const double* __restrict__ part, double* __restrict__ out) {
-  if (threadIdx.x < 12) {
-    double a = 0.0;
-    for (int b = 0; b < kRedBlocks; ++b) a += part[b * 12 + threadIdx.x];
-    out[threadIdx.x] = a;
-  }
+// The block sums added in block order.  A chain of 512 dependent additions per
+// sum: from LDS, where the whole block loads the partials first (read one by
+// one from memory they took 13 us; 7 us so).
+constexpr int kRedParts = kRedBlocks * 12;
+__global__ __launch_bounds__(512) void k_reduce_final(const double* __restrict__ part,
+                                                       double* __restrict__ out) {
+  __shared__ double s[kRedParts];
+  for (int k = threadIdx.x; k < kRedParts; k += 512) s[k] = part[k];
   __syncthreads();
-  if (threadIdx.x == 0) out[0] = out[1] + out[2];
+  double a = 0.0;
+  if (threadIdx.x < 12) {
+#pragma unroll 32
+    for (int b = 0; b < kRedBlocks; ++b) a += s[b * 12 + threadIdx.x];
+  }
+  // E = E_kin + E_th
+  const double th = __shfl(a, 2, kWave), kin = __shfl(a, 1, kWave);
+  if (threadIdx.x == 0) a = kin + th;
+  if (threadIdx.x < 12) out[threadIdx.x] = a;
 }
 
 // ============================================================================
@@ -4306,17 +4316,18 @@ hipError_t reduce_noalloc(const sph_particles* s, hipStream_t stream, double* ou
   double* res = base + kRedBlocks * 12;
   hipLaunchKernelGGL(k_reduce_part, dim3(kRedBlocks), dim3(256), 0, stream, parts_of(s),
                      (int)s->n, part);
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64), 0, stream, part, res);
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(512), 0, stream, part, res);
   e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(out, res, 12 * sizeof(double), hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   return e;
 }
 
-hipError_t launch_reduce(sph_ctx* c, const sph_particles* s, double* dev_out) {
+// out: memory the device writes and the host reads (pinned).
+hipError_t launch_reduce(sph_ctx* c, const sph_particles* s, double* out) {
   hipLaunchKernelGGL(k_reduce_part, dim3(kRedBlocks), dim3(256), 0, c->stream, parts_of(s),
                      (int)s->n, c->red_part);
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64), 0, c->stream, c->red_part, dev_out);
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(512), 0, c->stream, c->red_part, out);
   return hipGetLastError();
 }
 
