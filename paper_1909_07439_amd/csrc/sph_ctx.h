@@ -70,8 +70,9 @@ struct sph_ctx {
   uint8_t* lleaf = nullptr;
   uint8_t* gsize = nullptr;  // particles of the group starting at each particle (0 elsewhere)
   uint8_t* gstart = nullptr;
-  uint32_t* tree_cnt = nullptr;  // kLevels * blocks (level-major), scanned in place
-  uint32_t* grp_cnt = nullptr;   // blocks
+  // node counts per level and block (level-major), then group counts per
+  // block; scanned in place
+  uint32_t* tree_cnt = nullptr;
   int64_t node_cap = 0;
   int32_t* node_level = nullptr;
   int32_t* node_first = nullptr;

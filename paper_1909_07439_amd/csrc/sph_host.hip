@@ -302,7 +302,7 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   const int64_t N = n_max;
   const int64_t nblk_sort = (N + sph::kSortTile - 1) / sph::kSortTile;
   const int64_t nblk_tree = (N + sph::kTreeTile - 1) / sph::kTreeTile;
-  const int64_t scan_max = std::max<int64_t>(256 * nblk_sort, sph::kLevels * nblk_tree);
+  const int64_t scan_max = std::max<int64_t>(256 * nblk_sort, (sph::kLevels + 1) * nblk_tree + 4);
   ALLOC(c->keys[0], N);
   ALLOC(c->keys[1], N);
   ALLOC(c->vals[0], N);
@@ -321,8 +321,7 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   ALLOC(c->lleaf, N);
   ALLOC(c->gsize, N);
   ALLOC(c->gstart, N);
-  ALLOC(c->tree_cnt, sph::kLevels * nblk_tree);
-  ALLOC(c->grp_cnt, nblk_tree);
+  ALLOC(c->tree_cnt, (sph::kLevels + 1) * nblk_tree + 4);
   c->node_cap = 2 * N + 1024;
   ALLOC(c->node_level, c->node_cap);
   ALLOC(c->node_first, c->node_cap);
@@ -400,7 +399,7 @@ void sph_destroy(sph_ctx* c) {
   }
   void* ptrs[] = {c->keys[0],   c->keys[1],     c->vals[0],      c->vals[1],     c->radix_cnt,
                   c->scan_part, c->scan_total,  c->gtmp,         c->gtmp_id,     c->dlev,
-                  c->lleaf,     c->gsize,        c->gstart,       c->tree_cnt,    c->grp_cnt,
+                  c->lleaf,     c->gsize,        c->gstart,       c->tree_cnt,
                   c->node_level, c->node_first, c->node_count,   c->node_parent, c->node_child,
                   c->node_nchild, c->chunk_box, c->wnode,       c->grp_first,
                   c->grp_count, c->ginfo,       c->frec,         c->a1,          c->nb_cnt,

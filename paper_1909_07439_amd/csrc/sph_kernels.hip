@@ -602,12 +602,21 @@ __device__ __forceinline__ int diff_level(uint64_t a, uint64_t b) {
 }
 
 __device__ __forceinline__ int window_level(const uint8_t* d, int idx, int s, int n, int T) {
-  int run = d[idx];
+  int run = 22;  // d is 0 at the first particle and before
   int best = 22;
-  for (int k = 0; k < T; ++k) {
-    if (k > 0 && s - k >= 0) run = min(run, (int)d[idx - k]);
-    const int b = s + T - k;
-    if (b <= n) best = min(best, max((int)d[idx + T - k], run));
+  for (int k = 0; k < T; k += 8) {  // loads of eight steps at a time
+    int dl[8], dr[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int q = min(k + u, T - 1);
+      dl[u] = d[idx - q];
+      dr[u] = s + T - q <= n ? d[idx + T - q] : 22;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {  // a repeated last step changes nothing
+      run = min(run, dl[u]);
+      best = min(best, max(dr[u], run));
+    }
   }
   return best;
 }
@@ -737,8 +746,7 @@ __global__ __launch_bounds__(256) void k_tree_levels(const uint64_t* __restrict_
                                                       uint8_t* __restrict__ lleaf,
                                                       uint8_t* __restrict__ gsize,
                                                       uint8_t* __restrict__ gstart,
-                                                      uint32_t* __restrict__ tree_cnt,
-                                                      uint32_t* __restrict__ grp_cnt, int nblk,
+                                                      uint32_t* __restrict__ tree_cnt, int nblk,
                                                       int32_t* __restrict__ nnchild,
                                                       int64_t node_cap) {
   __shared__ uint8_t d[kTreeTile + 2 * kHalo + 1];
@@ -817,21 +825,33 @@ __global__ __launch_bounds__(256) void k_tree_levels(const uint64_t* __restrict_
     if (start) atomicAdd(&gc, 1u);
   }
   __syncthreads();
+  // the group counts follow the node counts of the levels, so that one scan
+  // does both (its length rounded up with zeros)
   if (threadIdx.x < kLevels) tree_cnt[threadIdx.x * nblk + blockIdx.x] = lc[threadIdx.x];
-  if (threadIdx.x == 0) grp_cnt[blockIdx.x] = gc;
+  if (threadIdx.x == 0) tree_cnt[kLevels * nblk + blockIdx.x] = gc;
+  if (blockIdx.x == 0 && threadIdx.x < 3) tree_cnt[(kLevels + 1) * nblk + threadIdx.x] = 0;
 }
 
+// tree_off: exclusive prefix of the node counts, level by level, then of the
+// group counts; total: nodes and groups together.
 __global__ __launch_bounds__(256) void k_tree_emit(
     const uint64_t* __restrict__ keys, int n, int n_group, const uint8_t* __restrict__ dlev,
     const uint8_t* __restrict__ lleaf, const uint8_t* __restrict__ gsize,
     const uint8_t* __restrict__ gstart, const uint32_t* __restrict__ tree_off,
-    const uint32_t* __restrict__ grp_off, int nblk, int64_t node_cap,
+    const uint32_t* __restrict__ total, int nblk, int64_t node_cap,
     int32_t* __restrict__ nlevel, int32_t* __restrict__ nfirst, int32_t* __restrict__ ncount,
     int32_t* __restrict__ nparent, int32_t* __restrict__ nchild, int32_t* __restrict__ nnchild,
     int32_t* __restrict__ gfirst, int32_t* __restrict__ gcount, DevState* __restrict__ ds) {
   __shared__ uint32_t wc[4][kLevels];
+  __shared__ uint32_t first[4][kLevels];  // index of a wavefront's first node of a level
   __shared__ uint32_t gw[4];
-  if ((int64_t)ds->n_nodes > node_cap || ds->n_nodes < 0) {
+  __shared__ uint8_t s_d[kTreeTile + kHalo];  // start levels from the tile's first particle on
+  const int n_nodes = (int)tree_off[kLevels * nblk];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ds->n_nodes = n_nodes;
+    ds->n_groups = (int)(*total - (uint32_t)n_nodes);
+  }
+  if ((int64_t)n_nodes > node_cap || n_nodes < 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&ds->err, kErrNodes);
     return;
   }
@@ -841,6 +861,12 @@ __global__ __launch_bounds__(256) void k_tree_emit(
   const int dsv = valid ? dlev[s] : 99;
   const int ll = valid ? lleaf[s] : -1;
   const bool gs = valid && gstart[s];
+  const uint32_t off = tid < kLevels ? tree_off[tid * nblk + blockIdx.x] : 0u;
+  s_d[tid] = valid ? (uint8_t)dsv : (uint8_t)0;  // a cell ends at the last particle
+  if (tid < kHalo) {
+    const int j = s + kTreeTile;
+    s_d[kTreeTile + tid] = j < n ? dlev[j] : (uint8_t)0;
+  }
   for (int l = 0; l < kLevels; ++l) {
     const uint64_t b = ballot64(valid && dsv <= l && l <= ll);
     if (lane == 0) wc[w][l] = (uint32_t)popc64(b);
@@ -848,20 +874,41 @@ __global__ __launch_bounds__(256) void k_tree_emit(
   const uint64_t bg = ballot64(gs);
   if (lane == 0) gw[w] = (uint32_t)popc64(bg);
   __syncthreads();
+  if (tid < kLevels) {
+    uint32_t f = off;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      first[q][tid] = f;
+      f += wc[q][tid];
+    }
+  }
+  __syncthreads();
+  // only leaves need their particle count (the walk reads particles of leaves
+  // only; inner counts are derived on the host for inspection).  A leaf that
+  // starts here ends where a cell of its level or above starts next: within
+  // n_leaf particles, unless it is a level-21 cell of coincident keys.
+  // Latency bound at small n: what a level needs is in LDS before the level
+  // loop (a galloping search of the keys from each leaf and a load of the
+  // offset per level were chains of dependent loads: 12.5 -> 6.8 us at 1000
+  // particles, 16.5 -> 11.0 at 294,912, 467 -> 295 at 16.8M).
+  int leaf_count = 0;
+  if (dsv <= ll) {
+    int t = tid + 1;
+    const int t1 = min(tid + kHalo, kTreeTile + kHalo - 1);
+    while (t < t1 && (int)s_d[t] > ll) ++t;
+    leaf_count = (int)s_d[t] <= ll ? t - tid : cell_end(keys, n, s, ll) - s;
+  }
   int prev = -1, par_at_d = -1;
   for (int l = 0; l < kLevels; ++l) {
+    if (ballot64(valid && dsv - 1 <= l && l <= ll) == 0ull) continue;
     const bool mem = valid && dsv <= l && l <= ll;
     const uint64_t b = ballot64(mem);
-    uint32_t r = (uint32_t)popc64(b & lanemask_lt());
-    for (int q = 0; q < w; ++q) r += wc[q][l];
-    const int idx = (int)(tree_off[l * nblk + blockIdx.x] + r);
+    const int idx = (int)(first[w][l] + (uint32_t)popc64(b & lanemask_lt()));
     if (valid && l == dsv - 1) par_at_d = idx - 1;  // last level-(d-1) node before s
     if (mem) {
       nlevel[idx] = l;
       nfirst[idx] = s;
-      // only leaves need their particle count (the walk reads particles of
-      // leaves only); inner counts are derived on the host for inspection
-      ncount[idx] = (l == ll) ? cell_end(keys, n, s, l) - s : 0;
+      ncount[idx] = (l == ll) ? leaf_count : 0;
       const int parent = (l == 0) ? -1 : (l == dsv ? par_at_d : prev);
       nparent[idx] = parent;
       nchild[idx] = -1;
@@ -873,7 +920,7 @@ __global__ __launch_bounds__(256) void k_tree_emit(
   uint32_t rg = (uint32_t)popc64(bg & lanemask_lt());
   for (int q = 0; q < w; ++q) rg += gw[q];
   if (gs) {
-    const int g = (int)(grp_off[blockIdx.x] + rg);
+    const int g = (int)(tree_off[kLevels * nblk + blockIdx.x] - (uint32_t)n_nodes + rg);
     gfirst[g] = s;
     gcount[g] = gsize[s];
   }
@@ -4007,14 +4054,13 @@ hipError_t launch_tree(sph_ctx* c) {
   const int nblk = (n + kTreeTile - 1) / kTreeTile;
   hipLaunchKernelGGL(k_tree_levels, dim3(nblk), dim3(256), 0, c->stream, c->keys[0], n,
                      c->kp.n_leaf, c->kp.n_group, c->dlev, c->lleaf, c->gsize, c->gstart,
-                     c->tree_cnt, c->grp_cnt, nblk, c->node_nchild, c->node_cap);
-  hipError_t e = scan_u32(c, c->tree_cnt, (int64_t)kLevels * nblk, nullptr, &c->ds->n_nodes);
-  if (e != hipSuccess) return e;
-  e = scan_u32(c, c->grp_cnt, nblk, nullptr, &c->ds->n_groups);
+                     c->tree_cnt, nblk, c->node_nchild, c->node_cap);
+  const int64_t counts = ((int64_t)(kLevels + 1) * nblk + 3) / 4 * 4;
+  const hipError_t e = scan_u32(c, c->tree_cnt, counts, c->scan_total, nullptr);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_tree_emit, dim3(nblk), dim3(256), 0, c->stream, c->keys[0], n,
                      c->kp.n_group, c->dlev, c->lleaf, c->gsize, c->gstart, c->tree_cnt,
-                     c->grp_cnt, nblk, c->node_cap, c->node_level, c->node_first,
+                     c->scan_total, nblk, c->node_cap, c->node_level, c->node_first,
                      c->node_count, c->node_parent, c->node_child, c->node_nchild,
                      c->grp_first, c->grp_count, c->ds);
   return hipGetLastError();  // node_props checks the node count (tree_guard)
@@ -4041,10 +4087,11 @@ static hipError_t node_props(sph_ctx* c, const sph_particles* s, int mode) {
   const int nb = (int)std::min<int64_t>(std::max<int64_t>((items / 4 + 15) / 16, 16), 4096);
   const int nbi =
       small ? (int)std::min<int64_t>(std::max<int64_t>((c->node_cap / 8 + 63) / 64, 16), 4096) : 0;
-  // the last launch of an h_max refresh stamps a phase boundary
+  // the last launch stamps a phase boundary: here, unless the mixed code
+  // records follow
   const bool mixed = c->kp.precision == SPH_PREC_MIXED;
   const hipEvent_t mark = c->mark;
-  c->mark = mode != 1 && small && !mixed ? mark : nullptr;
+  c->mark = small && !mixed ? mark : nullptr;
   launch_last(c, k_range_boxes, dim3(nb + nbi), dim3(256), s->x, s->y, s->z, s->h, c->node_first,
               c->node_count, c->node_child, c->node_nchild, c->wnode, c->grp_first, c->grp_count,
               c->ginfo, c->ds, mode, nb, n, c->chunk_box, c->node_parent);
@@ -4053,18 +4100,16 @@ static hipError_t node_props(sph_ctx* c, const sph_particles* s, int mode) {
     const int lb =
         (int)std::min<int64_t>(std::max<int64_t>((c->node_cap / 4 + 255) / 256, 1), 1024);
     for (int l = kLevels - 2; l >= 0; --l) {
-      c->mark = mode != 1 && l == 0 && !mixed ? mark : nullptr;
+      c->mark = l == 0 && !mixed ? mark : nullptr;
       launch_last(c, k_level_boxes, dim3(lb), dim3(256), l, c->tree_cnt, nblk, c->node_first,
                   c->node_child, c->node_nchild, c->wnode, c->ds, mode);
     }
   }
   // mixed: the code records with the current h and m (a new tree's after its
   // frame, below)
-  if (mode != 1 && mixed) {
+  if (mixed) {
     c->mark = mark;
-    pack_q(c, s, mode);
-  } else if (mode == 1) {
-    c->mark = mark;  // the caller's last launch stamps it
+    if (mode != 1) pack_q(c, s, mode);
   }
   return hipGetLastError();
 }
@@ -4075,13 +4120,10 @@ hipError_t launch_node_h(sph_ctx* c, const sph_particles* s, bool always) {
 hipError_t launch_node_boxes(sph_ctx* c, const sph_particles* s) {
   const hipError_t e = node_props(c, s, 1);
   if (e != hipSuccess) return e;
-  // the mixed code records need the frame (the FP64 packed positions come
-  // from the permute)
+  // the mixed code records and their frame (FP64 contexts have neither)
   if (c->kp.precision == SPH_PREC_MIXED) {
     hipLaunchKernelGGL(k_qframe, dim3(1), dim3(64), 0, c->stream, c->kp, c->wnode, c->ds);
     pack_q(c, s, 1);
-  } else {
-    launch_last(c, k_qframe, dim3(1), dim3(64), c->kp, c->wnode, c->ds);
   }
   return hipGetLastError();
 }
