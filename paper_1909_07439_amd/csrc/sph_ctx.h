@@ -9,6 +9,7 @@
 
 namespace sph {
 constexpr int kMaxFields = 20;
+constexpr int kSortHeadWords = 64;  // words of the radix sort's head
 constexpr int kSortTile = 2048;  // keys per radix-sort block (256 threads x 8)
 constexpr int kTreeTile = 256;   // particles per tree block
 constexpr int kScanTile = 2048;  // elements per scan block
@@ -56,7 +57,8 @@ struct sph_ctx {
   // sort
   uint64_t* keys[2] = {nullptr, nullptr};
   uint32_t* vals[2] = {nullptr, nullptr};
-  uint32_t* radix_cnt = nullptr;  // look-back status (8 passes x 256 x blocks), histograms, tickets
+  // look-back status (8 passes x 256 x blocks), histograms, head, key bits
+  uint32_t* radix_cnt = nullptr;
   int64_t n_max_sort_blocks = 0;
   uint32_t* scan_part = nullptr;  // block partials of the scans
   uint32_t* scan_total = nullptr; // scratch totals (several slots)

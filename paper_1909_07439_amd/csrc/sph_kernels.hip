@@ -252,47 +252,87 @@ __device__ __forceinline__ double wrap_coord(double v, double lo, double len, in
   return v;
 }
 
+// Prediction of particle i (optional) and its key.
+__device__ __forceinline__ uint64_t predict_key(const KParams& kp, const Parts& p, bool predict,
+                                                double dt, int i, bool& bad) {
+  double x = p.x[i], y = p.y[i], z = p.z[i];
+  if (predict) {
+    const double hdt2 = 0.5 * dt * dt;
+    const double vx = p.vx[i], vy = p.vy[i], vz = p.vz[i];
+    const double ax = p.ax[i], ay = p.ay[i], az = p.az[i];
+    x = wrap_coord(x + (vx * dt + hdt2 * ax), kp.lo[0], kp.len[0], kp.periodic[0]);
+    y = wrap_coord(y + (vy * dt + hdt2 * ay), kp.lo[1], kp.len[1], kp.periodic[1]);
+    z = wrap_coord(z + (vz * dt + hdt2 * az), kp.lo[2], kp.len[2], kp.periodic[2]);
+    p.x[i] = x;
+    p.y[i] = y;
+    p.z[i] = z;
+    p.vx[i] = vx + ax * dt;
+    p.vy[i] = vy + ay * dt;
+    p.vz[i] = vz + az * dt;
+    p.u[i] = p.u[i] + p.dudt[i] * dt;
+  }
+  bad |= !(isfinite(x) && isfinite(y) && isfinite(z));
+  const uint64_t ix = quantise(x, kp.lo[0], kp.key_scale);
+  const uint64_t iy = quantise(y, kp.lo[1], kp.key_scale);
+  const uint64_t iz = quantise(z, kp.lo[2], kp.key_scale);
+  return (spread3(ix) << 2) | (spread3(iy) << 1) | spread3(iz);
+}
+
+// Words of the radix sort besides the look-back status and the histograms.
+struct SortHead {
+  uint32_t tickets[8];     // next tile of every pass
+  uint32_t ticket;         // next item of k_resort
+  uint32_t done[9];        // tiles finished in every stage of k_resort
+  uint32_t shift;          // lowest key bit the passes sort
+  uint32_t resort;         // 1: a long run of equal sorted bits is out of order
+};
+
+__device__ __forceinline__ uint64_t wave_or_u64(uint64_t v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor((unsigned long long)v, o);
+  return v;
+}
+
 // Block 0 also clears the radix sort's digit histograms and tile tickets
-// (the sort follows at once).
+// (the sort follows at once); every block leaves the key bits that are set in
+// one of its keys and those that are clear in one (range[0], range[1]).
 __global__ __launch_bounds__(256) void k_predict_keys(KParams kp, Parts p, int predict,
                                                        const DevState* __restrict__ ds,
                                                        uint64_t* __restrict__ keys,
                                                        uint32_t* __restrict__ vals,
                                                        uint32_t* __restrict__ ghist,
-                                                       uint32_t* __restrict__ tickets,
+                                                       SortHead* __restrict__ head,
+                                                       uint64_t* __restrict__ range,
                                                        uint32_t* __restrict__ err) {
+  __shared__ uint64_t wr[4][2];
   if (blockIdx.x == 0) {
-    for (int k = threadIdx.x; k < 8 * 256; k += blockDim.x) ghist[k] = 0u;
-    if (threadIdx.x < 8) tickets[threadIdx.x] = 0u;
+    for (int k = threadIdx.x; k < 2 * 8 * 256; k += blockDim.x) ghist[k] = 0u;
+    uint32_t* hw = reinterpret_cast<uint32_t*>(head);
+    if (threadIdx.x < sizeof(SortHead) / 4) hw[threadIdx.x] = 0u;
   }
   const int n = kp.n;
   const double dt = predict ? ds->dt_cur : 0.0;
-  const double hdt2 = 0.5 * dt * dt;
   bool bad = false;
+  uint64_t ones = 0ull, zeros = 0ull;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    double x = p.x[i], y = p.y[i], z = p.z[i];
-    if (predict) {
-      const double vx = p.vx[i], vy = p.vy[i], vz = p.vz[i];
-      const double ax = p.ax[i], ay = p.ay[i], az = p.az[i];
-      x = wrap_coord(x + (vx * dt + hdt2 * ax), kp.lo[0], kp.len[0], kp.periodic[0]);
-      y = wrap_coord(y + (vy * dt + hdt2 * ay), kp.lo[1], kp.len[1], kp.periodic[1]);
-      z = wrap_coord(z + (vz * dt + hdt2 * az), kp.lo[2], kp.len[2], kp.periodic[2]);
-      p.x[i] = x;
-      p.y[i] = y;
-      p.z[i] = z;
-      p.vx[i] = vx + ax * dt;
-      p.vy[i] = vy + ay * dt;
-      p.vz[i] = vz + az * dt;
-      p.u[i] = p.u[i] + p.dudt[i] * dt;
-    }
-    bad |= !(isfinite(x) && isfinite(y) && isfinite(z));
-    const uint64_t ix = quantise(x, kp.lo[0], kp.key_scale);
-    const uint64_t iy = quantise(y, kp.lo[1], kp.key_scale);
-    const uint64_t iz = quantise(z, kp.lo[2], kp.key_scale);
-    keys[i] = (spread3(ix) << 2) | (spread3(iy) << 1) | spread3(iz);
+    const uint64_t key = predict_key(kp, p, predict != 0, dt, i, bad);
+    ones |= key;
+    zeros |= ~key;
+    keys[i] = key;
     vals[i] = (uint32_t)i;
   }
   if (bad) atomicOr(err, kErrNonFinite);
+  ones = wave_or_u64(ones);
+  zeros = wave_or_u64(zeros);
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    wr[w][0] = ones;
+    wr[w][1] = zeros;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2)
+    range[2 * blockIdx.x + threadIdx.x] =
+        wr[0][threadIdx.x] | wr[1][threadIdx.x] | wr[2][threadIdx.x] | wr[3][threadIdx.x];
 }
 
 // ============================================================================
@@ -326,82 +366,112 @@ __device__ __forceinline__ void lds_count_digit(uint32_t* cnt, uint32_t d, bool 
   }
 }
 
-// One-sweep radix sort.  k_radix_prep counts the digits of all eight passes
-// in one read of the keys (global histograms) and clears the look-back
-// status of every pass; k_radix_pass then sorts one 8-bit digit per launch:
-// each block takes the next tile (an atomic ticket, so every earlier tile
-// belongs to a block that already runs), publishes its digit counts, and
-// looks back over the earlier tiles' published counts or inclusive prefixes
-// for its exclusive prefix (decoupled look-back), then scatters stably.
-// Status words: flag in the top two bits (1 count only, 2 inclusive prefix),
-// the count in the low 30 (n < 2^30).  A word carries nothing but itself, so
-// relaxed device-scope atomics suffice (no acquire/release cache maintenance).
+// One-sweep radix sort of the keys' leading bits.  k_radix_prep counts the
+// digits of all passes in one read of the keys (global histograms) and clears
+// the look-back status of every pass; k_radix_pass then sorts one 8-bit digit
+// per launch: each block takes the next tile (an atomic ticket, so every
+// earlier tile belongs to a block that already runs), publishes its digit
+// counts, and looks back over the earlier tiles' published counts or
+// inclusive prefixes for its exclusive prefix (decoupled look-back), then
+// scatters stably.  Status words: flag in the top two bits (1 count only, 2
+// inclusive prefix), the count in the low 30 (n < 2^30).  A word carries
+// nothing but itself, so relaxed device-scope atomics suffice (no
+// acquire/release cache maintenance).
+//
+// A 63-bit key of n particles needs about log2 n bits to tell most particles
+// apart, so the passes sort only the top bits from the highest one that
+// varies (launch_sort chooses their number); k_sort_fix then orders the few
+// runs that agree in all of them, and k_resort sorts everything by all 63
+// bits where a run is too long for that.  What each pass costs is latency
+// (tile count, look-back) at small n, and its 24 bytes per particle at large
+// n: 8.3 us at 32^3, 13.3 at 294,912, 205 at 16.8M particles.
 constexpr uint32_t kStAgg = 1u << 30, kStPre = 2u << 30, kStMask = (1u << 30) - 1u;
 constexpr int kLookbackSpin = 1 << 22;  // bounded wait; the predecessors always publish
 constexpr int kLookW = 16;               // earlier tiles read per look-back round
 
+// Sorted bits start here: 8 npass bits up to the highest one that varies.
+__device__ __forceinline__ uint32_t sort_shift(uint64_t varying, int npass) {
+  const int top = varying ? 64 - __clzll((long long)varying) : 0;
+  return (uint32_t)max(0, top - 8 * npass);
+}
+
+__device__ __forceinline__ void count_digits(const uint64_t* __restrict__ keys, int n, int base,
+                                             uint32_t shift, int npass, uint32_t (*h)[256]) {
+#pragma unroll
+  for (int k = 0; k < kSortTile / 256; ++k) {
+    const int i = base + k * 256 + threadIdx.x;
+    const bool valid = i < n;
+    const uint64_t key = valid ? keys[i] >> shift : 0ull;
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+      if (p < npass) lds_count_digit(h[p], (uint32_t)((key >> (8 * p)) & 255ull), valid);
+  }
+}
+
 __global__ __launch_bounds__(256) void k_radix_prep(const uint64_t* __restrict__ keys, int n,
-                                                     int nblk, uint32_t* __restrict__ status,
-                                                     uint32_t* __restrict__ ghist) {
+                                                     int nblk, int npass, int nrange,
+                                                     const uint64_t* __restrict__ range,
+                                                     uint32_t* __restrict__ status,
+                                                     uint32_t* __restrict__ ghist,
+                                                     SortHead* __restrict__ head) {
   __shared__ uint32_t h[8][256];
+  __shared__ uint64_t wr[4][2];
   const int tid = threadIdx.x;
+  uint64_t ones = 0ull, zeros = 0ull;
+  for (int k = tid; k < nrange; k += 256) {
+    ones |= range[2 * k];
+    zeros |= range[2 * k + 1];
+  }
 #pragma unroll
   for (int p = 0; p < 8; ++p) h[p][tid] = 0u;
-  __syncthreads();
-  for (int t = blockIdx.x; t < nblk; t += gridDim.x) {
-#pragma unroll
-    for (int p = 0; p < 8; ++p) status[((int64_t)p * nblk + t) * 256 + tid] = 0u;
-    const int base = t * kSortTile;
-#pragma unroll
-    for (int k = 0; k < kSortTile / 256; ++k) {
-      const int i = base + k * 256 + tid;
-      const bool valid = i < n;
-      const uint64_t key = valid ? keys[i] : 0ull;
-#pragma unroll
-      for (int p = 0; p < 8; ++p) lds_count_digit(h[p], (uint32_t)((key >> (8 * p)) & 255ull), valid);
-    }
+  ones = wave_or_u64(ones);
+  zeros = wave_or_u64(zeros);
+  if ((tid & 63) == 0) {
+    wr[tid >> 6][0] = ones;
+    wr[tid >> 6][1] = zeros;
   }
   __syncthreads();
-#pragma unroll
-  for (int p = 0; p < 8; ++p)
+  const uint32_t shift =
+      sort_shift((wr[0][0] | wr[1][0] | wr[2][0] | wr[3][0]) &
+                     (wr[0][1] | wr[1][1] | wr[2][1] | wr[3][1]),
+                 npass);
+  if (blockIdx.x == 0 && tid == 0) head->shift = shift;
+  for (int t = blockIdx.x; t < nblk; t += gridDim.x) {
+    for (int p = 0; p < npass; ++p) status[((int64_t)p * nblk + t) * 256 + tid] = 0u;
+    count_digits(keys, n, t * kSortTile, shift, npass, h);
+  }
+  __syncthreads();
+  for (int p = 0; p < npass; ++p)
     if (h[p][tid]) atomicAdd(&ghist[p * 256 + tid], h[p][tid]);
 }
 
-__global__ __launch_bounds__(256) void k_radix_pass(const uint64_t* __restrict__ kin,
-                                                     const uint32_t* __restrict__ vin,
-                                                     uint64_t* __restrict__ kout,
-                                                     uint32_t* __restrict__ vout, int n,
-                                                     int pass, int nblk,
-                                                     uint32_t* __restrict__ status,
-                                                     const uint32_t* __restrict__ ghist,
-                                                     uint32_t* __restrict__ tickets,
-                                                     uint32_t* __restrict__ err) {
+struct SortLds {
+  // wc[d * NS + s]: keys of digit d in set s, then the tile's keys of digit d
+  // before set s (at most kSortTile: 16 bits suffice);
+  // the digit counts (16 KB), then the tile in digit order (24 KB)
+  alignas(16) unsigned char buf[kSortTile * 12];
+  uint32_t run[256];
+  uint32_t lst[256];
+  uint32_t lds4[4];
+  int tile;
+};
+
+// One tile of one pass: digits (key >> shift) & 255; st: the pass's status
+// words, gh: this thread's digit of the pass's histogram.
+__device__ __forceinline__ void radix_tile(SortLds& L, const uint64_t* __restrict__ kin,
+                                           const uint32_t* __restrict__ vin,
+                                           uint64_t* __restrict__ kout,
+                                           uint32_t* __restrict__ vout, int n, uint32_t shift,
+                                           int tile, uint32_t* __restrict__ st, uint32_t gh,
+                                           uint32_t* __restrict__ err) {
   constexpr int PER = kSortTile / 256;
   constexpr int NS = PER * 4;  // (key slice, wavefront) sets of 64 keys, in key order
-  // wc[d * NS + s]: keys of digit d in set s, then the tile's keys of digit d
-  // before set s (at most kSortTile: 16 bits suffice)
-  // the digit counts (16 KB), then the tile in digit order (24 KB)
-  __shared__ alignas(16) unsigned char s_buf[kSortTile * 12];
   static_assert(256 * NS * 2 <= kSortTile * 12, "digit counts fit the tile buffer");
-  uint16_t* wc = reinterpret_cast<uint16_t*>(s_buf);
-  uint64_t* s_key = reinterpret_cast<uint64_t*>(s_buf);
-  uint32_t* s_val = reinterpret_cast<uint32_t*>(s_buf + kSortTile * 8);
-  __shared__ uint32_t run[256];
-  __shared__ uint32_t lst[256];
-  __shared__ uint32_t lds4[4];
-  __shared__ int s_tile;
   static_assert(kSortTile <= 65535, "16-bit tile offsets");
+  uint16_t* wc = reinterpret_cast<uint16_t*>(L.buf);
+  uint64_t* s_key = reinterpret_cast<uint64_t*>(L.buf);
+  uint32_t* s_val = reinterpret_cast<uint32_t*>(L.buf + kSortTile * 8);
   const int tid = threadIdx.x, w = tid >> 6;
-  const int shift = 8 * pass;
-  const uint32_t gh = ghist[pass * 256 + tid];  // in flight from the start
-  {
-    uint32_t* z = reinterpret_cast<uint32_t*>(wc);
-#pragma unroll
-    for (int q = 0; q < NS / 2; ++q) z[q * 256 + tid] = 0u;
-  }
-  if (tid == 0) s_tile = (int)atomicAdd(&tickets[pass], 1u);
-  __syncthreads();
-  const int tile = s_tile;
   const int base = tile * kSortTile;
   uint64_t key[PER];
   uint32_t val[PER], rank[PER];
@@ -439,12 +509,11 @@ __global__ __launch_bounds__(256) void k_radix_pass(const uint64_t* __restrict__
   }
   // publish this tile's counts; scan the global digit counts while earlier
   // tiles publish theirs; then the exclusive prefix over earlier tiles
-  uint32_t* st = status + (int64_t)pass * nblk * 256;
   __hip_atomic_store(&st[(int64_t)tile * 256 + tid], (tile == 0 ? kStPre : kStAgg) | mine,
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // start of every digit: keys with a smaller digit anywhere
   uint32_t all;
-  const uint32_t gofs = block256_excl_scan(gh, lds4, &all);
+  const uint32_t gofs = block256_excl_scan(gh, L.lds4, &all);
   uint32_t excl = 0u;
   if (tile > 0) {
     // a window of kLookW earlier tiles per round: their loads are in flight
@@ -482,15 +551,15 @@ __global__ __launch_bounds__(256) void k_radix_pass(const uint64_t* __restrict__
   // the tile's keys in digit order in LDS first, so that each digit's run is
   // stored by consecutive lanes to consecutive addresses
   uint32_t tot2;
-  const uint32_t ls = block256_excl_scan(mine, lds4, &tot2);  // tile-local start of digit tid
-  lst[tid] = ls;
-  run[tid] = gofs + excl - ls;  // global position of local position 0, for digit tid
+  const uint32_t ls = block256_excl_scan(mine, L.lds4, &tot2);  // tile-local start of digit tid
+  L.lst[tid] = ls;
+  L.run[tid] = gofs + excl - ls;  // global position of local position 0, for digit tid
   __syncthreads();
   uint32_t lp[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const uint32_t d = (uint32_t)((key[k] >> shift) & 255ull);
-    lp[k] = lst[d] + (uint32_t)wc[d * NS + k * 4 + w] + rank[k];
+    lp[k] = L.lst[d] + (uint32_t)wc[d * NS + k * 4 + w] + rank[k];
   }
   __syncthreads();  // the counts are overwritten by the sorted tile
 #pragma unroll
@@ -508,10 +577,169 @@ __global__ __launch_bounds__(256) void k_radix_pass(const uint64_t* __restrict__
     if (q < cnt) {
       const uint64_t kk = s_key[q];
       const uint32_t d = (uint32_t)((kk >> shift) & 255ull);
-      const uint32_t pos = run[d] + (uint32_t)q;
+      const uint32_t pos = L.run[d] + (uint32_t)q;
       kout[pos] = kk;
       vout[pos] = s_val[q];
     }
+  }
+}
+
+__device__ __forceinline__ void clear_counts(SortLds& L) {
+  uint32_t* z = reinterpret_cast<uint32_t*>(L.buf);
+#pragma unroll
+  for (int q = 0; q < kSortTile / 128; ++q) z[q * 256 + threadIdx.x] = 0u;
+}
+
+__global__ __launch_bounds__(256) void k_radix_pass(const uint64_t* __restrict__ kin,
+                                                     const uint32_t* __restrict__ vin,
+                                                     uint64_t* __restrict__ kout,
+                                                     uint32_t* __restrict__ vout, int n,
+                                                     int pass, int nblk,
+                                                     uint32_t* __restrict__ status,
+                                                     const uint32_t* __restrict__ ghist,
+                                                     SortHead* __restrict__ head,
+                                                     uint32_t* __restrict__ err) {
+  __shared__ SortLds L;
+  const uint32_t gh = ghist[pass * 256 + threadIdx.x];  // in flight from the start
+  const uint32_t shift = head->shift + 8u * (uint32_t)pass;
+  clear_counts(L);
+  if (threadIdx.x == 0) L.tile = (int)atomicAdd(&head->tickets[pass], 1u);
+  __syncthreads();
+  radix_tile(L, kin, vin, kout, vout, n, shift, L.tile, status + (int64_t)pass * nblk * 256, gh,
+             err);
+}
+
+// After the passes: every run of keys that agree in the sorted bits is put in
+// the order of the whole keys (stably, so that the result is that of all
+// passes).  A block orders the runs that start in its tile, each of at most
+// kRunMax keys: every key counts the keys of its run that go before it.
+// Other blocks read the keys that a block moves only for their sorted bits,
+// which the moves keep.  Longer runs that are out of order are left to
+// k_resort.  Bound by one read of the keys.
+constexpr int kRunMax = 64;
+
+__global__ __launch_bounds__(256) void k_sort_fix(uint64_t* __restrict__ keys,
+                                                   uint32_t* __restrict__ vals, int n,
+                                                   SortHead* __restrict__ head) {
+  constexpr int H = kRunMax + 1;             // halo on both sides
+  constexpr int W = kSortTile + kRunMax;     // positions looked at: the tile and what
+                                             // its last run can hold beyond it
+  constexpr int PER = (W + 255) / 256;
+  __shared__ uint64_t s_key[kSortTile + 2 * H];
+  const uint32_t shift = head->shift;
+  if (shift == 0u) return;  // sorted by all bits that vary
+  const int base = blockIdx.x * kSortTile;
+  for (int t = threadIdx.x; t < kSortTile + 2 * H; t += 256) {
+    const int j = base - H + t;
+    s_key[t] = j >= 0 && j < n ? keys[j] : 0ull;
+  }
+  __syncthreads();
+  // position j is s_key[j - base + H]
+  auto same = [&](int j, uint64_t pre) {  // j holds a key of the run
+    return j >= 0 && j < n && (s_key[j - base + H] >> shift) == pre;
+  };
+  int to[PER];
+  uint64_t key[PER];
+  uint32_t val[PER];
+  bool longrun = false;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = base + k * 256 + (int)threadIdx.x;
+    to[k] = -1;
+    key[k] = 0ull;
+    val[k] = 0u;
+    if (i >= n || i >= base + W) continue;
+    const uint64_t kk = s_key[i - base + H];
+    const uint64_t pre = kk >> shift;
+    if (!same(i - 1, pre) && !same(i + 1, pre)) continue;  // alone
+    int a = i, e = i + 1;  // the run, as far as kRunMax + 1 keys
+    while (i - a < kRunMax && same(a - 1, pre)) --a;
+    while (e - a <= kRunMax && e < base + kSortTile + H && same(e, pre)) ++e;
+    if (e - a > kRunMax || i - a >= kRunMax) {
+      longrun |= same(i + 1, pre) && i + 1 < base + kSortTile + H && s_key[i + 1 - base + H] < kk;
+      continue;
+    }
+    if (a < base || a >= base + kSortTile) continue;  // another block's
+    int r = a;
+    for (int j = a; j < e; ++j) {
+      const uint64_t o = s_key[j - base + H];
+      r += (o < kk || (o == kk && j < i)) ? 1 : 0;
+    }
+    if (r != i) {
+      to[k] = r;
+      key[k] = kk;
+      val[k] = vals[i];
+    }
+  }
+  if (longrun) head->resort = 1u;
+  __syncthreads();  // all values read
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (to[k] >= 0) {
+      keys[to[k]] = key[k];
+      vals[to[k]] = val[k];
+    }
+}
+
+// All eight passes in one launch, for keys with a long run out of order;
+// without one it ends at once.  Items are taken in order by a ticket: a stage
+// of digit counts over all tiles, then the passes' tiles.  An item waits for
+// the stage before its own to end: those items belong to blocks that already
+// run, so the wait ends however many blocks are resident.  Equal keys are in
+// the order of the particles already and stay so.
+__global__ __launch_bounds__(256) void k_resort(uint64_t* k0, uint32_t* v0, uint64_t* k1,
+                                                 uint32_t* v1, int n, int nblk,
+                                                 uint32_t* __restrict__ status, uint32_t* ghist,
+                                                 SortHead* head, uint32_t* __restrict__ err) {
+  if (head->resort == 0u) return;
+  __shared__ SortLds L;
+  const int tid = threadIdx.x;
+  for (;;) {
+    __syncthreads();  // the LDS of the item before
+    if (tid == 0) {
+      const int t = (int)atomicAdd(&head->ticket, 1u);
+      const int stage = t / nblk;
+      if (stage >= 1 && stage <= 8) {
+        int spins = 0;
+        while (__hip_atomic_load(&head->done[stage - 1], __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)nblk) {
+          __builtin_amdgcn_s_sleep(8);
+          if (++spins > kLookbackSpin) {
+            atomicOr(err, kErrSort);
+            break;
+          }
+        }
+      }
+      L.tile = t;
+    }
+    __syncthreads();
+    __threadfence();  // what the stage before wrote
+    const int t = L.tile, stage = t / nblk, tile = t - stage * nblk;
+    if (stage > 8) return;
+    if (stage == 0) {
+      uint32_t(*h)[256] = reinterpret_cast<uint32_t(*)[256]>(L.buf);
+      for (int p = 0; p < 8; ++p) {
+        h[p][tid] = 0u;
+        status[((int64_t)p * nblk + tile) * 256 + tid] = 0u;
+      }
+      __syncthreads();
+      count_digits(k0, n, tile * kSortTile, 0u, 8, h);
+      __syncthreads();
+      for (int p = 0; p < 8; ++p)
+        if (h[p][tid]) atomicAdd(&ghist[p * 256 + tid], h[p][tid]);
+    } else {
+      const int pass = stage - 1;
+      const uint32_t gh = __hip_atomic_load(&ghist[pass * 256 + tid], __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+      clear_counts(L);
+      __syncthreads();
+      const bool even = (pass & 1) == 0;
+      radix_tile(L, even ? k0 : k1, even ? v0 : v1, even ? k1 : k0, even ? v1 : v0, n,
+                 8u * (uint32_t)pass, tile, status + (int64_t)pass * nblk * 256, gh, err);
+    }
+    __threadfence();  // every thread's writes, before the stage counts this item
+    __syncthreads();
+    if (tid == 0) atomicAdd(&head->done[stage], 1u);
   }
 }
 
@@ -3966,50 +4194,75 @@ static int stream_blocks(int n) {
 }
 
 // The radix sort's workspace: look-back status words of every pass and tile,
-// then the eight digit histograms, then the eight tile tickets.
+// then the eight digit histograms of the passes and of k_resort, then the
+// head, then the key bits of every block of k_predict_keys.
 struct SortWs {
-  uint32_t *status, *ghist, *tickets;
+  uint32_t *status, *ghist;
+  SortHead* head;
+  uint64_t* range;
 };
 static SortWs sort_ws(sph_ctx* c) {
   const int64_t nst = (int64_t)c->n_max_sort_blocks * 8 * 256;
+  static_assert(sizeof(SortHead) <= 4 * kSortHeadWords, "the head fits its words");
   SortWs w;
   w.status = c->radix_cnt;
   w.ghist = c->radix_cnt + nst;
-  w.tickets = w.ghist + 8 * 256;
+  w.head = reinterpret_cast<SortHead*>(w.ghist + 2 * 8 * 256);
+  w.range = reinterpret_cast<uint64_t*>(w.ghist + 2 * 8 * 256 + kSortHeadWords);
   return w;
+}
+
+// Passes of the sort: enough of the leading key bits that a cell of them
+// holds 2^-6 particles on average (the key bits of an axis shorter than the
+// longest do not vary at the top and do not count), so that denser regions
+// keep runs of a few particles.  Sort (all its launches) of 32^3 particles in
+// a cube 45 us, of 294,912 in a box of 16:1:1 94, of 16.8M in a cube 983 with
+// the 3, 5 and 4 passes this gives; 77, 119 and 1750 with all eight.
+static int sort_passes(const sph_ctx* c) {
+  int want = 6;
+  for (int64_t m = c->n; m > 1; m = (m + 1) >> 1) ++want;
+  int top = -1, have = 0;
+  for (int bit = 3 * kKeyLevels - 1; bit >= 0; --bit) {
+    const int axis = 2 - bit % 3, level = bit / 3;  // bit of cell coordinate
+    if (!(c->kp.len[axis] * c->kp.key_scale > ldexp(1.0, level))) continue;
+    if (top < 0) top = bit;
+    if (++have == want) return (top - bit + 8) / 8;
+  }
+  return 8;
 }
 
 hipError_t launch_predict_keys(sph_ctx* c, const sph_particles* s, bool predict, double) {
   c->kp.n = c->n;
   const SortWs w = sort_ws(c);
+  const int src = sort_passes(c) & 1;
   hipLaunchKernelGGL(k_predict_keys, dim3(stream_blocks(c->n)), dim3(256), 0, c->stream, c->kp,
-                     parts_of(s), predict ? 1 : 0, c->ds, c->keys[0], c->vals[0], w.ghist,
-                     w.tickets, &c->ds->err);
+                     parts_of(s), predict ? 1 : 0, c->ds, c->keys[src], c->vals[src], w.ghist,
+                     w.head, w.range, &c->ds->err);
   return hipGetLastError();
 }
 
-// Follows launch_predict_keys, which cleared the histograms and tickets.
+// Follows launch_predict_keys, which cleared the histograms and the head.
+// The result is in buffer 0.
 hipError_t launch_sort(sph_ctx* c) {
   const int n = c->n;
   const int nblk = (n + kSortTile - 1) / kSortTile;
   const SortWs w = sort_ws(c);
-  uint32_t* status = w.status;
-  uint32_t* ghist = w.ghist;
-  uint32_t* tickets = w.tickets;
   const int pblocks = std::min(nblk, 4 * c->n_cu);
-  hipLaunchKernelGGL(k_radix_prep, dim3(pblocks), dim3(256), 0, c->stream, c->keys[0], n, nblk,
-                     status, ghist);
-  for (int pass = 0; pass < 8; ++pass) {
-    const int src = pass & 1, dst = src ^ 1;
-    if (pass < 7)
-      hipLaunchKernelGGL(k_radix_pass, dim3(nblk), dim3(256), 0, c->stream, c->keys[src],
-                         c->vals[src], c->keys[dst], c->vals[dst], n, pass, nblk, status, ghist,
-                         tickets, &c->ds->err);
-    else
-      launch_last(c, k_radix_pass, dim3(nblk), dim3(256), c->keys[src], c->vals[src],
-                  c->keys[dst], c->vals[dst], n, pass, nblk, status, ghist, tickets, &c->ds->err);
+  const int npass = sort_passes(c);
+  int src = npass & 1;
+  hipLaunchKernelGGL(k_radix_prep, dim3(pblocks), dim3(256), 0, c->stream, c->keys[src], n, nblk,
+                     npass, stream_blocks(n), w.range, w.status, w.ghist, w.head);
+  for (int pass = 0; pass < npass; ++pass, src ^= 1) {
+    const int dst = src ^ 1;
+    hipLaunchKernelGGL(k_radix_pass, dim3(nblk), dim3(256), 0, c->stream, c->keys[src],
+                       c->vals[src], c->keys[dst], c->vals[dst], n, pass, nblk, w.status, w.ghist,
+                       w.head, &c->ds->err);
   }
-  return hipGetLastError();  // 8 passes: the result is back in buffer 0
+  hipLaunchKernelGGL(k_sort_fix, dim3(nblk), dim3(256), 0, c->stream, c->keys[0], c->vals[0], n,
+                     w.head);
+  launch_last(c, k_resort, dim3(std::min(nblk, 2 * c->n_cu)), dim3(256), c->keys[0], c->vals[0],
+              c->keys[1], c->vals[1], n, nblk, w.status, w.ghist + 8 * 256, w.head, &c->ds->err);
+  return hipGetLastError();
 }
 
 hipError_t launch_permute(sph_ctx* c, const sph_particles* s, bool outputs_too) {
