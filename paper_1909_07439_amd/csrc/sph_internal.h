@@ -202,6 +202,16 @@ __device__ __forceinline__ double seg_max(double v) {
   return v;
 }
 template <int LPI>
+__device__ __forceinline__ double seg_min(double v) {
+  if constexpr (LPI > 32) v = fmin(v, xor_lane_f64<32>(v));
+  if constexpr (LPI > 16) v = fmin(v, xor_lane_f64<16>(v));
+  if constexpr (LPI > 8) v = fmin(v, xor_lane_f64<8>(v));
+  if constexpr (LPI > 4) v = fmin(v, xor_lane_f64<4>(v));
+  if constexpr (LPI > 2) v = fmin(v, xor_lane_f64<2>(v));
+  if constexpr (LPI > 1) v = fmin(v, xor_lane_f64<1>(v));
+  return v;
+}
+template <int LPI>
 __device__ __forceinline__ uint32_t seg_sum_u32(uint32_t v) {
   if constexpr (LPI > 32) v += xor_lane_u32<32>(v);
   if constexpr (LPI > 16) v += xor_lane_u32<16>(v);

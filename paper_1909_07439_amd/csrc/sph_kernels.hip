@@ -50,19 +50,9 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   return v;
 }
 
-__device__ __forceinline__ double wave_max_f64(double v) {
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) v = fmax(v, __shfl_xor(v, d, kWave));
-  return v;
-}
+__device__ __forceinline__ double wave_max_f64(double v) { return seg_max<kWave>(v); }
+__device__ __forceinline__ double wave_min_f64(double v) { return seg_min<kWave>(v); }
 
-__device__ __forceinline__ double wave_min_f64(double v) {
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) v = fmin(v, __shfl_xor(v, d, kWave));
-  return v;
-}
-
-// Exclusive scan over a 256-thread block; lds must hold 4 words.
 __device__ __forceinline__ uint32_t block256_excl_scan(uint32_t v, uint32_t* lds,
                                                        uint32_t* total) {
   const uint32_t inc = wave_incl_scan_u32(v);
@@ -1168,7 +1158,9 @@ __device__ __forceinline__ void tree_guard(DevState* ds, int64_t node_cap) {
 // ---- node and group boxes and largest h -----------------------------------
 // Every leaf and group covers a contiguous range of the sorted particles:
 // k_range_boxes reduces each one's particles (four per wavefront, 16 lanes
-// each, so the particle loads coalesce).  Inner nodes then take the union of
+// each, so the particle loads coalesce; the lanes combine by DPP moves, as
+// LDS permutes took most of it: 32 -> 23 us at 294,912 particles, 840 -> 600
+// at 16.8M).  Inner nodes then take the union of
 // their children's boxes and the largest of their h_max, one launch per
 // level from the deepest up (k_level_boxes).  No atomics.  A leaf's or
 // group's box is exactly the range's; an inner node's holds its children's
@@ -1394,14 +1386,12 @@ __global__ __launch_bounds__(256) void k_range_boxes(
       }
       b.hm = fmax(b.hm, h[s]);
     }
-    for (int d = 8; d > 0; d >>= 1) {
-      if (do_bb)
-        for (int a = 0; a < 3; ++a) {
-          b.lo[a] = fmin(b.lo[a], __shfl_xor(b.lo[a], d, 16));
-          b.hi[a] = fmax(b.hi[a], __shfl_xor(b.hi[a], d, 16));
-        }
-      b.hm = fmax(b.hm, __shfl_xor(b.hm, d, 16));
-    }
+    if (do_bb)
+      for (int a = 0; a < 3; ++a) {
+        b.lo[a] = seg_min<16>(b.lo[a]);
+        b.hi[a] = seg_max<16>(b.hi[a]);
+      }
+    b.hm = seg_max<16>(b.hm);
     if (item && sub == 0) {
       if (is_node)
         write_node_box(b, it, f, e, 0, nchild, wn, do_bb);
@@ -1510,6 +1500,7 @@ constexpr int kFCap = 512;  // frontier entries per level in LDS
 constexpr int kLCap = 128;  // leaves per flush
 constexpr int kPMax = 128;  // pairs per particle slot
 constexpr int kTile = 256;  // candidates staged in LDS at a time
+constexpr int kFCapFb = 256, kTileFb = 128;  // of the flagged groups' density
 constexpr int kSG = 8;      // groups sharing one super-group walk
 constexpr int kSLCap = 256; // leaves a super-group walk may collect
 
@@ -1566,37 +1557,39 @@ struct WalkLds {
 // folded to the nearest periodic image once, when staged.  `a` carries one
 // more per-particle value (m_j for the density, h_j for the force), `j` the
 // particle index.
-template <typename T>
+template <typename T, int N = kTile>
 struct TileOf {
-  T x[kTile];
-  T y[kTile];
-  T z[kTile];
-  T a[kTile];
-  int j[kTile];
+  T x[N];
+  T y[N];
+  T z[N];
+  T a[N];
+  int j[N];
 };
 
 // Breadth-first walk.  open_r(node) returns the opening radius for a node;
 // flush(nleaf) consumes the leaf list (loff filled).  A level's frontier
-// holds kFCap entries in LDS and continues in this wavefront's region of
+// holds FC entries in LDS and continues in this wavefront's region of
 // global memory (`spill`, kSpill entries per level; search regions much
 // larger than the local particle spacing need it).  Returns false on
 // frontier overflow.
-template <bool WHOLE = true, typename RadiusFn, typename FlushFn>
+template <bool WHOLE = true, int FC, typename RadiusFn, typename FlushFn>
 __device__ bool group_walk(const WalkNode* __restrict__ nodes, const GroupInfo& G,
-                           const KParams& kp, WalkLds& L, int (&front)[2][kFCap],
+                           const KParams& kp, WalkLds& L, int (&front)[2][FC],
                            int* __restrict__ spill, RadiusFn open_r, FlushFn flush) {
   const int lane = threadIdx.x;
-  const int cap = kFCap + kSpill;
+  constexpr int cap = kFCap + kSpill;
+  constexpr int stride = FC < kFCap ? 2 * kSpill : kSpill;  // spill entries per level
+  static_assert(cap - FC <= stride, "a level's frontier fits LDS and its spill region");
   auto fget = [&](int lvl, int k) -> int {
-    return k < kFCap ? front[lvl][k]
-                     : __hip_atomic_load(&spill[lvl * kSpill + (k - kFCap)], __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
+    return k < FC ? front[lvl][k]
+                  : __hip_atomic_load(&spill[lvl * stride + (k - FC)], __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
   };
   auto fput = [&](int lvl, int k, int v) {
-    if (k < kFCap)
+    if (k < FC)
       front[lvl][k] = v;
     else
-      __hip_atomic_store(&spill[lvl * kSpill + (k - kFCap)], v, __ATOMIC_RELAXED,
+      __hip_atomic_store(&spill[lvl * stride + (k - FC)], v, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   };
   int nf = 1, cur = 0, nleaf = 0;
@@ -1712,14 +1705,14 @@ __device__ __forceinline__ int leaf_offsets(WalkLds& L, int nleaf) {
 // Every lane resolves its candidates' particle indices first and then issues
 // all their loads before storing any, so a whole tile costs about one
 // memory latency instead of one per candidate step.
-template <typename T>
+template <typename T, int N>
 __device__ __forceinline__ void stage_tile(const WalkLds& L, int nleaf, int c0, int cnt,
                                            const double* __restrict__ px,
                                            const double* __restrict__ py,
                                            const double* __restrict__ pz,
-                                           const double* __restrict__ pa, TileOf<T>& S,
+                                           const double* __restrict__ pa, TileOf<T, N>& S,
                                            const GroupInfo& G, const KParams& kp) {
-  constexpr int PER = kTile / kWave;
+  constexpr int PER = N / kWave;
   const int lane = threadIdx.x;
   int jj[PER];
 #pragma unroll
@@ -1772,15 +1765,15 @@ __device__ __forceinline__ void stage_tile(const WalkLds& L, int nleaf, int c0, 
 // Candidate loop over the flushed leaves, one staged tile at a time: lane
 // `sub` of every slot visits tile entries sub, sub+LPI, ...;
 // body(valid, c) is called by all lanes with c the tile index.
-template <int LPI, typename T, typename Body>
+template <int LPI, typename T, int N, typename Body>
 __device__ __forceinline__ void for_tiles(const WalkLds& L, int nleaf, int total, int sub,
                                           const double* __restrict__ px,
                                           const double* __restrict__ py,
                                           const double* __restrict__ pz,
-                                          const double* __restrict__ pa, TileOf<T>& S,
+                                          const double* __restrict__ pa, TileOf<T, N>& S,
                                           const GroupInfo& G, const KParams& kp, Body body) {
-  for (int c0 = 0; c0 < total; c0 += kTile) {
-    const int cnt = min(kTile, total - c0);
+  for (int c0 = 0; c0 < total; c0 += N) {
+    const int cnt = min(N, total - c0);
     stage_tile<T>(L, nleaf, c0, cnt, px, py, pz, pa, S, G, kp);
     for (int cb = 0; cb < cnt; cb += LPI) {
       const int c = cb + sub;
@@ -2058,7 +2051,13 @@ __device__ __forceinline__ void density_outputs(const KParams& kp, const Parts& 
   }
 }
 
-template <bool MIXED, int LPI>
+// FB: only the groups of flag_list, which the neighbour-list kernels flagged,
+// each with its own walk and without storing leaf lists.  A group's walks,
+// staging and sums are serial chains of some 100 us, so what counts is how
+// many wavefronts a CU holds: with a smaller frontier and tile in LDS (25 KB
+// instead of 33 in FP64) and without the super-group code, six instead of
+// four (3157 flagged groups of 30,011 particles: 369 -> 231 us).
+template <bool MIXED, int LPI, bool FB>
 __global__ __launch_bounds__(64) void k_density(KParams kp, Parts p,
                                                 const WalkNode* __restrict__ nodes,
                                                 const GroupInfo* __restrict__ groups,
@@ -2069,18 +2068,18 @@ __global__ __launch_bounds__(64) void k_density(KParams kp, Parts p,
                                                 const int32_t* __restrict__ flag_list,
                                                 int32_t* __restrict__ walk_spill,
     DevState* __restrict__ ds) {
-  int* __restrict__ spill = walk_spill + (int64_t)blockIdx.x * 2 * kSpill;
+  // FB: half the wavefronts, each with twice the spill
+  int* __restrict__ spill = walk_spill + (int64_t)blockIdx.x * (FB ? 4 : 2) * kSpill;
   using R = typename std::conditional<MIXED, float, double>::type;
   constexpr int GS = kWave / LPI;
-  // flag_list != nullptr: only the groups the neighbour-list kernels
-  // flagged, each with its own walk and without storing leaf lists
-  const bool fb = flag_list != nullptr;
+  constexpr bool fb = FB;
+  if (FB && ds->n_flagged == 0) return;
   __shared__ WalkLds L;
-  __shared__ int s_front[2][kFCap];
-  __shared__ TileOf<R> T;
+  __shared__ int s_front[2][FB ? kFCapFb : kFCap];
+  __shared__ TileOf<R, FB ? kTileFb : kTile> T;
   __shared__ R s_r[kPMax * GS];
   __shared__ R s_m[kPMax * GS];
-  __shared__ int s_sl[kSLCap];  // leaves found by the super-group walk
+  __shared__ int s_sl[FB ? 1 : kSLCap];  // leaves found by the super-group walk
 
   const int lane = threadIdx.x;
   const int slot = lane / LPI, sub = lane % LPI;
@@ -2239,7 +2238,7 @@ __global__ __launch_bounds__(64) void k_density(KParams kp, Parts p,
           __syncthreads();
         };
         bool wok;
-        if (store && sok)
+        if (!fb && store && sok)
           wok = true, list_walk(nodes, s_sl, nsl, G, kp, L, radius, flush);
         else
           wok = group_walk(nodes, G, kp, L, s_front, spill, radius, flush);
@@ -2512,6 +2511,7 @@ __global__ __launch_bounds__(64) void k_force(KParams kp, Parts p,
   // 1): the list kernel does the unflagged groups, and the few flagged ones
   // are striped over all wavefronts
   const bool only_flagged = flag_list != nullptr && use_lists;
+  if (only_flagged && ds->n_flagged == 0) return;
   const int g_first = only_flagged ? (int)blockIdx.x : gbeg + local;
   const int g_end = only_flagged ? ds->n_flagged : gend;
   const int g_step = only_flagged ? (int)gridDim.x : nloc;
@@ -4417,16 +4417,27 @@ bool lists_mode(const sph_ctx* c) { return c->kp.n_group == 4 || c->kp.n_group =
     } break;                           \
   }
 
+// Wavefronts for the flagged groups: one for each that the tree can have, at
+// most about what is resident at a time.
+static int flagged_blocks(const sph_ctx* c) {
+  return std::min((c->n + 7) / 8 * 8, c->walk_blocks / 2);
+}
+
 template <bool MIXED>
 static hipError_t density_dispatch(sph_ctx* c, const sph_particles* s, const int32_t* gflag) {
   const Parts p = parts_of(s);
-  // the flagged groups (usually none, at most a few per cent) are striped
-  // over a quarter of the walk grid: an empty launch then costs less
-  const dim3 grid(gflag ? std::max(c->walk_blocks / 4, 8) : c->walk_blocks), block(64);
-  SPH_LPI_SWITCH(c->kp.n_group,
-                 launch_last(c, (k_density<MIXED, LPI>), grid, block, c->kp, p, c->wnode, c->ginfo,
-                             c->frec, c->leaf_pool, c->pool_cap, c->gl_off, c->gl_cnt, gflag,
-                             c->walk_spill, c->ds));
+  if (gflag) {
+    SPH_LPI_SWITCH_LISTS(c->kp.n_group,
+                         launch_last(c, (k_density<MIXED, LPI, true>), dim3(flagged_blocks(c)),
+                                     dim3(64), c->kp, p, c->wnode, c->ginfo, c->frec,
+                                     c->leaf_pool, c->pool_cap, c->gl_off, c->gl_cnt, gflag,
+                                     c->walk_spill, c->ds));
+  } else {
+    SPH_LPI_SWITCH(c->kp.n_group,
+                   launch_last(c, (k_density<MIXED, LPI, false>), dim3(c->walk_blocks), dim3(64),
+                               c->kp, p, c->wnode, c->ginfo, c->frec, c->leaf_pool, c->pool_cap,
+                               c->gl_off, c->gl_cnt, gflag, c->walk_spill, c->ds));
+  }
   return hipGetLastError();
 }
 
@@ -4522,7 +4533,7 @@ template <bool MIXED>
 static hipError_t force_dispatch(sph_ctx* c, const sph_particles* s, double* oax, double* oay,
                                  double* oaz, double* odu, const int32_t* gflag) {
   const Parts p = parts_of(s);
-  const dim3 grid(c->walk_blocks), block(64);
+  const dim3 grid(gflag ? flagged_blocks(c) : c->walk_blocks), block(64);
   SPH_LPI_SWITCH(c->kp.n_group,
                  launch_last(c, (k_force<MIXED, LPI>), grid, block, c->kp, p, c->wnode, c->ginfo,
                              c->frec, c->leaf_pool, c->gl_off, c->gl_cnt, oax, oay, oaz, odu, gflag,
