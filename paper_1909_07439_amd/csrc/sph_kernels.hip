@@ -733,6 +733,133 @@ __global__ __launch_bounds__(256) void k_resort(uint64_t* k0, uint32_t* v0, uint
   }
 }
 
+// Few particles: prediction, keys and sort by one block, keys in registers and
+// LDS, PER per thread.  The leading npass digits first; if two neighbours are
+// then out of order, all eight.  The separate launches take some 5 us each,
+// whatever they do: 29 -> 9 us at 1000 particles, 37 -> 15 at 1728, 44 -> 29
+// at 3375; its own time is that of one CU and doubles with n, so that beyond
+// 4096 particles the launches win (47 us at 8000).
+template <int PER>
+__global__ __launch_bounds__(1024) void k_sort_small(KParams kp, Parts p, int predict, int npass,
+                                                      const DevState* __restrict__ ds,
+                                                      uint64_t* __restrict__ keys,
+                                                      uint32_t* __restrict__ vals,
+                                                      uint32_t* __restrict__ err) {
+  constexpr int NS = PER * 16;  // (key slice, wavefront) sets of 64 keys, in key order
+  __shared__ alignas(16) uint16_t wc[256 * NS];
+  __shared__ uint64_t s_key[PER * 1024];
+  __shared__ uint32_t s_val[PER * 1024];
+  __shared__ uint32_t lst[256];
+  __shared__ uint32_t wtot[4];
+  __shared__ uint64_t wr[16][2];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int n = kp.n;
+  const double dt = predict ? ds->dt_cur : 0.0;
+  uint64_t key[PER];
+  uint32_t val[PER];
+  uint64_t ones = 0ull, zeros = 0ull;
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * 1024 + tid;
+    key[k] = 0ull;
+    val[k] = (uint32_t)i;
+    if (i < n) {
+      key[k] = predict_key(kp, p, predict != 0, dt, i, bad);
+      ones |= key[k];
+      zeros |= ~key[k];
+    }
+  }
+  if (bad) atomicOr(err, kErrNonFinite);
+  ones = wave_or_u64(ones);
+  zeros = wave_or_u64(zeros);
+  if (lane == 0) {
+    wr[w][0] = ones;
+    wr[w][1] = zeros;
+  }
+  __syncthreads();
+  for (int q = 0; q < 16; ++q) {
+    ones |= wr[q][0];
+    zeros |= wr[q][1];
+  }
+  uint32_t shift = sort_shift(ones & zeros, npass);
+  for (;;) {
+    for (int pass = 0; pass < npass; ++pass, shift += 8) {
+      for (int q = tid; q < 256 * NS / 8; q += 1024)
+        reinterpret_cast<uint4*>(wc)[q] = make_uint4(0u, 0u, 0u, 0u);
+      __syncthreads();
+      uint32_t rank[PER];
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const bool valid = k * 1024 + tid < n;
+        const uint32_t d = (uint32_t)((key[k] >> shift) & 255ull);
+        const uint64_t m = match_digit8(d, ballot64(valid));
+        rank[k] = (uint32_t)popc64(m & lanemask_lt());
+        if (valid && rank[k] == 0) wc[d * NS + k * 16 + w] = (uint16_t)popc64(m);
+      }
+      __syncthreads();
+      // thread d < 256: exclusive offsets of digit d over the sets, its start
+      uint32_t mine = 0u, inc = 0u;
+      if (tid < 256) {
+        uint16_t c[NS];
+#pragma unroll
+        for (int q = 0; q < NS; ++q) c[q] = wc[tid * NS + q];
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+          const uint32_t v = c[q];
+          c[q] = (uint16_t)mine;
+          mine += v;
+        }
+#pragma unroll
+        for (int q = 0; q < NS; ++q) wc[tid * NS + q] = c[q];
+        inc = wave_incl_scan_u32(mine);
+        if (lane == 63) wtot[w] = inc;
+      }
+      __syncthreads();
+      if (tid < 256) {
+        uint32_t off = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) off += q < w ? wtot[q] : 0u;
+        lst[tid] = off + inc - mine;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const uint32_t d = (uint32_t)((key[k] >> shift) & 255ull);
+        if (k * 1024 + tid < n) {
+          const uint32_t at = lst[d] + (uint32_t)wc[d * NS + k * 16 + w] + rank[k];
+          s_key[at] = key[k];
+          s_val[at] = val[k];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const int i = k * 1024 + tid;
+        key[k] = i < n ? s_key[i] : 0ull;
+        val[k] = i < n ? s_val[i] : 0u;
+      }
+    }
+    bool out = false;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = k * 1024 + tid;
+      out |= i + 1 < n && key[k] > s_key[i + 1];
+    }
+    if (!__syncthreads_or(out)) break;
+    npass = 8;  // equal keys are in the order of the particles and stay so
+    shift = 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * 1024 + tid;
+    if (i < n) {
+      keys[i] = key[k];
+      vals[i] = val[k];
+    }
+  }
+}
+
 // ============================================================================
 // Permute the particle fields into key order (gather, then copy back).
 // ============================================================================
@@ -764,6 +891,47 @@ __global__ __launch_bounds__(256) void k_copy_back(FieldSet fs, const double* __
     if (fs.xyzm)
       fs.xyzm[k] =
           make_double4(tmp[k], tmp[stride + k], tmp[2 * stride + k], tmp[fs.im * stride + k]);
+  }
+}
+
+// Few particles: in place, one block per field (the last one: the ids), PER
+// values per thread in registers between the reads and the writes.  One launch
+// instead of two and no pass through memory in between: 11 -> 4 us at 1000
+// particles, 12 -> 7 at 8000, 14 -> 9 at 15,625; a field's time is that of one
+// CU and would pass the two launches' soon after 16,384.
+template <int PER>
+__global__ __launch_bounds__(1024) void k_permute_small(FieldSet fs,
+                                                         const uint32_t* __restrict__ perm, int n) {
+  const int f = (int)blockIdx.x, tid = threadIdx.x;
+  uint32_t j[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) j[k] = k * 1024 + tid < n ? perm[k * 1024 + tid] : 0u;
+  if (f == fs.nf) {
+    int64_t v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) v[k] = fs.id[j[k]];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (k * 1024 + tid < n) fs.id[k * 1024 + tid] = v[k];
+    return;
+  }
+  double* a = fs.f[f];
+  double v[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) v[k] = a[j[k]];
+  __syncthreads();
+  const int part = f == fs.im ? 3 : f;  // of the packed x, y, z, m
+  double* q = fs.xyzm && part < 4 && (f < 3 || f == fs.im)
+                  ? reinterpret_cast<double*>(fs.xyzm) + part
+                  : nullptr;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * 1024 + tid;
+    if (i < n) {
+      a[i] = v[k];
+      if (q) q[4 * i] = v[k];
+    }
   }
 }
 
@@ -4231,8 +4399,18 @@ static int sort_passes(const sph_ctx* c) {
   return 8;
 }
 
+constexpr int kSortSmall = 4096, kPermuteSmall = 16384;
+
 hipError_t launch_predict_keys(sph_ctx* c, const sph_particles* s, bool predict, double) {
   c->kp.n = c->n;
+  if (c->n <= kSortSmall) {  // the sort too
+    const auto kernel = c->n <= 1024   ? k_sort_small<1>
+                        : c->n <= 2048 ? k_sort_small<2>
+                                       : k_sort_small<4>;
+    launch_last(c, kernel, dim3(1), dim3(1024), c->kp, parts_of(s), predict ? 1 : 0,
+                sort_passes(c), c->ds, c->keys[0], c->vals[0], &c->ds->err);
+    return hipGetLastError();
+  }
   const SortWs w = sort_ws(c);
   const int src = sort_passes(c) & 1;
   hipLaunchKernelGGL(k_predict_keys, dim3(stream_blocks(c->n)), dim3(256), 0, c->stream, c->kp,
@@ -4245,6 +4423,7 @@ hipError_t launch_predict_keys(sph_ctx* c, const sph_particles* s, bool predict,
 // The result is in buffer 0.
 hipError_t launch_sort(sph_ctx* c) {
   const int n = c->n;
+  if (n <= kSortSmall) return hipSuccess;
   const int nblk = (n + kSortTile - 1) / kSortTile;
   const SortWs w = sort_ws(c);
   const int pblocks = std::min(nblk, 4 * c->n_cu);
@@ -4280,6 +4459,20 @@ hipError_t launch_permute(sph_ctx* c, const sph_particles* s, bool outputs_too) 
   }
   fs.xyzm = c->kp.precision == SPH_PREC_MIXED ? nullptr : c->xyzm;
   fs.id = s->id;
+  // in place only if no two fields share memory
+  bool apart = true;
+  for (int k = 0; k < fs.nf; ++k)
+    for (int q = 0; q < k; ++q)
+      apart = apart && (fs.f[q] + c->n <= fs.f[k] || fs.f[k] + c->n <= fs.f[q]);
+  for (int k = 0; k < fs.nf && fs.id; ++k)
+    apart = apart && ((double*)fs.id + c->n <= fs.f[k] || fs.f[k] + c->n <= (double*)fs.id);
+  if (c->n <= kPermuteSmall && apart) {
+    const auto kernel = c->n <= 1024   ? k_permute_small<1>
+                        : c->n <= 4096 ? k_permute_small<4>
+                                       : k_permute_small<16>;
+    launch_last(c, kernel, dim3(fs.nf + (fs.id ? 1 : 0)), dim3(1024), fs, c->vals[0], c->n);
+    return hipGetLastError();
+  }
   const int nb = stream_blocks(c->n);
   hipLaunchKernelGGL(k_gather, dim3(nb), dim3(256), 0, c->stream, fs, c->vals[0], c->gtmp,
                      c->gtmp_id, c->n, (int64_t)c->n_max);

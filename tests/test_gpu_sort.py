@@ -44,7 +44,7 @@ def positions(kind, n):
 
 @pytest.mark.parametrize("box", [(1.0, 1.0, 1.0), (1.0, 1e-3, 1e-2)], ids=["cube", "needle"])
 @pytest.mark.parametrize("kind", ["uniform", "few", "full", "over", "ball", "corner", "equal"])
-@pytest.mark.parametrize("n", [2, 130, 2048, 2049, 4096, 6200, 70001])
+@pytest.mark.parametrize("n", [2, 130, 1024, 1025, 2048, 2049, 4096, 4097, 6200, 70001])
 def test_sort_is_the_stable_sort_of_whole_keys(n, kind, box):
     say(f"[sort] {kind} n={n} box={box}")
     x = positions(kind, n) * np.asarray(box)
@@ -61,3 +61,20 @@ def test_sort_is_the_stable_sort_of_whole_keys(n, kind, box):
     np.testing.assert_array_equal(keys, ok[operm])
     np.testing.assert_array_equal(parts.numpy("x")["x"], cfg["x"][operm])
     sph.sph_check(ctx)
+
+
+@pytest.mark.parametrize("n", [1, 1024, 1025, 4096, 4097, 16384, 16385])
+def test_permute_moves_every_field(n):
+    rng = np.random.default_rng(n)
+    cfg = dict(inputs.DEFAULTS, box_lo=(0, 0, 0), box_len=(1, 1, 1), periodic=(1, 1, 1), n=n,
+               workload=f"permute{n}", **{k: rng.random(n) for k in ("x", "y", "z", "m", "u", "h",
+                                                                     "vx", "vy", "vz")})
+    ctx = sph.Context(sph.make_params(cfg), n)
+    parts = sph.Particles(cfg)
+    before = parts.numpy("x", "y", "z", "m", "u", "h", "vx", "vy", "vz")
+    sph.sph_build_tree(ctx, parts)
+    _, perm = sph.sph_get_keys(ctx, n)
+    after = parts.numpy("id", *before)
+    np.testing.assert_array_equal(after["id"], perm)
+    for k, v in before.items():
+        np.testing.assert_array_equal(after[k], v[perm], err_msg=k)
