@@ -3598,15 +3598,18 @@ void k_density_lists(KParams kp, Parts p,
   const int4* __restrict__ qpos = reinterpret_cast<const int4*>(pos);
   const float qsx = ds->qf.step[0], qsy = ds->qf.step[1], qsz = ds->qf.step[2];
 
-  // groups the list kernel flagged are left to the walking kernel; their
-  // flags are looked up only if there are any
-  const bool any_flag = ds->n_flagged != 0;
+  // groups the list kernel flagged (1) are left to the walking kernel; their
+  // flags are looked up only if there are any.  Those that this kernel flags
+  // (2) are not looked at: whether one is seen in time would depend on the
+  // order of the wavefronts, and with it where the walking kernel's iteration
+  // starts and what it counts.
+  const bool any_flag = ds->n_flag_rows != 0;
 
   for (int g = gr.beg; g < gr.end; g += gr.step) {
     const int first = g * CS, count = min(CS, kp.n - first);
     const bool inr = slot < count;
     const int i = first + (inr ? slot : 0);
-    const bool act = inr && (!any_flag || gflag[grp_of[i]] == 0);
+    const bool act = inr && (!any_flag || gflag[grp_of[i]] != 1);
     if (any_flag && ballot64(act) == 0ull) continue;
     const double mi = p.m[i];
     double h = p.h[i];

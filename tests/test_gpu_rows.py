@@ -92,3 +92,25 @@ def test_rows_hold_the_walks_sets(n, clump, n_group, precision):
         np.testing.assert_array_equal(off, woff)
         np.testing.assert_array_equal(idx, widx)
     ctx.close()
+
+
+@pytest.mark.parametrize("precision", [sph.SPH_PREC_FP64, sph.SPH_PREC_MIXED])
+def test_outgrown_rows_give_the_same_bits_again(precision):
+    """Groups whose h outgrows their rows: which wavefront flags one first must
+    not show in the results or in the counts."""
+    cfg = inputs.lattice(40, jitter=0.3)
+    cfg["h"] = cfg["h"] * np.random.default_rng(3).uniform(0.85, 1.1, cfg["n"])
+    seen = []
+    for _ in range(2):
+        parts = sph.Particles(cfg)
+        ctx = sph.Context(sph.make_params(cfg, precision), cfg["n"])
+        sph.sph_build_tree(ctx, parts)
+        sph.sph_density(ctx, parts)
+        sph.sph_force(ctx, parts)
+        stats = sph.sph_stats(ctx)
+        assert stats["groups_h_outgrew"] > 100
+        seen.append((parts.numpy("h", "rho", "ax", "dudt"), stats))
+    for k, v in seen[0][0].items():
+        np.testing.assert_array_equal(v, seen[1][0][k], err_msg=k)
+    for k in ("groups_h_outgrew", "density_pairs", "density_pair_sums", "density_candidates"):
+        assert seen[0][1][k] == seen[1][1][k], k
