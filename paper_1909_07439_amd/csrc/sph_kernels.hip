@@ -4753,11 +4753,18 @@ hipError_t launch_force(sph_ctx* c, const sph_particles* s, bool step_mode, bool
                                            : force_dispatch<false>(c, s, o[0], o[1], o[2], o[3], gf);
 }
 
+// Lanes per particle: 64 / n_group, but 16 in FP64 as long as chunks of eight
+// particles would leave SIMDs without a wavefront.  A wavefront alone on its
+// SIMD waits for each block of gathered records, so half the row per lane is
+// half the blocks: 19.5 -> 13.5 us at 1000 particles, 19.5 -> 14.0 at 4096;
+// even at 13,824 (25.6 and 26.6), worse beyond (230 and 251 at 262,144).  The
+// FP32 sums of the mixed mode keep their lanes.
 template <bool MIXED, int KIND>
 static void force_lists_kind(sph_ctx* c, const Parts& p, double* const* o) {
+  const int n_group = !MIXED && c->n <= 8 * 4 * c->n_cu ? 4 : c->kp.n_group;
   const int waves = force_waves(MIXED) * 4 * c->n_cu;  // resident at once
   const dim3 grid(std::max(waves / kForceWpb / 8 * 8, 8)), block(kWave * kForceWpb);
-  SPH_LPI_SWITCH_LISTS(c->kp.n_group,
+  SPH_LPI_SWITCH_LISTS(n_group,
                        launch_last(c, (k_force_lists<MIXED, LPI, KIND>), grid, block, c->kp, p,
                                    c->ginfo, c->frec, c->nl_idx, c->nl_len, c->gflag, c->grp_of,
                                    o[0], o[1], o[2], o[3], c->ds));

@@ -52,6 +52,25 @@ def test_density_of_ragged_rows(n, kernel, n_group, precision):
         assert e <= t, (k, e)
 
 
+@pytest.mark.parametrize("kernel", ["m4", "wc6"])
+@pytest.mark.parametrize("n", [9, 1003, 8191, 8192, 8193])
+def test_force_of_ragged_rows_fp64(n, kernel):
+    """Either side of the particle count up to which more lanes share a row;
+    tolerance as of the density, relative to the pair terms' magnitudes."""
+    cfg = cloud(n, kernel, 11 + n)
+    rng = np.random.default_rng(n)
+    for k in ("vx", "vy", "vz"):
+        cfg[k] = rng.normal(0.0, 0.1, n)
+    o = oracle.evaluate(cfg, oracle.make_params(cfg))
+    out, ctx, _, info = gpu_eval(cfg)
+    sph.sph_check(ctx)
+    assert info["stats"]["force_pairs"] == int(o["nneigh_force"].sum())
+    for k, nk in (("ax", "anorm"), ("ay", "anorm"), ("az", "anorm"), ("dudt", "unorm")):
+        e = float((np.abs(out[k] - o[k]) / np.maximum(o[nk], 1e-300)).max())
+        say(f"  {k}: {e:.2e}")
+        assert e <= 1e-12, (k, e)
+
+
 def blobs(n, seed, clump=0):
     """Two jittered blobs in opposite corners of an open box (the curve jumps
     between them), with `clump` particles of one at one point: coincident
