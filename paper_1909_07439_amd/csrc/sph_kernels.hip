@@ -1233,14 +1233,15 @@ __global__ __launch_bounds__(256) void k_tree_emit(
   __shared__ uint32_t gw[4];
   __shared__ uint8_t s_d[kTreeTile + kHalo];  // start levels from the tile's first particle on
   const int n_nodes = (int)tree_off[kLevels * nblk];
+  // a tree that outgrew the node arrays is reported and left empty, so that no
+  // later launch reads or writes past them
+  const bool fits = n_nodes >= 0 && (int64_t)n_nodes <= node_cap;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ds->n_nodes = n_nodes;
-    ds->n_groups = (int)(*total - (uint32_t)n_nodes);
+    ds->n_nodes = fits ? n_nodes : 0;
+    ds->n_groups = fits ? (int)(*total - (uint32_t)n_nodes) : 0;
+    if (!fits) atomicOr(&ds->err, kErrNodes);
   }
-  if ((int64_t)n_nodes > node_cap || n_nodes < 0) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&ds->err, kErrNodes);
-    return;
-  }
+  if (!fits) return;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int s = blockIdx.x * kTreeTile + tid;
   const bool valid = s < n;
@@ -1312,17 +1313,6 @@ __global__ __launch_bounds__(256) void k_tree_emit(
   }
 }
 
-// If the tree outgrew the node arrays, report it and leave an empty tree so
-// that no later launch reads or writes past the arrays (one thread, after
-// k_tree_emit; repeating it changes nothing).
-__device__ __forceinline__ void tree_guard(DevState* ds, int64_t node_cap) {
-  if ((int64_t)ds->n_nodes > node_cap || ds->n_nodes < 0) {
-    atomicOr(&ds->err, kErrNodes);
-    ds->n_nodes = 0;
-    ds->n_groups = 0;
-  }
-}
-
 // ---- node and group boxes and largest h -----------------------------------
 // Every leaf and group covers a contiguous range of the sorted particles:
 // k_range_boxes reduces each one's particles (four per wavefront, 16 lanes
@@ -1391,14 +1381,15 @@ __device__ __forceinline__ void write_group_box(const Box7& b, int g, int f, int
   }
 }
 
-__global__ void k_tree_guard(DevState* __restrict__ ds, int64_t node_cap) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) tree_guard(ds, node_cap);
-}
+constexpr int kNoChunks = 2048;
 
 // Small trees: every inner node by one wavefront, in the launch of the leaves
 // and groups, from the particles of its range and the boxes of the whole
 // kChunk-particle chunks inside it (k_chunk_boxes); its range ends where its
 // next sibling starts, or, for a last child, where its parent's range ends.
+// Up to kNoChunks particles the particles alone: the chunk boxes' launches take
+// longer than the reads that they spare (boxes and refresh of a step: 16.6 ->
+// 12.6 us at 1000 particles, 23 -> 18 at 1728; 22 -> 26 at 3375).
 // One launch instead of one per level; on large trees the chunks' particles
 // are read by many nodes of the lower levels, and the per-level launches win.
 __device__ __forceinline__ void wave_box(Box7& b, int do_bb) {
@@ -1436,10 +1427,7 @@ __global__ __launch_bounds__(256) void k_chunk_boxes(const double* __restrict__ 
                                                       const double* __restrict__ z,
                                                       const double* __restrict__ h, int n,
                                                       double* __restrict__ cb,
-                                                      DevState* __restrict__ ds, int mode,
-                                                      int64_t node_cap) {
-  // boxes of a new tree: its node count is checked before k_range_boxes reads it
-  if (mode == 1 && blockIdx.x == 0 && threadIdx.x == 0) tree_guard(ds, node_cap);
+                                                      const DevState* __restrict__ ds, int mode) {
   if (!h_refresh_needed(ds, mode)) return;
   const int do_bb = mode == 1 ? 1 : 0;
   const int nch = (n + kChunk - 1) / kChunk;
@@ -1489,7 +1477,7 @@ __device__ void inner_ranges(int blk, int nblocks, const double* __restrict__ x,
     Box7 b;
     box_empty(b);
     const int c0 = (f + kChunk - 1) / kChunk, c1 = e / kChunk;
-    if (c1 > c0) {
+    if (c1 > c0 && n > kNoChunks) {
       add_particles(b, f, c0 * kChunk, x, y, z, h, do_bb);
       for (int c = c0 + lane_id(); c < c1; c += kWave) {
         const double* q = cb + 8 * (int64_t)c;
@@ -4512,7 +4500,7 @@ hipError_t launch_tree(sph_ctx* c) {
                      c->scan_total, nblk, c->node_cap, c->node_level, c->node_first,
                      c->node_count, c->node_parent, c->node_child, c->node_nchild,
                      c->grp_first, c->grp_count, c->ds);
-  return hipGetLastError();  // node_props checks the node count (tree_guard)
+  return hipGetLastError();
 }
 
 // Node boxes (positions) and largest h; group boxes.  The positions are the
@@ -4524,13 +4512,10 @@ static hipError_t node_props(sph_ctx* c, const sph_particles* s, int mode) {
   // per wavefront in the same launch (from chunk boxes), large trees: one
   // launch per level afterwards (the deepest first; the last level holds
   // leaves only; the level offsets are the scanned per-level node counts).
-  // A new tree's node count is checked before the box kernels read it.
-  if (small) {
+  if (small && n > kNoChunks) {
     const int nch = (n + kChunk - 1) / kChunk;
     hipLaunchKernelGGL(k_chunk_boxes, dim3((nch + 3) / 4), dim3(256), 0, c->stream, s->x, s->y,
-                       s->z, s->h, n, c->chunk_box, c->ds, mode, c->node_cap);
-  } else if (mode == 1) {
-    hipLaunchKernelGGL(k_tree_guard, dim3(1), dim3(64), 0, c->stream, c->ds, c->node_cap);
+                       s->z, s->h, n, c->chunk_box, c->ds, mode);
   }
   const int64_t items = c->node_cap + (int64_t)n;
   const int nb = (int)std::min<int64_t>(std::max<int64_t>((items / 4 + 15) / 16, 16), 4096);
@@ -4729,7 +4714,8 @@ template <bool MIXED>
 static hipError_t force_dispatch(sph_ctx* c, const sph_particles* s, double* oax, double* oay,
                                  double* oaz, double* odu, const int32_t* gflag) {
   const Parts p = parts_of(s);
-  const dim3 grid(gflag ? flagged_blocks(c) : c->walk_blocks), block(64);
+  // (with lists, every group walks once some h has outgrown its rows)
+  const dim3 grid(gflag ? std::min((c->n + 7) / 8 * 8, c->walk_blocks) : c->walk_blocks), block(64);
   SPH_LPI_SWITCH(c->kp.n_group,
                  launch_last(c, (k_force<MIXED, LPI>), grid, block, c->kp, p, c->wnode, c->ginfo,
                              c->frec, c->leaf_pool, c->gl_off, c->gl_cnt, oax, oay, oaz, odu, gflag,
@@ -4754,16 +4740,24 @@ hipError_t launch_force(sph_ctx* c, const sph_particles* s, bool step_mode, bool
 }
 
 // Lanes per particle: 64 / n_group, but 16 in FP64 as long as chunks of eight
-// particles would leave SIMDs without a wavefront.  A wavefront alone on its
-// SIMD waits for each block of gathered records, so half the row per lane is
-// half the blocks: 19.5 -> 13.5 us at 1000 particles, 19.5 -> 14.0 at 4096;
-// even at 13,824 (25.6 and 26.6), worse beyond (230 and 251 at 262,144).  The
-// FP32 sums of the mixed mode keep their lanes.
+// particles would leave SIMDs without a wavefront, and 32 for half of those
+// sizes.  A wavefront alone on its SIMD waits for each block of gathered
+// records, so half the row per lane is half the blocks: 8, 16 and 32 lanes
+// 19.5, 13.4 and 10.2 us at 1000 particles, 19.5, 13.5 and 13.0 at 3375; 25.6
+// and 26.6 with 8 and 16 at 13,824, worse beyond (230 and 251 at 262,144).
+// The FP32 sums of the mixed mode keep their lanes.
 template <bool MIXED, int KIND>
 static void force_lists_kind(sph_ctx* c, const Parts& p, double* const* o) {
   const int n_group = !MIXED && c->n <= 8 * 4 * c->n_cu ? 4 : c->kp.n_group;
   const int waves = force_waves(MIXED) * 4 * c->n_cu;  // resident at once
   const dim3 grid(std::max(waves / kForceWpb / 8 * 8, 8)), block(kWave * kForceWpb);
+  if constexpr (!MIXED) {
+    if (c->n <= 8 * 2 * c->n_cu) {
+      launch_last(c, (k_force_lists<MIXED, 32, KIND>), grid, block, c->kp, p, c->ginfo, c->frec,
+                  c->nl_idx, c->nl_len, c->gflag, c->grp_of, o[0], o[1], o[2], o[3], c->ds);
+      return;
+    }
+  }
   SPH_LPI_SWITCH_LISTS(n_group,
                        launch_last(c, (k_force_lists<MIXED, LPI, KIND>), grid, block, c->kp, p,
                                    c->ginfo, c->frec, c->nl_idx, c->nl_len, c->gflag, c->grp_of,
