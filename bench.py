@@ -397,9 +397,11 @@ def main():
         lpl = st["list_candidates_per_launch"]
         # row entries written per launch = the entries the force kernel reads
         rpl = st["force_candidates"]
-        rl = roofline(f"k_lists<{tag}>", LIST_FLOPS_PER_ENTRY * rpl, tim["lists"],
+        # the lists are two kernels: the leaf walks and the rows
+        both = [traffic_record(k, cfg, tag) for k in ("k_leaves", "k_rows")]
+        rl = roofline(f"k_leaves + k_rows<{tag}>", LIST_FLOPS_PER_ENTRY * rpl, tim["lists"],
                       {"row_entries": rpl}, LIST_FLOPS_PER_ENTRY,
-                      traffic_record("k_lists", cfg, tag))
+                      None if None in both else sum(both))
         rl["candidate_tests_per_row_entry"] = lpl / max(rpl, 1)
         rl["candidate_tests_per_force_pair"] = lpl / max(fpl, 1)
         kernels.append((tim["lists"], rl))
