@@ -2977,6 +2977,17 @@ __device__ __forceinline__ float list_thr(float support, float x, float w) {
   return fmaf(2e-6f * w, s, s * s * 1.00001f);
 }
 
+// The FP32 tests of the list kernels take lengths times 2^e, e from a group's
+// (or part's) own radius r: exact, so it changes no test, but the squares then
+// neither overflow nor vanish in any unit of length (unscaled, radii beyond
+// 1.8e19 or below 1e-22 lost neighbours).  e is 0 for r in 2^-32 .. 2^32, where
+// FP32 holds the squares as they are, and otherwise brings r to 1 .. 2.
+__device__ __forceinline__ int list_exponent(double r) {
+  if (!(r > 0.0) || !isfinite(r)) return 0;
+  const int e = -ilogb(r);
+  return __builtin_amdgcn_readfirstlane(abs(e) <= 32 ? 0 : min(max(e, -1000), 1000));
+}
+
 // Groups per unit of k_leaves (its log2): kSGL, or fewer on sets too small to
 // give every fourth wavefront a unit of that size.
 __device__ __forceinline__ int unit_shift(int ng, int nwaves) {
@@ -3148,15 +3159,20 @@ void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
           w[a] = fmax(hi - c[a], c[a] - lo);
         }
         const double hl = kp.h_margin * wave_max_f64(in ? Gk.hmax : 0.0);
+        const int se = list_exponent(hl);  // of the FP32 lengths below
         __syncthreads();
         if (in) {
           // FP32 offsets from the part's centre
-          s_g[lane][0] = make_float4((float)(Gk.c[0] - c[0]), (float)(Gk.c[1] - c[1]),
-                                     (float)(Gk.c[2] - c[2]), (float)(kp.h_margin * Gk.hmax));
-          s_g[lane][1] = make_float4((float)Gk.w[0], (float)Gk.w[1], (float)Gk.w[2], 0.f);
+          s_g[lane][0] = make_float4((float)ldexp(Gk.c[0] - c[0], se),
+                                     (float)ldexp(Gk.c[1] - c[1], se),
+                                     (float)ldexp(Gk.c[2] - c[2], se),
+                                     (float)ldexp(kp.h_margin * Gk.hmax, se));
+          s_g[lane][1] = make_float4((float)ldexp(Gk.w[0], se), (float)ldexp(Gk.w[1], se),
+                                     (float)ldexp(Gk.w[2], se), 0.f);
         }
         // bound of the FP32 offsets' rounding within the part's reach
-        const float eps = (float)(1e-6 * (fmax(w[0], fmax(w[1], w[2])) + kp.support * hl));
+        const float eps =
+            (float)ldexp(1e-6 * (fmax(w[0], fmax(w[1], w[2])) + kp.support * hl), se);
         __syncthreads();
         int n = 0;
         const bool fits =
@@ -3173,15 +3189,18 @@ void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
             bool amb = false;
 #pragma unroll
             for (int a = 0; a < 3; ++a) amb |= kp.periodic[a] && fabs(dc[a]) + w[a] > kp.half[a];
-            const float x = (float)dc[0], y = (float)dc[1], z = (float)dc[2];
-            const float e4 = 4.f * fmaf(1e-6f, fmaxf(nd.w[0], fmaxf(nd.w[1], nd.w[2])), eps);
+            const float x = (float)ldexp(dc[0], se), y = (float)ldexp(dc[1], se),
+                        z = (float)ldexp(dc[2], se);
+            const float nwx = ldexpf(nd.w[0], se), nwy = ldexpf(nd.w[1], se),
+                        nwz = ldexpf(nd.w[2], se), nh = margin * ldexpf(nd.hmax, se);
+            const float e4 = 4.f * fmaf(1e-6f, fmaxf(nwx, fmaxf(nwy, nwz)), eps);
             uint32_t border = 0;
             for (int gk = a0; gk < a1; ++gk) {
               const float4 gc = s_g[gk][0], gw = s_g[gk][1];
-              const float dx = fmaxf(fabsf(x - gc.x) - (nd.w[0] + gw.x), 0.f);
-              const float dy = fmaxf(fabsf(y - gc.y) - (nd.w[1] + gw.y), 0.f);
-              const float dz = fmaxf(fabsf(z - gc.z) - (nd.w[2] + gw.z), 0.f);
-              const float R = S * fmaxf(gc.w, margin * nd.hmax);
+              const float dx = fmaxf(fabsf(x - gc.x) - (nwx + gw.x), 0.f);
+              const float dy = fmaxf(fabsf(y - gc.y) - (nwy + gw.y), 0.f);
+              const float dz = fmaxf(fabsf(z - gc.z) - (nwz + gw.z), 0.f);
+              const float R = S * fmaxf(gc.w, nh);
               const float t = fmaf(dz, dz, fmaf(dy, dy, dx * dx)) - R * R;
               const float tol = R * fmaf(4e-5f, R, e4);
               bits |= t < 0.f ? 1u << (24 + gk) : 0u;
@@ -3324,7 +3343,10 @@ void k_rows(KParams kp, const double* __restrict__ hp, const WalkNode* __restric
     const bool fary = kp.periodic[1] && gwy + reach >= kp.half[1];
     const bool farz = kp.periodic[2] && gwz + reach >= kp.half[2];
     const bool amb = farx || fary || farz;
-    float wr = 0.f;  // distance at which FP64 offsets may have been rounded
+    // FP64: the lengths' power of two in the FP32 tests, and the distance at
+    // which offsets may have been rounded
+    int se = 0;
+    float wr = 0.f;
     int32_t qgx = 0, qgy = 0, qgz = 0;
     if constexpr (MIXED) {
       const QFrame& qf = ds->qf;
@@ -3332,8 +3354,10 @@ void k_rows(KParams kp, const double* __restrict__ hp, const WalkNode* __restric
       qgy = qcode(gcy, qf, 1, kp.periodic[1]);
       qgz = qcode(gcz, qf, 2, kp.periodic[2]);
     } else {
-      wr = (float)fmax(gwx + (farx ? kp.len[0] : 0.0),
-                       fmax(gwy + (fary ? kp.len[1] : 0.0), gwz + (farz ? kp.len[2] : 0.0)));
+      se = list_exponent(groups[g].hmax);
+      wr = (float)ldexp(fmax(gwx + (farx ? kp.len[0] : 0.0),
+                             fmax(gwy + (fary ? kp.len[1] : 0.0), gwz + (farz ? kp.len[2] : 0.0))),
+                        se);
     }
     // a particle as the tests take it: its offset and its squared radius
     struct Raw {
@@ -3359,10 +3383,20 @@ void k_rows(KParams kp, const double* __restrict__ hp, const WalkNode* __restric
         c.z = qsep(r.q.z, qgz, stz);
         c.w = list_thr(S, marginf * __int_as_float(r.q.w), 0.f);
       } else {
-        c.x = (float)fold(r.d.x - gcx, kp.len[0], kp.half[0], kp.periodic[0]);
-        c.y = (float)fold(r.d.y - gcy, kp.len[1], kp.half[1], kp.periodic[1]);
-        c.z = (float)fold(r.d.z - gcz, kp.len[2], kp.half[2], kp.periodic[2]);
-        c.w = list_thr(S, (float)(kp.h_margin * r.h), wr);
+        double dx = fold(r.d.x - gcx, kp.len[0], kp.half[0], kp.periodic[0]);
+        double dy = fold(r.d.y - gcy, kp.len[1], kp.half[1], kp.periodic[1]);
+        double dz = fold(r.d.z - gcz, kp.len[2], kp.half[2], kp.periodic[2]);
+        double hl = kp.h_margin * r.h;
+        if (__builtin_expect(se != 0, 0)) {
+          dx = ldexp(dx, se);
+          dy = ldexp(dy, se);
+          dz = ldexp(dz, se);
+          hl = ldexp(hl, se);
+        }
+        c.x = (float)dx;
+        c.y = (float)dy;
+        c.z = (float)dz;
+        c.w = list_thr(S, (float)hl, wr);
       }
       return c;
     };
@@ -3413,9 +3447,9 @@ void k_rows(KParams kp, const double* __restrict__ hp, const WalkNode* __restric
             float dx = px - c[q].x, dy = py - c[q].y, dz = pz - c[q].z;
             if constexpr (FOLD) {
               auto nearest = [&](float d, int a) {
-                return kp.periodic[a]
-                           ? fmaf(-(float)kp.len[a], rintf(d * (float)kp.inv_len[a]), d)
-                           : d;
+                return kp.periodic[a] ? fmaf(-(float)ldexp(kp.len[a], se),
+                                             rintf(d * (float)ldexp(kp.inv_len[a], -se)), d)
+                                      : d;
               };
               dx = nearest(dx, 0);
               dy = nearest(dy, 1);
