@@ -17,6 +17,15 @@ constexpr int kNLCapMax = 256;  // largest neighbour-list row (entries)
 constexpr int kChunk = 256;     // particles per chunk box (inner-node boxes of small trees)
 constexpr int kSmallTree = 1 << 21;  // particles up to which inner nodes take one launch
 constexpr int kSpill = 4096;    // walk frontier entries per level beyond LDS, per wavefront
+constexpr int kLeafWaves = 6;   // wavefronts per SIMD of the list kernels' tree walk
+// Wavefronts of that walk: as many as are resident at once.
+inline int leaf_walk_waves(int n_cu) { return kLeafWaves * 4 * n_cu / 8 * 8; }
+// Leaf-list space, in units of 16 entries per particle.  A tree of leaves of
+// up to 8 particles can have one leaf per particle (a cell of 2^3 lattice
+// sites splits into eight leaves at n_leaf 7), and eight groups then reach
+// some 1000 leaves: with the space and the limit of larger leaves a third of
+// the groups of 64^3 particles (M6, Wendland C6) had no list.
+__host__ __device__ constexpr int leaf_list_factor(int n_leaf) { return n_leaf < 8 ? 4 : 1; }
 
 // Per-particle data the force loop reads for a neighbour j (written by the
 // density pass once h, rho, Omega are final).
@@ -95,7 +104,7 @@ struct sph_ctx {
   int32_t* nl_len = nullptr;   // entries found per particle (may exceed kp.nl_cap)
   int32_t* gflag = nullptr;    // per group: 0 lists complete, 1 row overflow, 2 h outgrew rows
   int32_t* flag_list = nullptr;  // indices of the flagged groups (DevState::n_flagged of them)
-  int32_t* walk_spill = nullptr; // 2 * kSpill frontier entries per walk wavefront
+  int32_t* walk_spill = nullptr; // 2 * kSpill frontier entries per wavefront of a tree walk
   int32_t* grp_of = nullptr;     // group of each particle (neighbour-list kernel)
   int4* qrec = nullptr;          // mixed: position codes (DevState::qf) and h as FP32, key order
   // density / force

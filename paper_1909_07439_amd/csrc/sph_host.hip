@@ -335,7 +335,8 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   ALLOC(c->grp_first, N);
   ALLOC(c->grp_count, N);
   ALLOC(c->ginfo, N);
-  c->pool_cap = std::min<int64_t>(16 * N + 256 * (int64_t)c->walk_blocks, 0x7fffffff);
+  c->pool_cap = std::min<int64_t>(
+      16 * sph::leaf_list_factor(P.n_leaf) * N + 256 * (int64_t)c->walk_blocks, 0x7fffffff);
   ALLOC(c->leaf_pool, c->pool_cap);
   ALLOC(c->gl_off, N);
   ALLOC(c->gl_cnt, N);
@@ -343,7 +344,8 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   ALLOC(c->nl_len, N);
   ALLOC(c->gflag, N);
   ALLOC(c->flag_list, N);
-  ALLOC(c->walk_spill, (int64_t)2 * sph::kSpill * c->walk_blocks);
+  ALLOC(c->walk_spill, (int64_t)2 * sph::kSpill *
+                           std::max(c->walk_blocks, sph::leaf_walk_waves(c->n_cu)));
   ALLOC(c->grp_of, N);
   if (P.precision == SPH_PREC_MIXED) ALLOC(c->qrec, N);
   {

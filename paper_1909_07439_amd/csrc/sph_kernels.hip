@@ -2937,10 +2937,10 @@ __device__ __forceinline__ GroupRange xcd_items(int n) {
 // ============================================================================
 constexpr int kSGLShift = 3;
 constexpr int kSGL = 1 << kSGLShift;  // groups per super-group of the list kernels
-constexpr int kSLCapL = 512;  // leaves a list-kernel walk may collect
+constexpr int kSLCapL = 512;  // leaves a list-kernel walk may collect (trees of small leaves: more)
+constexpr int kOwnParticles = 16384;  // particles that the leaves of a single group's list may hold
 constexpr int kLeafPart = 64; // particles per leaf-list entry at most (>= the largest n_leaf)
-constexpr int kLeafWaves = 6; // wavefronts per SIMD of k_leaves
-constexpr int kRowWaves = 8;  // and of k_rows
+constexpr int kRowWaves = 8;  // wavefronts per SIMD of k_rows
 constexpr int kNoLeaves = -0x7fffffff;  // ll_cnt of a group whose walk failed
 
 // The value a wave-uniform lane `l` holds, as a wave-uniform scalar.
@@ -2995,9 +2995,10 @@ __device__ __forceinline__ int unit_shift(int ng, int nwaves) {
   while (u > 0 && (ng >> u) < nwaves / 4) --u;
   return u;
 }
-// Entries of a unit's leaf list: an equal share of the list space.
-__device__ __forceinline__ int leaf_list_cap(int64_t entries, int nu) {
-  return (int)min((int64_t)kSLCapL, entries / max(nu, 1));
+// Entries of a unit's leaf list: an equal share of the list space, at most
+// kSLCapL of them, or as many more as the space grows for small leaves.
+__device__ __forceinline__ int leaf_list_cap(int64_t entries, int nu, int n_leaf) {
+  return (int)min((int64_t)kSLCapL * leaf_list_factor(n_leaf), entries / max(nu, 1));
 }
 
 // Separation of a node's centre from c along the nearest periodic image, and
@@ -3022,26 +3023,26 @@ __device__ __forceinline__ double node_gap2(const WalkNode& nd, const double (&c
 // the box (c, w): visit(leaf, node, dc) is called by all lanes for every batch
 // of up to 64 nodes, with leaf set in the lanes that hold an opened leaf, and
 // ends the walk by returning false.  A level's frontier holds kFCap entries in
-// LDS and continues in this wavefront's region of global memory (spill_cap
+// LDS and continues in this wavefront's region of global memory (kSpill
 // entries per level).  Returns false if the walk ended early or its frontier
 // overflowed.
 template <typename Visit>
 __device__ __forceinline__ bool leaf_walk(const WalkNode* __restrict__ nodes, int n01, int n012,
                                           const double (&c)[3], const double (&w)[3], double hl,
                                           const KParams& kp, int (&front)[2][kFCap],
-                                          int* __restrict__ spill, int spill_cap, Visit visit) {
+                                          int* __restrict__ spill, Visit visit) {
   const int lane = threadIdx.x;
-  const int cap = kFCap + spill_cap;
+  constexpr int cap = kFCap + kSpill;
   auto fget = [&](int lvl, int k) -> int {
     return k < kFCap ? front[lvl][k]
-                     : __hip_atomic_load(&spill[lvl * spill_cap + (k - kFCap)], __ATOMIC_RELAXED,
+                     : __hip_atomic_load(&spill[lvl * kSpill + (k - kFCap)], __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
   };
   auto fput = [&](int lvl, int k, int v) {
     if (k < kFCap)
       front[lvl][k] = v;
     else
-      __hip_atomic_store(&spill[lvl * spill_cap + (k - kFCap)], v, __ATOMIC_RELAXED,
+      __hip_atomic_store(&spill[lvl * kSpill + (k - kFCap)], v, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   };
   // the first frontier: nodes 0 .. n012 - 1, of which the first n01 (levels 0
@@ -3100,16 +3101,15 @@ void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
               const GroupInfo* __restrict__ groups, const uint32_t* __restrict__ level_off,
               int nblk, int2* __restrict__ sg_list, int64_t sg_entries, int2* __restrict__ pool,
               int pool_cap, int32_t* __restrict__ ll_off, int32_t* __restrict__ ll_cnt,
-              int32_t* __restrict__ gflag, int32_t* __restrict__ walk_spill, int spill_cap,
-              DevState* __restrict__ ds) {
-  int* __restrict__ spill = walk_spill + (int64_t)blockIdx.x * 2 * spill_cap;
+              int32_t* __restrict__ gflag, int32_t* __restrict__ walk_spill, DevState* __restrict__ ds) {
+  int* __restrict__ spill = walk_spill + (int64_t)blockIdx.x * 2 * kSpill;
   __shared__ int front[2][kFCap];
   __shared__ float4 s_g[kSGL][2];  // per group: box centre from the part's, h_l; half-widths
   const int lane = threadIdx.x;
   const int ng = ds->n_groups;
   const int ush = unit_shift(ng, (int)gridDim.x), usz = 1 << ush;
   const int nu = (ng + usz - 1) >> ush;
-  const int cap = leaf_list_cap(sg_entries, nu);
+  const int cap = leaf_list_cap(sg_entries, nu, kp.n_leaf);
   const int n01 = (int)level_off[2 * nblk], n012 = (int)level_off[3 * nblk];
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, nloc = gridDim.x >> 3;
   const int chunk = (nu + 7) >> 3;
@@ -3143,7 +3143,9 @@ void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
       int a1 = ahead ? min(__builtin_ctzll(ahead), ngs) : ngs;
       // The part [a0, a1) into the unit's list, halved until it fits (kUnit);
       // a single group that still does not fit counts its leaves (kCount) and
-      // then writes them to space taken from the pool (kPool).
+      // then writes them to space taken from the pool (kPool); leaves of far
+      // more particles than its rows can take make it a case for the walking
+      // kernels.
       enum { kUnit, kCount, kPool };
       int mode = kUnit, off = 0, room = cap - used;
       int2* __restrict__ list = sg_list + base + used;
@@ -3176,7 +3178,7 @@ void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
         __syncthreads();
         int n = 0;
         const bool fits =
-            leaf_walk(nodes, n01, n012, c, w, hl, kp, front, spill, spill_cap,
+            leaf_walk(nodes, n01, n012, c, w, hl, kp, front, spill,
                       [&](bool leaf, const WalkNode& nd, const double (&dc)[3]) {
           if (ballot64(leaf) == 0ull) return true;
           uint32_t bits = 0;
@@ -3260,7 +3262,7 @@ void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
             a1 = a0 + (a1 - a0) / 2;
           } else {
             mode = kCount;
-            room = kSLCapL;
+            room = max(kSLCapL, kOwnParticles / kp.n_leaf);
           }
           continue;
         }
@@ -3304,7 +3306,7 @@ void k_rows(KParams kp, const double* __restrict__ hp, const WalkNode* __restric
   const int lane = threadIdx.x;
   const int ng = ds->n_groups;
   const int ush = unit_shift(ng, leaf_grid);
-  const int ucap = leaf_list_cap(sg_entries, (ng + (1 << ush) - 1) >> ush);
+  const int ucap = leaf_list_cap(sg_entries, (ng + (1 << ush) - 1) >> ush, kp.n_leaf);
   int psh = 0;
   while (psh < 2 && (ng << (psh + 1)) <= (int)gridDim.x) ++psh;
   const GroupRange gr = xcd_groups(ng << psh);
@@ -4679,13 +4681,11 @@ hipError_t launch_lists(sph_ctx* c, const sph_particles* s) {
   // As many wavefronts as are resident at once: the items go round them, and a
   // second generation of wavefronts would run alone at the end (k_rows asked
   // for 8 per SIMD with 6 resident: 428 us instead of 362 at 10^6 particles).
-  // The walk wavefronts' spill space is shared out over k_leaves' wavefronts.
-  const int grid = kLeafWaves * 4 * c->n_cu / 8 * 8;
+  const int grid = leaf_walk_waves(c->n_cu);
   const int row_grid = kRowWaves * 4 * c->n_cu / 8 * 8;
-  const int spill_cap = (int)((int64_t)kSpill * c->walk_blocks / grid);
   hipLaunchKernelGGL(k_leaves, dim3(grid), dim3(64), 0, c->stream, c->kp, c->wnode, c->ginfo,
                      c->tree_cnt, nblk, sg_list, sg_entries, pool, pool_cap, ll_off, ll_cnt,
-                     c->gflag, c->walk_spill, spill_cap, c->ds);
+                     c->gflag, c->walk_spill, c->ds);
   const auto rows = c->kp.precision == SPH_PREC_MIXED ? k_rows<true> : k_rows<false>;
   launch_last(c, rows, dim3(row_grid), dim3(64), c->kp, s->h, c->wnode, c->ginfo, sg_list,
               sg_entries, grid, pool, ll_off, ll_cnt, c->nl_idx, c->nl_len, c->gflag,
