@@ -607,6 +607,8 @@ static sph_status adj_launch(sph_ctx* c, const sph_particles* p, sph_cotangents*
 static sph_status adj_rows(sph_ctx* c, const sph_particles* p) {
   sph_status st = sync_state(c, true);
   if (st != SPH_OK) return st;
+  if (c->hs->n_groups == 0)
+    return fail(c, SPH_E_OVERFLOW, "adjoint: the last tree did not fit its node arrays");
   if (c->hs->n_flagged == 0) return SPH_OK;
   HIPCHK(c, sph::launch_node_h(c, p, true));
   HIPCHK(c, sph::launch_leaf_state(c, 1));

@@ -1218,6 +1218,13 @@ __global__ __launch_bounds__(256) void k_tree_levels(const uint64_t* __restrict_
   if (blockIdx.x == 0 && threadIdx.x < 3) tree_cnt[(kLevels + 1) * nblk + threadIdx.x] = 0;
 }
 
+// State of the list kernels on a tree without groups: all particles flagged,
+// the force left to the walk (of no group).
+__device__ __forceinline__ void no_rows(DevState* ds) {
+  ds->n_flag_rows = 1;
+  ds->leaf_state = 2;
+}
+
 // tree_off: exclusive prefix of the node counts, level by level, then of the
 // group counts; total: nodes and groups together.
 __global__ __launch_bounds__(256) void k_tree_emit(
@@ -1227,24 +1234,37 @@ __global__ __launch_bounds__(256) void k_tree_emit(
     const uint32_t* __restrict__ total, int nblk, int64_t node_cap,
     int32_t* __restrict__ nlevel, int32_t* __restrict__ nfirst, int32_t* __restrict__ ncount,
     int32_t* __restrict__ nparent, int32_t* __restrict__ nchild, int32_t* __restrict__ nnchild,
-    int32_t* __restrict__ gfirst, int32_t* __restrict__ gcount, DevState* __restrict__ ds) {
+    int32_t* __restrict__ gfirst, int32_t* __restrict__ gcount, int32_t* __restrict__ nl_len,
+    int32_t* __restrict__ grp_of, int32_t* __restrict__ gflag, DevState* __restrict__ ds) {
   __shared__ uint32_t wc[4][kLevels];
   __shared__ uint32_t first[4][kLevels];  // index of a wavefront's first node of a level
   __shared__ uint32_t gw[4];
   __shared__ uint8_t s_d[kTreeTile + kHalo];  // start levels from the tile's first particle on
   const int n_nodes = (int)tree_off[kLevels * nblk];
   // a tree that outgrew the node arrays is reported and left empty, so that no
-  // later launch reads or writes past them
+  // later launch reads or writes past them; its particles have empty rows and
+  // count as one flagged group that no list names, so that the list kernels
+  // pass them over (no list kernel will write rows for them)
   const bool fits = n_nodes >= 0 && (int64_t)n_nodes <= node_cap;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ds->n_nodes = fits ? n_nodes : 0;
     ds->n_groups = fits ? (int)(*total - (uint32_t)n_nodes) : 0;
     if (!fits) atomicOr(&ds->err, kErrNodes);
   }
-  if (!fits) return;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int s = blockIdx.x * kTreeTile + tid;
   const bool valid = s < n;
+  if (!fits) {
+    if (valid) {
+      nl_len[s] = 0;
+      grp_of[s] = 0;
+    }
+    if (s == 0) {
+      gflag[0] = 1;
+      no_rows(ds);
+    }
+    return;
+  }
   const int dsv = valid ? dlev[s] : 99;
   const int ll = valid ? lleaf[s] : -1;
   const bool gs = valid && gstart[s];
@@ -4203,6 +4223,7 @@ __global__ void k_set_leaf_state(DevState* ds, int v) {
     ds->n_flag_grew = 0;
     ds->n_flagged = 0;
     ds->pool_used = 0;
+    if (ds->n_groups == 0) no_rows(ds);
   }
 }
 
@@ -4535,7 +4556,7 @@ hipError_t launch_tree(sph_ctx* c) {
                      c->kp.n_group, c->dlev, c->lleaf, c->gsize, c->gstart, c->tree_cnt,
                      c->scan_total, nblk, c->node_cap, c->node_level, c->node_first,
                      c->node_count, c->node_parent, c->node_child, c->node_nchild,
-                     c->grp_first, c->grp_count, c->ds);
+                     c->grp_first, c->grp_count, c->nl_len, c->grp_of, c->gflag, c->ds);
   return hipGetLastError();
 }
 
