@@ -308,7 +308,7 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   ALLOC(c->vals[0], N);
   ALLOC(c->vals[1], N);
   c->n_max_sort_blocks = nblk_sort;
-  ALLOC(c->radix_cnt, 8 * 256 * nblk_sort + 2 * 8 * 256 + sph::kSortHeadWords +
+  ALLOC(c->radix_cnt, 8 * 256 * nblk_sort + 8 * 256 + sph::kSortHeadWords +
                           4 * std::min<int64_t>((N + 255) / 256, 8192));
   ALLOC(c->scan_part, scan_max / sph::kScanTile + 16);
   ALLOC(c->scan_total, 16);

@@ -272,9 +272,12 @@ __device__ __forceinline__ uint64_t predict_key(const KParams& kp, const Parts& 
 struct SortHead {
   uint32_t tickets[8];     // next tile of every pass
   uint32_t ticket;         // next item of k_resort
-  uint32_t done[9];        // tiles finished in every stage of k_resort
+  uint32_t done[10];       // items finished in every stage of k_resort
+  uint32_t items;          // items of every stage of k_resort but the first
   uint32_t shift;          // lowest key bit the passes sort
   uint32_t resort;         // 1: a long run of equal sorted bits is out of order
+  uint32_t runs;           // long runs listed
+  uint32_t over;           // runs listed that are too long for one block
 };
 
 __device__ __forceinline__ uint64_t wave_or_u64(uint64_t v) {
@@ -296,7 +299,7 @@ __global__ __launch_bounds__(256) void k_predict_keys(KParams kp, Parts p, int p
                                                        uint32_t* __restrict__ err) {
   __shared__ uint64_t wr[4][2];
   if (blockIdx.x == 0) {
-    for (int k = threadIdx.x; k < 2 * 8 * 256; k += blockDim.x) ghist[k] = 0u;
+    for (int k = threadIdx.x; k < 8 * 256; k += blockDim.x) ghist[k] = 0u;
     uint32_t* hw = reinterpret_cast<uint32_t*>(head);
     if (threadIdx.x < sizeof(SortHead) / 4) hw[threadIdx.x] = 0u;
   }
@@ -370,11 +373,10 @@ __device__ __forceinline__ void lds_count_digit(uint32_t* cnt, uint32_t d, bool 
 //
 // A 63-bit key of n particles needs about log2 n bits to tell most particles
 // apart, so the passes sort only the top bits from the highest one that
-// varies (launch_sort chooses their number); k_sort_fix then orders the few
-// runs that agree in all of them, and k_resort sorts everything by all 63
-// bits where a run is too long for that.  What each pass costs is latency
-// (tile count, look-back) at small n, and its 24 bytes per particle at large
-// n: 8.3 us at 32^3, 13.3 at 294,912, 205 at 16.8M particles.
+// varies (launch_sort chooses their number); k_sort_fix then orders the short
+// runs that agree in all of them, and k_resort the longer ones.  What each pass
+// costs is latency (tile count, look-back) at small n, and its 24 bytes per
+// particle at large n: 8.3 us at 32^3, 13.3 at 294,912, 205 at 16.8M particles.
 constexpr uint32_t kStAgg = 1u << 30, kStPre = 2u << 30, kStMask = (1u << 30) - 1u;
 constexpr int kLookbackSpin = 1 << 22;  // bounded wait; the predecessors always publish
 constexpr int kLookW = 16;               // earlier tiles read per look-back round
@@ -446,8 +448,24 @@ struct SortLds {
   int tile;
 };
 
+// Loads and stores of data that passes between blocks within one launch
+// (AGENT): past the L2s, each of which belongs to one XCD.
+template <bool AGENT, typename T>
+__device__ __forceinline__ T tile_load(const T* p) {
+  if constexpr (AGENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return *p;
+}
+template <bool AGENT, typename T>
+__device__ __forceinline__ void tile_store(T* p, T v) {
+  if constexpr (AGENT)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *p = v;
+}
+
 // One tile of one pass: digits (key >> shift) & 255; st: the pass's status
 // words, gh: this thread's digit of the pass's histogram.
+template <bool AGENT>
 __device__ __forceinline__ void radix_tile(SortLds& L, const uint64_t* __restrict__ kin,
                                            const uint32_t* __restrict__ vin,
                                            uint64_t* __restrict__ kout,
@@ -468,8 +486,8 @@ __device__ __forceinline__ void radix_tile(SortLds& L, const uint64_t* __restric
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = base + k * 256 + tid;
-    key[k] = i < n ? kin[i] : 0ull;
-    val[k] = i < n ? vin[i] : 0u;
+    key[k] = i < n ? tile_load<AGENT>(kin + i) : 0ull;
+    val[k] = i < n ? tile_load<AGENT>(vin + i) : 0u;
   }
   // rank of each key among the equal digits of its set (wave ballots), and
   // the count of every digit in every set
@@ -568,8 +586,8 @@ __device__ __forceinline__ void radix_tile(SortLds& L, const uint64_t* __restric
       const uint64_t kk = s_key[q];
       const uint32_t d = (uint32_t)((kk >> shift) & 255ull);
       const uint32_t pos = L.run[d] + (uint32_t)q;
-      kout[pos] = kk;
-      vout[pos] = s_val[q];
+      tile_store<AGENT>(kout + pos, kk);
+      tile_store<AGENT>(vout + pos, s_val[q]);
     }
   }
 }
@@ -595,8 +613,8 @@ __global__ __launch_bounds__(256) void k_radix_pass(const uint64_t* __restrict__
   clear_counts(L);
   if (threadIdx.x == 0) L.tile = (int)atomicAdd(&head->tickets[pass], 1u);
   __syncthreads();
-  radix_tile(L, kin, vin, kout, vout, n, shift, L.tile, status + (int64_t)pass * nblk * 256, gh,
-             err);
+  radix_tile<false>(L, kin, vin, kout, vout, n, shift, L.tile,
+                    status + (int64_t)pass * nblk * 256, gh, err);
 }
 
 // After the passes: every run of keys that agree in the sorted bits is put in
@@ -604,132 +622,478 @@ __global__ __launch_bounds__(256) void k_radix_pass(const uint64_t* __restrict__
 // passes).  A block orders the runs that start in its tile, each of at most
 // kRunMax keys: every key counts the keys of its run that go before it.
 // Other blocks read the keys that a block moves only for their sorted bits,
-// which the moves keep.  Longer runs that are out of order are left to
-// k_resort.  Bound by one read of the keys.
+// which the moves keep.  Longer runs are listed and, if one is out of order,
+// left to k_resort.  TILE: 2048 keys, or 512 where 2048 would leave CUs idle.
+// Bound by one read of the keys: runs are found from one bit
+// per key (followed key by key, runs of clustered particles took 20 to 100 us).
 constexpr int kRunMax = 64;
+constexpr int kRunBlock = 4096;  // keys of a run that one block of k_resort sorts
 
+// Scratch of the long runs (words, less than one per particle): the listed
+// runs' starts; starts, lengths and first items of those longer than
+// kRunBlock; words by which k_resort's blocks wait (one per kReadyLine words);
+// digit counts.
+constexpr int kReady = 64, kReadyLine = 32;
+struct RunWs {
+  uint32_t *runs, *start, *len, *item, *ready, *hist;
+  __host__ __device__ RunWs(uint32_t* w, int n) {
+    const int64_t nr = n / (kRunMax + 1) + 1, no = n / (kRunBlock + 1) + 1;
+    runs = w;
+    start = runs + nr;
+    len = start + no;
+    item = len + no;
+    ready = item + no;
+    hist = ready + kReady * kReadyLine;  // 8 x 256 of each
+  }
+};
+
+template <int TILE>
 __global__ __launch_bounds__(256) void k_sort_fix(uint64_t* __restrict__ keys,
                                                    uint32_t* __restrict__ vals, int n,
-                                                   SortHead* __restrict__ head) {
-  constexpr int H = kRunMax + 1;             // halo on both sides
-  constexpr int W = kSortTile + kRunMax;     // positions looked at: the tile and what
+                                                   RunWs ws, SortHead* __restrict__ head) {
+  constexpr int H = 64;                      // halo on both sides
+  static_assert(kRunMax <= H, "a run of the tile lies within its halos");
+  constexpr int W = TILE + kRunMax;     // positions looked at: the tile and what
                                              // its last run can hold beyond it
   constexpr int PER = (W + 255) / 256;
-  __shared__ uint64_t s_key[kSortTile + 2 * H];
+  constexpr int NK = TILE + 2 * H;
+  __shared__ uint64_t s_key[NK + 64];
+  __shared__ uint64_t s_first[NK / 64 + 1];  // bit t: position t begins a run
+  __shared__ uint32_t s_runs, s_at;
+  __shared__ int s_over;  // start of a run longer than kRunBlock (a tile begins one at most)
   const uint32_t shift = head->shift;
   if (shift == 0u) return;  // sorted by all bits that vary
-  const int base = blockIdx.x * kSortTile;
-  for (int t = threadIdx.x; t < kSortTile + 2 * H; t += 256) {
+  const int tid = threadIdx.x;
+  const int base = blockIdx.x * TILE;
+  if (tid == 0) {
+    s_runs = 0u;
+    s_over = -1;
+  }
+  if (blockIdx.x == 0 && tid < kReady) ws.ready[tid * kReadyLine] = 0u;
+  // position t of the block is particle base - H + t; the first particle and
+  // what lies past the last one begin a run
+  for (int t = tid; t < NK + 64; t += 256) {
     const int j = base - H + t;
-    s_key[t] = j >= 0 && j < n ? keys[j] : 0ull;
+    const bool in = j >= 0 && j < n;
+    const uint64_t kk = in ? keys[j] : 0ull, prev = in && j > 0 ? keys[j - 1] : 0ull;
+    s_key[t] = kk;
+    const uint64_t b = ballot64(j <= 0 || j >= n || (kk >> shift) != (prev >> shift));
+    if ((t & 63) == 0) s_first[t >> 6] = b;
   }
   __syncthreads();
-  // position j is s_key[j - base + H]
-  auto same = [&](int j, uint64_t pre) {  // j holds a key of the run
-    return j >= 0 && j < n && (s_key[j - base + H] >> shift) == pre;
-  };
   int to[PER];
   uint64_t key[PER];
   uint32_t val[PER];
   bool longrun = false;
+  int begins = 0;  // long runs that this thread's keys begin (bit k)
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int i = base + k * 256 + (int)threadIdx.x;
+    const int t = H + k * 256 + tid, i = base - H + t;
     to[k] = -1;
     key[k] = 0ull;
-    val[k] = 0u;
-    if (i >= n || i >= base + W) continue;
-    const uint64_t kk = s_key[i - base + H];
-    const uint64_t pre = kk >> shift;
-    if (!same(i - 1, pre) && !same(i + 1, pre)) continue;  // alone
-    int a = i, e = i + 1;  // the run, as far as kRunMax + 1 keys
-    while (i - a < kRunMax && same(a - 1, pre)) --a;
-    while (e - a <= kRunMax && e < base + kSortTile + H && same(e, pre)) ++e;
-    if (e - a > kRunMax || i - a >= kRunMax) {
-      longrun |= same(i + 1, pre) && i + 1 < base + kSortTile + H && s_key[i + 1 - base + H] < kk;
+    if (t >= H + W) continue;
+    // the words of this wavefront's 64 positions and of their neighbours
+    const uint64_t here = s_first[t >> 6], before = s_first[(t >> 6) - 1],
+                   after = s_first[(t >> 6) + 1];
+    if (ballot64((here & (after << 63 | here >> 1)) != ~0ull) == 0ull) continue;  // all alone
+    if (i >= n) continue;
+    // the run's first position a at or before t, at most 64 back or more, and
+    // its end e after t, at most 64 further or more
+    const int u = t & 63;
+    const uint64_t lo = here & (~0ull >> (63 - u)), hi = u < 63 ? here & (~0ull << (u + 1)) : 0ull;
+    const int a = lo ? t - u + 63 - __clzll((long long)lo)
+                     : before ? t - u - 1 - __clzll((long long)before) : t - kRunMax;
+    const int e = hi ? t - u + __builtin_ctzll(hi)
+                     : after ? t - u + 64 + __builtin_ctzll(after) : t + kRunMax + 1;
+    if (e - a == 1) continue;  // alone
+    const uint64_t kk = s_key[t];
+    if (e - a > kRunMax) {
+      longrun |= e > t + 1 && s_key[t + 1] < kk;
+      if (a == t && t < H + TILE) begins |= 1 << k;
       continue;
     }
-    if (a < base || a >= base + kSortTile) continue;  // another block's
+    if (a < H || a >= H + TILE) continue;  // another block's
     int r = a;
-    for (int j = a; j < e; ++j) {
-      const uint64_t o = s_key[j - base + H];
-      r += (o < kk || (o == kk && j < i)) ? 1 : 0;
+    for (int j = a; j < e; j += 4) {
+      uint64_t o[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = s_key[min(j + q, e - 1)];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        r += j + q < e && (o[q] < kk || (o[q] == kk && j + q < t)) ? 1 : 0;
     }
-    if (r != i) {
-      to[k] = r;
+    if (r != t) {
+      to[k] = base - H + r;
       key[k] = kk;
-      val[k] = vals[i];
     }
   }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    val[k] = 0u;
+    if (to[k] >= 0) val[k] = vals[base + k * 256 + tid];
+  }
   if (longrun) head->resort = 1u;
-  __syncthreads();  // all values read
+  uint32_t at = begins ? atomicAdd(&s_runs, (uint32_t)__popc(begins)) : 0u;
+  __syncthreads();  // all values read, all runs counted
 #pragma unroll
   for (int k = 0; k < PER; ++k)
     if (to[k] >= 0) {
       keys[to[k]] = key[k];
       vals[to[k]] = val[k];
     }
+  if (s_runs == 0u) return;
+  if (tid == 0) s_at = atomicAdd(&head->runs, s_runs);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (begins & (1 << k)) {
+      const int i = base + k * 256 + tid;
+      // (other blocks move keys only within their runs)
+      const bool over = i + kRunBlock < n &&
+                        (keys[i + kRunBlock] >> shift) == (s_key[H + k * 256 + tid] >> shift);
+      ws.runs[s_at + at++] = over ? ~0u : (uint32_t)i;
+      if (over) s_over = i;
+    }
+  __syncthreads();
+  if (s_over < 0) return;
+  // its length, and cleared digit counts
+  const int start = s_over;
+  const uint64_t pre = keys[start] >> shift;
+  int lo = kRunBlock, hi = n - start;  // start + lo is of the run, start + hi is not
+  while (hi - lo > 1) {
+    const int step = (hi - lo + 255) / 256, p = lo + tid * step;
+    const int c = __syncthreads_count(tid > 0 && p < hi && (keys[start + p] >> shift) == pre);
+    lo += c * step;
+    hi = min(lo + step, hi);
+  }
+  if (tid == 0) {
+    s_at = atomicAdd(&head->over, 1u);
+    ws.start[s_at] = (uint32_t)start;
+    ws.len[s_at] = (uint32_t)hi;
+  }
+  __syncthreads();
+  const int words = (int)(shift + 7) / 8 * 256;
+  for (int q = tid; q < words; q += 256) ws.hist[(int64_t)s_at * words + q] = 0u;
 }
 
-// All eight passes in one launch, for keys with a long run out of order;
-// without one it ends at once.  Items are taken in order by a ticket: a stage
-// of digit counts over all tiles, then the passes' tiles.  An item waits for
+// A run of up to kRunBlock keys that agree from bit `shift` (at most 39: three
+// passes or more) on, by one block in LDS.  A key's lower bits and its place in
+// the run make one number, so that no two are equal and any order of additions
+// will do: the keys fall into 4096 buckets by the 12 leading bits that vary,
+// and each counts those of its bucket that go before it.  If a bucket holds
+// more than kRunMax, the digits are sorted one by one, the lowest first.  Bound
+// by latency: k_resort on eight runs of 3750 keys takes 25 us (35 by digits).
+constexpr int kRunBits = 12;
+static_assert(kRunBlock == 1 << kRunBits, "a key's place in its run");
+
+struct RunLds {
+  uint64_t key[kRunBlock];
+  uint32_t cnt[kRunBlock];
+  uint32_t lst[256];
+  uint32_t lds4[4];
+  uint64_t wr[4][2];
+};
+
+__device__ __forceinline__ void sort_run(RunLds& L, uint64_t* __restrict__ keys,
+                                         uint32_t* __restrict__ vals, int n, uint32_t shift,
+                                         int start) {
+  constexpr int PER = kRunBlock / 256;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const uint64_t pre = keys[start] >> shift;
+  // the run's length: its keys are consecutive
+  auto same = [&](int p) { return start + p < n && (keys[start + p] >> shift) == pre; };
+  const int c16 = __syncthreads_count(same(PER * tid)) - 1;
+  const int len = PER * c16 + __syncthreads_count(tid < PER && same(PER * c16 + tid));
+  const int per = (len + 255) >> 8;
+  // a wavefront holds consecutive keys, a lane every 64th of them
+  const int p0 = w * per * 64 + lane;
+  auto holds = [&](int k) { return k < per && p0 + 64 * k < len; };
+  uint64_t key[PER];
+  uint32_t at[PER];
+  uint64_t ones = 0ull, zeros = 0ull;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) key[k] = holds(k) ? keys[start + p0 + 64 * k] : 0ull;
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (holds(k)) {
+      const uint64_t low = key[k] & ((1ull << shift) - 1ull);
+      ones |= low;
+      zeros |= ~low;
+      key[k] = low << kRunBits | (uint64_t)(p0 + 64 * k);
+      L.key[p0 + 64 * k] = key[k];
+    }
+  ones = wave_or_u64(ones);
+  zeros = wave_or_u64(zeros);
+  if (lane == 0) {
+    L.wr[w][0] = ones;
+    L.wr[w][1] = zeros;
+  }
+  for (int q = tid; q < kRunBlock; q += 256) L.cnt[q] = 0u;
+  __syncthreads();
+  bool out = false;
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    out |= holds(k) && p0 + 64 * k + 1 < len && key[k] > L.key[p0 + 64 * k + 1];
+  const uint64_t varying = (L.wr[0][0] | L.wr[1][0] | L.wr[2][0] | L.wr[3][0]) &
+                           (L.wr[0][1] | L.wr[1][1] | L.wr[2][1] | L.wr[3][1]);
+  if (!__syncthreads_or(out)) return;
+  const int top = kRunBits + 64 - __clzll((long long)varying);
+  const int bit0 = max(kRunBits, top - kRunBits);
+  auto bucket = [&](uint64_t v) { return (uint32_t)(v >> bit0) & (uint32_t)(kRunBlock - 1); };
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    at[k] = 0u;
+    if (holds(k)) at[k] = atomicAdd(&L.cnt[bucket(key[k])], 1u);
+  }
+  __syncthreads();
+  // first places of the buckets (16 a thread)
+  uint32_t mine = 0u, all;
+  bool large = false;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const uint32_t c = L.cnt[PER * tid + q];
+    L.cnt[PER * tid + q] = mine;
+    mine += c;
+    large |= c > (uint32_t)kRunMax;
+  }
+  const uint32_t before = block256_excl_scan(mine, L.lds4, &all);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) L.cnt[PER * tid + q] += before;
+  if (!__syncthreads_or(large)) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (holds(k)) L.key[L.cnt[bucket(key[k])] + at[k]] = key[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      if (!holds(k)) continue;
+      const uint32_t d = bucket(key[k]);
+      const int a = (int)L.cnt[d], e = d + 1 < kRunBlock ? (int)L.cnt[d + 1] : len;
+      int r = a;
+      for (int j = a; j < e; ++j) r += L.key[j] < key[k] ? 1 : 0;
+      at[k] = (uint32_t)r;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (holds(k)) L.key[at[k]] = key[k];
+    __syncthreads();
+  } else {
+    uint32_t* cnt = L.cnt + 256 * w;  // this wavefront's digit counts
+    for (int bit = kRunBits + __builtin_ctzll(varying); bit < top; bit += 8) {
+      __syncthreads();
+      for (int q = lane; q < 256; q += 64) cnt[q] = 0u;
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        at[k] = 0u;
+        if (k >= per) continue;
+        const uint32_t d = (uint32_t)(key[k] >> bit) & 255u;
+        const uint64_t m = match_digit8(d, ballot64(holds(k)));
+        const uint32_t r = (uint32_t)popc64(m & lanemask_lt()), c = cnt[d];
+        at[k] = c + r;
+        if (holds(k) && r == 0u) cnt[d] = c + (uint32_t)popc64(m);
+      }
+      __syncthreads();
+      mine = 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t c = L.cnt[256 * q + tid];
+        L.cnt[256 * q + tid] = mine;
+        mine += c;
+      }
+      L.lst[tid] = block256_excl_scan(mine, L.lds4, &all);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < PER; ++k)
+        if (holds(k)) {
+          const uint32_t d = (uint32_t)(key[k] >> bit) & 255u;
+          L.key[L.lst[d] + cnt[d] + at[k]] = key[k];
+        }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < PER; ++k)
+        if (holds(k)) key[k] = L.key[p0 + 64 * k];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    key[k] = holds(k) ? L.key[p0 + 64 * k] : 0ull;
+    at[k] = holds(k) ? vals[start + (int)(key[k] & (kRunBlock - 1))] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) loaded(at[k]);
+  __syncthreads();  // all values read
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (holds(k)) {
+      keys[start + p0 + 64 * k] = pre << shift | key[k] >> kRunBits;
+      vals[start + p0 + 64 * k] = at[k];
+    }
+}
+
+// For keys with a long run out of order; without one it ends at once.  Runs of
+// up to kRunBlock keys are sorted by a block each.  Longer ones are sorted by
+// the bits below the passes', each as an array of its own: a stage of digit
+// counts (1) and the passes (2 on).  Items (tiles of the runs: at most 3/2 of
+// the array's tiles, for at most five passes, so that their status words fit
+// the array's of eight) are taken in order by a ticket, and an item waits for
 // the stage before its own to end: those items belong to blocks that already
-// run, so the wait ends however many blocks are resident.  Equal keys are in
-// the order of the particles already and stay so.
-__global__ __launch_bounds__(256) void k_resort(uint64_t* k0, uint32_t* v0, uint64_t* k1,
-                                                 uint32_t* v1, int n, int nblk,
-                                                 uint32_t* __restrict__ status, uint32_t* ghist,
+// run, so the wait ends however many blocks are resident.
+// Sort (all its launches) in random order: 30,000 particles of a Plummer sphere
+// of 1/100 of the box 62 us, 10^6 189 (eight passes over everything: 80 and 236;
+// uniform: 44 and 146); a body of 1/1000 of the box, its runs longer than
+// kRunBlock from 33,000 particles on: 10^5 119 us, 10^6 266, 4 10^6 626 (91, 237,
+// 546).
+//
+// Between stages data passes from one XCD's L2 to another's.  All of it is
+// stored and loaded past them (tile_store, tile_load): a release and an acquire
+// fence for every tile, each of which goes over an L2, took 60 us of a pass over
+// 10^6 particles that takes 25 in launches of its own.
+// The last item of a stage tells the blocks that wait, by words of their own:
+// polls of the counter itself hold up the additions to it (75 us a stage).
+__device__ __forceinline__ void stage_end(SortHead* head, const RunWs& ws, int stage, int items) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's stores are done
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    uint32_t before = 0u;
+    if (threadIdx.x == 0)
+      before = __hip_atomic_fetch_add(&head->done[stage], 1u, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane((int)before) == items - 1)
+      tile_store<true>(ws.ready + (int)threadIdx.x * kReadyLine, (uint32_t)stage + 1u);
+  }
+}
+static_assert(kReady == kWave, "one lane per word");
+
+// All stages before `stage` have ended.
+__device__ __forceinline__ void stage_wait(const RunWs& ws, int stage,
+                                           uint32_t* __restrict__ err) {
+  const uint32_t* p = ws.ready + (int)(blockIdx.x % kReady) * kReadyLine;
+  int spins = 0;
+  while ((int)tile_load<true>(p) < stage) {
+    __builtin_amdgcn_s_sleep(4);
+    if (++spins > kLookbackSpin) {
+      atomicOr(err, kErrSort);
+      break;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void k_resort(uint64_t* k0, uint32_t* v0, uint64_t* k1,
+                                                 uint32_t* v1, int n, uint32_t* status, RunWs ws,
                                                  SortHead* head, uint32_t* __restrict__ err) {
   if (head->resort == 0u) return;
-  __shared__ SortLds L;
+  __shared__ union {
+    SortLds sort;
+    RunLds run;
+  } U;
   const int tid = threadIdx.x;
+  const uint32_t shift = head->shift;
+  const int nr = (int)head->runs;
+  for (int r = blockIdx.x; r < nr; r += gridDim.x) {
+    const uint32_t i = ws.runs[r];
+    if (i == ~0u) continue;  // a longer one
+    sort_run(U.run, k0, v0, n, shift, (int)i);
+    __syncthreads();  // the LDS of the next
+  }
+  const int no = (int)head->over;
+  if (no == 0) return;
+  SortLds& L = U.sort;
+  const int npass = (int)(shift + 7) / 8;
+  const bool odd = npass & 1;  // the runs then begin in the second buffer
+  // first item of every run: by each block for up to 256 of them, otherwise by
+  // one for all (stage 0, ticket 0)
+  __shared__ uint32_t s_item[256];
+  const bool few = no <= 256;
+  int items = 0;  // of every stage but 0 (0: not known yet)
+  if (few) {
+    uint32_t all;
+    const uint32_t tiles = tid < no ? (ws.len[tid] + kSortTile - 1) / kSortTile : 0u;
+    s_item[tid] = block256_excl_scan(tiles, L.lds4, &all);
+    items = (int)all;
+  }
+  const int t0 = few ? 0 : 1;  // ticket of the first item
   for (;;) {
     __syncthreads();  // the LDS of the item before
     if (tid == 0) {
       const int t = (int)atomicAdd(&head->ticket, 1u);
-      const int stage = t / nblk;
-      if (stage >= 1 && stage <= 8) {
-        int spins = 0;
-        while (__hip_atomic_load(&head->done[stage - 1], __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)nblk) {
-          __builtin_amdgcn_s_sleep(8);
-          if (++spins > kLookbackSpin) {
-            atomicOr(err, kErrSort);
-            break;
-          }
+      L.tile = t;
+      if (t >= t0) {
+        if (items == 0) {
+          stage_wait(ws, 1, err);
+          items = (int)tile_load<true>(&head->items);
+        }
+        const int stage = 1 + (t - t0) / items;
+        if (stage > 1 && stage <= npass + 1) stage_wait(ws, stage, err);
+      }
+    }
+    __syncthreads();
+    const int t = L.tile;
+    if (t < t0) {
+      uint32_t before = 0u;
+      for (int r0 = 0; r0 < no; r0 += 256) {
+        const int r = r0 + tid;
+        uint32_t all;
+        const uint32_t o = block256_excl_scan(
+            r < no ? (ws.len[r] + kSortTile - 1) / kSortTile : 0u, L.lds4, &all);
+        if (r < no) tile_store<true>(ws.item + r, before + o);
+        before += all;
+      }
+      if (tid == 0) tile_store<true>(&head->items, before);
+      stage_end(head, ws, 0, 1);
+      continue;
+    }
+    if (items == 0) items = (int)tile_load<true>(&head->items);
+    const int stage = 1 + (t - t0) / items, item = (t - t0) % items;
+    if (stage > npass + 1) return;
+    // the run of the item: the last with no later first item
+    int r = 0, first = 0;
+    if (few) {
+      r = __syncthreads_count(tid < no && (int)s_item[tid] <= item) - 1;
+      first = (int)s_item[r];
+    } else {
+      for (int size = no; size > 1;) {
+        const int step = (size + 255) / 256;
+        const int c = __syncthreads_count(tid * step < size &&
+                                          (int)tile_load<true>(ws.item + r + tid * step) <= item);
+        r += (c - 1) * step;
+        size = min(step, size - (c - 1) * step);
+      }
+      first = (int)tile_load<true>(ws.item + r);
+    }
+    const int start = (int)ws.start[r], len = (int)ws.len[r], tile = item - first;
+    uint32_t* hist = ws.hist + (int64_t)r * npass * 256;
+    if (stage == 1) {
+      uint32_t(*h)[256] = reinterpret_cast<uint32_t(*)[256]>(L.buf);
+      for (int p = 0; p < npass; ++p) {
+        h[p][tid] = 0u;
+        tile_store<true>(status + ((int64_t)p * items + item) * 256 + tid, 0u);
+      }
+      __syncthreads();
+      count_digits(k0 + start, len, tile * kSortTile, 0u, npass, h);
+      if (odd) {
+        for (int i = tile * kSortTile + tid; i < min((tile + 1) * kSortTile, len); i += 256) {
+          tile_store<true>(k1 + start + i, k0[start + i]);
+          tile_store<true>(v1 + start + i, v0[start + i]);
         }
       }
-      L.tile = t;
-    }
-    __syncthreads();
-    __threadfence();  // what the stage before wrote
-    const int t = L.tile, stage = t / nblk, tile = t - stage * nblk;
-    if (stage > 8) return;
-    if (stage == 0) {
-      uint32_t(*h)[256] = reinterpret_cast<uint32_t(*)[256]>(L.buf);
-      for (int p = 0; p < 8; ++p) {
-        h[p][tid] = 0u;
-        status[((int64_t)p * nblk + tile) * 256 + tid] = 0u;
-      }
       __syncthreads();
-      count_digits(k0, n, tile * kSortTile, 0u, 8, h);
-      __syncthreads();
-      for (int p = 0; p < 8; ++p)
-        if (h[p][tid]) atomicAdd(&ghist[p * 256 + tid], h[p][tid]);
+      for (int p = 0; p < npass; ++p)
+        if (h[p][tid]) atomicAdd(&hist[p * 256 + tid], h[p][tid]);
     } else {
-      const int pass = stage - 1;
-      const uint32_t gh = __hip_atomic_load(&ghist[pass * 256 + tid], __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
+      const int pass = stage - 2;
+      const uint32_t gh = tile_load<true>(&hist[pass * 256 + tid]);
       clear_counts(L);
       __syncthreads();
-      const bool even = (pass & 1) == 0;
-      radix_tile(L, even ? k0 : k1, even ? v0 : v1, even ? k1 : k0, even ? v1 : v0, n,
-                 8u * (uint32_t)pass, tile, status + (int64_t)pass * nblk * 256, gh, err);
+      const bool second = odd == ((pass & 1) == 0);
+      radix_tile<true>(L, (second ? k1 : k0) + start, (second ? v1 : v0) + start,
+                 (second ? k0 : k1) + start, (second ? v0 : v1) + start, len,
+                 8u * (uint32_t)pass, tile, status + ((int64_t)pass * items + first) * 256, gh,
+                 err);
     }
-    __threadfence();  // every thread's writes, before the stage counts this item
-    __syncthreads();
-    if (tid == 0) atomicAdd(&head->done[stage], 1u);
+    stage_end(head, ws, stage, items);
   }
 }
 
@@ -4410,8 +4774,8 @@ static int stream_blocks(int n) {
 }
 
 // The radix sort's workspace: look-back status words of every pass and tile,
-// then the eight digit histograms of the passes and of k_resort, then the
-// head, then the key bits of every block of k_predict_keys.
+// then the digit histograms of the passes, then the head, then the key bits of
+// every block of k_predict_keys.
 struct SortWs {
   uint32_t *status, *ghist;
   SortHead* head;
@@ -4423,8 +4787,8 @@ static SortWs sort_ws(sph_ctx* c) {
   SortWs w;
   w.status = c->radix_cnt;
   w.ghist = c->radix_cnt + nst;
-  w.head = reinterpret_cast<SortHead*>(w.ghist + 2 * 8 * 256);
-  w.range = reinterpret_cast<uint64_t*>(w.ghist + 2 * 8 * 256 + kSortHeadWords);
+  w.head = reinterpret_cast<SortHead*>(w.ghist + 8 * 256);
+  w.range = reinterpret_cast<uint64_t*>(w.ghist + 8 * 256 + kSortHeadWords);
   return w;
 }
 
@@ -4485,10 +4849,18 @@ hipError_t launch_sort(sph_ctx* c) {
                        c->vals[src], c->keys[dst], c->vals[dst], n, pass, nblk, w.status, w.ghist,
                        w.head, &c->ds->err);
   }
-  hipLaunchKernelGGL(k_sort_fix, dim3(nblk), dim3(256), 0, c->stream, c->keys[0], c->vals[0], n,
-                     w.head);
-  launch_last(c, k_resort, dim3(std::min(nblk, 2 * c->n_cu)), dim3(256), c->keys[0], c->vals[0],
-              c->keys[1], c->vals[1], n, nblk, w.status, w.ghist + 8 * 256, w.head, &c->ds->err);
+  // the permute's staging space is free during the sort
+  const RunWs ws(reinterpret_cast<uint32_t*>(c->gtmp), n);
+  if (nblk < c->n_cu)
+    hipLaunchKernelGGL(k_sort_fix<512>, dim3((n + 511) / 512), dim3(256), 0, c->stream, c->keys[0],
+                       c->vals[0], n, ws, w.head);
+  else
+    hipLaunchKernelGGL(k_sort_fix<kSortTile>, dim3(nblk), dim3(256), 0, c->stream, c->keys[0],
+                       c->vals[0], n, ws, w.head);
+  // enough blocks for many runs at once, few enough to end quickly without one
+  const int blocks = n > (1 << 17) ? 3 * c->n_cu : std::max(nblk + nblk / 2, c->n_cu / 2);
+  launch_last(c, k_resort, dim3(std::min(blocks, 3 * c->n_cu)), dim3(256), c->keys[0], c->vals[0],
+              c->keys[1], c->vals[1], n, w.status, ws, w.head, &c->ds->err);
   return hipGetLastError();
 }
 
