@@ -22,7 +22,6 @@ hipError_t launch_leaf_state(sph_ctx* c, int v);
 namespace {
 
 constexpr int kRing = 1024;        // timed launches kept per phase
-constexpr int kPool = 15 * kRing;  // phase boundaries kept, over all phases
 enum Phase {
   kPhSort = 0,
   kPhPermute,
@@ -36,16 +35,26 @@ enum Phase {
   kPhForceFb,
   kPhAdjoint,
   kPhAdjForce,
-  kNPh
+  kNPh,
+  kPhNone = kNPh
 };
 
 }  // namespace
 
 // Events of the phase boundaries, owned by the context.  A boundary's event is
 // stamped by the last kernel before it (launch_last); a phase is the pair of
-// boundaries around it, so consecutive phases share one.
+// boundaries around it, so consecutive phases share one.  A boundary is taken
+// only if a phase that still keeps launches begins or ends there: two for each
+// kept launch are enough, whatever calls fill the phases and in which order.
+// As many as steps alone take are created with the context, the rest when used.
+// They only time: no system-scope fence (the cache write-back and invalidation
+// would idle the GPU for microseconds at every phase boundary); sph_timings
+// reads them after a stream synchronise.
+constexpr int kPool = 2 * kNPh * kRing, kPoolAtCreate = 15 * kRing;
+constexpr unsigned kEventFlags = hipEventDisableSystemFence;
 struct sph_timing {
   hipEvent_t ev[kPool];
+  int made = 0;            // events created
   int used = 0;            // events taken since sph_timings
   int last = -1;           // the latest boundary of the running call (-1: none)
   int span[kNPh][kRing][2];  // first and last boundary of each timed launch
@@ -94,38 +103,53 @@ void timing_begin(sph_ctx* c) {
     c->timing = false;
   }
 }
+// Whether phase `ph` keeps another launch.
+bool ph_open(const sph_ctx* c, int ph) {
+  return c->timing && ph != kPhNone && c->tm->count[ph] < kRing;
+}
 // The next event of the pool as the latest boundary; -1 if there is none.
 int next_boundary(sph_ctx* c) {
   sph_timing* x = c->tm;
-  if (!c->timing || x->used >= kPool) return x ? (x->last = -1) : -1;
+  x->last = -1;
+  if (x->used >= kPool) return -1;
+  if (x->used == x->made) {
+    if (hipEventCreateWithFlags(&x->ev[x->made], kEventFlags) != hipSuccess) {
+      (void)hipGetLastError();
+      return -1;
+    }
+    ++x->made;
+  }
   return x->last = x->used++;
 }
-// The last kernel of the next launcher call stamps a boundary.
-void ph_mark(sph_ctx* c) {
+// The last kernel of the next launcher call stamps a boundary, if phase `ends`
+// that ends there or phase `begins` that begins there keeps its launch.
+void ph_mark(sph_ctx* c, int ends, int begins) {
+  c->mark = nullptr;
+  if (!ph_open(c, ends) && !ph_open(c, begins)) return;
   const int k = next_boundary(c);
-  c->mark = k >= 0 ? c->tm->ev[k] : nullptr;
+  if (k >= 0) c->mark = c->tm->ev[k];
 }
 // A boundary of its own on the stream, where no kernel precedes the phase.
-void ph_record(sph_ctx* c) {
+void ph_record(sph_ctx* c, int begins) {
+  if (!ph_open(c, begins)) return;
   const int k = next_boundary(c);
   if (k >= 0) (void)hipEventRecord(c->tm->ev[k], c->stream);
 }
+int ph_last(const sph_ctx* c) { return c->timing ? c->tm->last : -1; }
 // Phase `ph` runs from boundary `from` to the latest one.
 void ph_span(sph_ctx* c, int ph, int from) {
-  sph_timing* x = c->tm;
-  if (!c->timing || from < 0 || x->last < 0 || x->count[ph] >= kRing) return;
-  int* sp = x->span[ph][x->count[ph]++];
+  if (!ph_open(c, ph) || from < 0 || c->tm->last < 0) return;
+  int* sp = c->tm->span[ph][c->tm->count[ph]++];
   sp[0] = from;
-  sp[1] = x->last;
+  sp[1] = c->tm->last;
 }
-int ph_last(const sph_ctx* c) { return c->timing ? c->tm->last : -1; }
 
 // Runs one launcher as phase `ph`, from the latest boundary to one that its
-// last kernel stamps.
+// last kernel stamps; phase `next` follows.
 template <typename Fn>
-hipError_t ph_run(sph_ctx* c, int ph, Fn fn) {
+hipError_t ph_run(sph_ctx* c, int ph, int next, Fn fn) {
   const int from = ph_last(c);
-  ph_mark(c);
+  ph_mark(c, ph, next);
   const hipError_t e = fn();
   ph_span(c, ph, from);
   return e;
@@ -378,12 +402,9 @@ sph_status sph_create(const sph_params* prm, int64_t n_max, void* stream, sph_ct
   }
   c->tm = x;
   bool ok = true;
-  // timing-only events: no system-scope fence (the cache write-back and
-  // invalidation would idle the GPU for microseconds at every phase boundary);
-  // sph_timings reads them after a stream synchronise
   for (int ph = 0; ph < kNPh; ++ph) x->count[ph] = 0;
-  for (int k = 0; k < kPool && ok; ++k)
-    ok = hipEventCreateWithFlags(&x->ev[k], hipEventDisableSystemFence) == hipSuccess;
+  for (; x->made < kPoolAtCreate && ok; ++x->made)
+    ok = hipEventCreateWithFlags(&x->ev[x->made], kEventFlags) == hipSuccess;
   x->ready = ok;
   g_create_err.clear();
   *out = c;
@@ -417,17 +438,20 @@ void sph_destroy(sph_ctx* c) {
   delete c;
 }
 
+static int density_phase(const sph_ctx* c) { return sph::lists_mode(c) ? kPhLists : kPhDensity; }
+
 // After a launch that stamped a phase boundary (counters cleared).
 static sph_status do_build(sph_ctx* c, sph_particles* p, bool outputs_too, bool predict) {
   c->n = (int32_t)p->n;
   c->kp.n = c->n;
   c->densities_on_tree = 0;
-  HIPCHK(c, ph_run(c, kPhSort, [&] {
+  HIPCHK(c, ph_run(c, kPhSort, kPhPermute, [&] {
     const hipError_t e = sph::launch_predict_keys(c, p, predict, 0.0);
     return e == hipSuccess ? sph::launch_sort(c) : e;
   }));
-  HIPCHK(c, ph_run(c, kPhPermute, [&] { return sph::launch_permute(c, p, outputs_too); }));
-  HIPCHK(c, ph_run(c, kPhTree, [&] {
+  HIPCHK(c, ph_run(c, kPhPermute, kPhTree,
+                   [&] { return sph::launch_permute(c, p, outputs_too); }));
+  HIPCHK(c, ph_run(c, kPhTree, predict ? density_phase(c) : kPhNone, [&] {
     const hipError_t e = sph::launch_tree(c);
     return e == hipSuccess ? sph::launch_node_boxes(c, p) : e;
   }));
@@ -439,7 +463,7 @@ sph_status sph_build_tree(sph_ctx* c, sph_particles* p) {
   sph_status st = check_parts(c, p, false, false);
   if (st != SPH_OK) return st;
   TimingScope scope(c, c->timing_every > 0);
-  ph_mark(c);
+  ph_mark(c, kPhNone, kPhSort);
   HIPCHK(c, sph::launch_reset_counters(c));
   return do_build(c, p, true, false);
 }
@@ -448,12 +472,13 @@ sph_status sph_build_tree(sph_ctx* c, sph_particles* p) {
 // walking kernel for flagged groups; or the walking kernel for all groups.
 static sph_status run_density(sph_ctx* c, sph_particles* p) {
   if (sph::lists_mode(c)) {
-    HIPCHK(c, ph_run(c, kPhLists, [&] { return sph::launch_lists(c, p); }));
+    HIPCHK(c, ph_run(c, kPhLists, kPhDensity, [&] { return sph::launch_lists(c, p); }));
     ++c->lists_launches;
-    HIPCHK(c, ph_run(c, kPhDensity, [&] { return sph::launch_density_lists(c, p); }));
-    HIPCHK(c, ph_run(c, kPhDensityFb, [&] { return sph::launch_density(c, p, true); }));
+    HIPCHK(c, ph_run(c, kPhDensity, kPhDensityFb,
+                     [&] { return sph::launch_density_lists(c, p); }));
+    HIPCHK(c, ph_run(c, kPhDensityFb, kPhNone, [&] { return sph::launch_density(c, p, true); }));
   } else {
-    HIPCHK(c, ph_run(c, kPhDensity, [&] { return sph::launch_density(c, p, false); }));
+    HIPCHK(c, ph_run(c, kPhDensity, kPhNone, [&] { return sph::launch_density(c, p, false); }));
   }
   ++c->density_launches;
   ++c->densities_on_tree;
@@ -461,13 +486,16 @@ static sph_status run_density(sph_ctx* c, sph_particles* p) {
 }
 
 // Force: from the lists while they hold every pair, the walking kernel for
-// the rest (or for all groups).
-static sph_status run_force(sph_ctx* c, sph_particles* p, bool step_mode) {
+// the rest (or for all groups); phase `next` follows.
+static sph_status run_force(sph_ctx* c, sph_particles* p, bool step_mode, int next) {
   if (sph::lists_mode(c)) {
-    HIPCHK(c, ph_run(c, kPhForce, [&] { return sph::launch_force_lists(c, p, step_mode); }));
-    HIPCHK(c, ph_run(c, kPhForceFb, [&] { return sph::launch_force(c, p, step_mode, true); }));
+    HIPCHK(c, ph_run(c, kPhForce, kPhForceFb,
+                     [&] { return sph::launch_force_lists(c, p, step_mode); }));
+    HIPCHK(c, ph_run(c, kPhForceFb, next,
+                     [&] { return sph::launch_force(c, p, step_mode, true); }));
   } else {
-    HIPCHK(c, ph_run(c, kPhForce, [&] { return sph::launch_force(c, p, step_mode, false); }));
+    HIPCHK(c, ph_run(c, kPhForce, next,
+                     [&] { return sph::launch_force(c, p, step_mode, false); }));
   }
   ++c->force_launches;
   return SPH_OK;
@@ -488,7 +516,7 @@ sph_status sph_density(sph_ctx* c, sph_particles* p, int32_t* iters_out) {
   // tree starts from the h the last one converged to), or the list walk
   // could leave out a neighbour whose h grew past its node's h_max
   HIPCHK(c, sph::launch_node_h(c, p, true));
-  ph_mark(c);
+  ph_mark(c, kPhNone, density_phase(c));
   HIPCHK(c, sph::launch_leaf_state(c, 1));
   st = run_density(c, p);
   if (st != SPH_OK) return st;
@@ -511,9 +539,9 @@ sph_status sph_force(sph_ctx* c, sph_particles* p, double* dt_next_out) {
   if (p->n != c->n) return fail(c, SPH_E_ARG, "n differs from the last sph_build_tree");
   TimingScope scope(c, c->timing_every > 0);
   HIPCHK(c, sph::launch_node_h(c, p, false));
-  ph_mark(c);
+  ph_mark(c, kPhNone, kPhForce);
   HIPCHK(c, sph::launch_force_reset(c));
-  st = run_force(c, p, false);
+  st = run_force(c, p, false, kPhNone);
   if (st != SPH_OK) return st;
   if (dt_next_out) {
     st = sync_state(c, true);
@@ -523,18 +551,19 @@ sph_status sph_force(sph_ctx* c, sph_particles* p, double* dt_next_out) {
   return SPH_OK;
 }
 
-// A step up to the corrector; `begin` is the phase boundary it starts from.
-static sph_status step_to_force(sph_ctx* c, sph_particles* p, double dt, int& begin) {
-  ph_mark(c);
+// A step up to the corrector; `begin` is the phase boundary it starts from, and
+// phase `next` follows.
+static sph_status step_to_force(sph_ctx* c, sph_particles* p, double dt, int& begin, int next) {
+  ph_mark(c, kPhStep, kPhSort);
   begin = ph_last(c);
   HIPCHK(c, sph::launch_step_begin(c, dt));
   sph_status st = do_build(c, p, false, true);
   if (st != SPH_OK) return st;
   st = run_density(c, p);
   if (st != SPH_OK) return st;
-  ph_mark(c);
+  ph_mark(c, kPhNone, kPhForce);
   HIPCHK(c, sph::launch_node_h(c, p, false));
-  return run_force(c, p, true);
+  return run_force(c, p, true, next);
 }
 
 sph_status sph_step(sph_ctx* c, sph_particles* p, double dt, double* dt_next_out) {
@@ -545,9 +574,9 @@ sph_status sph_step(sph_ctx* c, sph_particles* p, double dt, double* dt_next_out
   // phase events on one call in timing_every; other entry points always record
   TimingScope scope(c, c->timing_every > 0 && (c->step_calls++ % c->timing_every) == 0);
   int begin = -1;
-  st = step_to_force(c, p, dt, begin);
+  st = step_to_force(c, p, dt, begin, kPhIntegrate);
   if (st != SPH_OK) return st;
-  HIPCHK(c, ph_run(c, kPhIntegrate, [&] { return sph::launch_correct(c, p); }));
+  HIPCHK(c, ph_run(c, kPhIntegrate, kPhStep, [&] { return sph::launch_correct(c, p); }));
   ph_span(c, kPhStep, begin);
   if (dt_next_out) {
     st = sync_state(c, true);
@@ -593,12 +622,13 @@ static sph_status adj_check(sph_ctx* c, const sph_particles* p, const sph_cotang
 // h and must be complete.
 static sph_status adj_launch(sph_ctx* c, const sph_particles* p, sph_cotangents* g, double dt,
                              bool step_mode) {
-  ph_record(c);
+  ph_record(c, kPhAdjoint);
   const int from = ph_last(c);
-  ph_mark(c);
+  ph_mark(c, kPhNone, kPhAdjForce);
   HIPCHK(c, sph::launch_adjoint(c, p, g, dt, step_mode, 0));
-  HIPCHK(c, ph_run(c, kPhAdjForce, [&] { return sph::launch_adjoint(c, p, g, dt, step_mode, 1); }));
-  ph_mark(c);
+  HIPCHK(c, ph_run(c, kPhAdjForce, kPhNone,
+                   [&] { return sph::launch_adjoint(c, p, g, dt, step_mode, 1); }));
+  ph_mark(c, kPhAdjoint, step_mode ? kPhIntegrate : kPhNone);
   HIPCHK(c, sph::launch_adjoint(c, p, g, dt, step_mode, 2));
   ph_span(c, kPhAdjoint, from);
   return SPH_OK;
@@ -640,7 +670,7 @@ sph_status sph_step_adjoint(sph_ctx* c, sph_particles* p, double dt, sph_cotange
   // the forward step up to the corrector (as sph_step)
   TimingScope scope(c, c->timing_every > 0);
   int begin = -1;
-  st = step_to_force(c, p, dt, begin);
+  st = step_to_force(c, p, dt, begin, kPhStep);
   if (st != SPH_OK) return st;
   ph_span(c, kPhStep, begin);
   // reverse sweep at the predicted state (x1, v_p, u_p, new a in scratch)
@@ -648,7 +678,7 @@ sph_status sph_step_adjoint(sph_ctx* c, sph_particles* p, double dt, sph_cotange
   if (st != SPH_OK) return st;
   st = adj_launch(c, p, g, dt, true);
   if (st != SPH_OK) return st;
-  HIPCHK(c, ph_run(c, kPhIntegrate, [&] { return sph::launch_correct(c, p); }));
+  HIPCHK(c, ph_run(c, kPhIntegrate, kPhNone, [&] { return sph::launch_correct(c, p); }));
   return SPH_OK;
 }
 
