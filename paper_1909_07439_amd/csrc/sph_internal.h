@@ -238,7 +238,9 @@ __device__ __forceinline__ int wave_max_i32(int v) {
 // load one record's bytes together, straight into LDS (64 bytes per access),
 // and each lane then reads its record from there.  The pieces of a record sit
 // permuted (slot = piece ^ key) so that the reads of 8 consecutive lanes fall
-// in distinct banks.
+// in distinct banks of 32; over the 64 banks two of 16 lanes still meet, and the
+// conflict counter shows it (3.7e8 per launch at 16.8M particles, 0 without LDS;
+// the wait for LDS rose from 1.2e7 to 1.4e8).
 typedef int Piece __attribute__((ext_vector_type(4)));
 
 template <int RB>

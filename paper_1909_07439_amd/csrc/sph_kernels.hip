@@ -44,12 +44,6 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
   return v;
 }
 
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-  return v;
-}
-
 __device__ __forceinline__ double wave_max_f64(double v) { return seg_max<kWave>(v); }
 __device__ __forceinline__ double wave_min_f64(double v) { return seg_min<kWave>(v); }
 
@@ -88,8 +82,7 @@ __global__ __launch_bounds__(256) void k_scan_partials(const uint32_t* __restric
 
 // One block of 1024 threads scans nb partials in chunks; writes the total.
 __global__ __launch_bounds__(1024) void k_scan_top(uint32_t* __restrict__ part, int nb,
-                                                    uint32_t* __restrict__ total_out,
-                                                    int32_t* __restrict__ total_i32) {
+                                                    uint32_t* __restrict__ total_out) {
   __shared__ uint32_t lds[16];
   __shared__ uint32_t carry;
   if (threadIdx.x == 0) carry = 0;
@@ -113,10 +106,7 @@ __global__ __launch_bounds__(1024) void k_scan_top(uint32_t* __restrict__ part, 
     if (threadIdx.x == 0) carry = c0 + tot;
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    if (total_out) *total_out = carry;
-    if (total_i32) *total_i32 = (int32_t)carry;
-  }
+  if (threadIdx.x == 0) *total_out = carry;
 }
 
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* in, uint32_t* out, int64_t n,
@@ -145,8 +135,7 @@ __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* in, uint32_t
 constexpr int kScanSingleMax = 1024 * 64;
 
 __global__ __launch_bounds__(1024) void k_scan_single(uint32_t* __restrict__ data, int n,
-                                                       uint32_t* __restrict__ total_out,
-                                                       int32_t* __restrict__ total_i32) {
+                                                       uint32_t* __restrict__ total_out) {
   __shared__ uint32_t lds[16];
   const int t = threadIdx.x;
   const int q = (n + 4095) / 4096;  // uint4 per thread, <= 16
@@ -188,24 +177,18 @@ __global__ __launch_bounds__(1024) void k_scan_single(uint32_t* __restrict__ dat
       d4[idx] = o;
     }
   }
-  if (t == 0) {
-    if (total_out) *total_out = tot;
-    if (total_i32) *total_i32 = (int32_t)tot;
-  }
+  if (t == 0) *total_out = tot;
 }
 
-static hipError_t scan_u32(sph_ctx* c, uint32_t* data, int64_t n, uint32_t* total,
-                           int32_t* total_i32) {
+static hipError_t scan_u32(sph_ctx* c, uint32_t* data, int64_t n, uint32_t* total) {
   if (n > 0 && n <= kScanSingleMax && (n & 3) == 0 && (reinterpret_cast<uintptr_t>(data) & 15) == 0) {
-    hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(1024), 0, c->stream, data, (int)n, total,
-                       total_i32);
+    hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(1024), 0, c->stream, data, (int)n, total);
     return hipGetLastError();
   }
   const int nb = (int)((n + kScanTile - 1) / kScanTile);
   if (nb == 0) return hipSuccess;
   hipLaunchKernelGGL(k_scan_partials, dim3(nb), dim3(256), 0, c->stream, data, n, c->scan_part);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, c->stream, c->scan_part, nb, total,
-                     total_i32);
+  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, c->stream, c->scan_part, nb, total);
   hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(256), 0, c->stream, data, data, n,
                      c->scan_part);
   return hipGetLastError();
@@ -1592,7 +1575,7 @@ __device__ __forceinline__ void no_rows(DevState* ds) {
 // tree_off: exclusive prefix of the node counts, level by level, then of the
 // group counts; total: nodes and groups together.
 __global__ __launch_bounds__(256) void k_tree_emit(
-    const uint64_t* __restrict__ keys, int n, int n_group, const uint8_t* __restrict__ dlev,
+    const uint64_t* __restrict__ keys, int n, const uint8_t* __restrict__ dlev,
     const uint8_t* __restrict__ lleaf, const uint8_t* __restrict__ gsize,
     const uint8_t* __restrict__ gstart, const uint32_t* __restrict__ tree_off,
     const uint32_t* __restrict__ total, int nblk, int64_t node_cap,
@@ -2112,7 +2095,7 @@ struct TileOf {
 // global memory (`spill`, kSpill entries per level; search regions much
 // larger than the local particle spacing need it).  Returns false on
 // frontier overflow.
-template <bool WHOLE = true, int FC, typename RadiusFn, typename FlushFn>
+template <int FC, typename RadiusFn, typename FlushFn>
 __device__ bool group_walk(const WalkNode* __restrict__ nodes, const GroupInfo& G,
                            const KParams& kp, WalkLds& L, int (&front)[2][FC],
                            int* __restrict__ spill, RadiusFn open_r, FlushFn flush) {
@@ -2151,8 +2134,7 @@ __device__ bool group_walk(const WalkNode* __restrict__ nodes, const GroupInfo& 
         open = box_gap2(nd, G, kp) < R * R;
         // an inner node wholly within the radius of every point of the group
         // box is taken whole, like a leaf, all of its leaves being opened
-        // (unless WHOLE is false: then only true leaves are listed)
-        inside = WHOLE && open && nd.nchild > 0 && box_far2(nd, G, kp) < R * R;
+        inside = open && nd.nchild > 0 && box_far2(nd, G, kp) < R * R;
       }
       const bool leaf = open && (nd.nchild == 0 || inside);
       const bool inner = open && nd.nchild > 0 && !inside;
@@ -2438,14 +2420,6 @@ __device__ __forceinline__ T kdf(T q) {
     const T t = a > T(0) ? a : T(0), s = b > T(0) ? b : T(0);
     return fma(T(3) * s, s, T(-0.75) * (t * t));
   }
-}
-
-// Nearest periodic image of a separation d (|d| < L) of the mixed-precision
-// pair loops, in three FP64 operations: d - L rint(d / L) (lp = L, ilp = 1/L
-// on periodic axes, 0 on open ones).  It agrees with fold() except within a
-// rounding of |d| = L/2, far outside any support (S h < L/2).
-__device__ __forceinline__ double fold_r(double d, double lp, double ilp) {
-  return fma(-lp, rint(d * ilp), d);
 }
 
 // The exact FP64 pair predicate of both precisions: r^2 = fma(dz, dz,
@@ -4796,7 +4770,7 @@ static SortWs sort_ws(sph_ctx* c) {
 // holds 2^-6 particles on average (the key bits of an axis shorter than the
 // longest do not vary at the top and do not count), so that denser regions
 // keep runs of a few particles.  Sort (all its launches) of 32^3 particles in
-// a cube 45 us, of 294,912 in a box of 16:1:1 94, of 16.8M in a cube 983 with
+// a cube 40 us, of 294,912 in a box of 16:1:1 90, of 16.8M in a cube 983 with
 // the 3, 5 and 4 passes this gives; 77, 119 and 1750 with all eight.
 static int sort_passes(const sph_ctx* c) {
   int want = 6;
@@ -4922,10 +4896,10 @@ hipError_t launch_tree(sph_ctx* c) {
                      c->kp.n_leaf, c->kp.n_group, c->dlev, c->lleaf, c->gsize, c->gstart,
                      c->tree_cnt, nblk, c->node_nchild, c->node_cap);
   const int64_t counts = ((int64_t)(kLevels + 1) * nblk + 3) / 4 * 4;
-  const hipError_t e = scan_u32(c, c->tree_cnt, counts, c->scan_total, nullptr);
+  const hipError_t e = scan_u32(c, c->tree_cnt, counts, c->scan_total);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_tree_emit, dim3(nblk), dim3(256), 0, c->stream, c->keys[0], n,
-                     c->kp.n_group, c->dlev, c->lleaf, c->gsize, c->gstart, c->tree_cnt,
+                     c->dlev, c->lleaf, c->gsize, c->gstart, c->tree_cnt,
                      c->scan_total, nblk, c->node_cap, c->node_level, c->node_first,
                      c->node_count, c->node_parent, c->node_child, c->node_nchild,
                      c->grp_first, c->grp_count, c->nl_len, c->grp_of, c->gflag, c->ds);
