@@ -3296,7 +3296,6 @@ __device__ __forceinline__ GroupRange xcd_items(int n) {
 constexpr int kSGLShift = 3;
 constexpr int kSGL = 1 << kSGLShift;  // groups per super-group of the list kernels
 constexpr int kSLCapL = 512;  // leaves a list-kernel walk may collect (trees of small leaves: more)
-constexpr int kOwnParticles = 16384;  // particles that the leaves of a single group's list may hold
 constexpr int kLeafPart = 64; // particles per leaf-list entry at most (>= the largest n_leaf)
 constexpr int kRowWaves = 8;  // wavefronts per SIMD of k_rows
 constexpr int kNoLeaves = -0x7fffffff;  // ll_cnt of a group whose walk failed
@@ -3501,9 +3500,9 @@ void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
       int a1 = ahead ? min(__builtin_ctzll(ahead), ngs) : ngs;
       // The part [a0, a1) into the unit's list, halved until it fits (kUnit);
       // a single group that still does not fit counts its leaves (kCount) and
-      // then writes them to space taken from the pool (kPool); leaves of far
-      // more particles than its rows can take make it a case for the walking
-      // kernels.
+      // then writes them to space taken from the pool (kPool); more than
+      // 512 leaves (1024 small ones) make it a case for the walking kernels: at
+      // 24^3 particles, one per leaf and Wendland C6, some groups reach 690.
       enum { kUnit, kCount, kPool };
       int mode = kUnit, off = 0, room = cap - used;
       int2* __restrict__ list = sg_list + base + used;
@@ -3620,7 +3619,7 @@ void k_leaves(KParams kp, const WalkNode* __restrict__ nodes,
             a1 = a0 + (a1 - a0) / 2;
           } else {
             mode = kCount;
-            room = max(kSLCapL, kOwnParticles / kp.n_leaf);
+            room = kp.n_leaf < 8 ? 2 * kSLCapL : kSLCapL;
           }
           continue;
         }
