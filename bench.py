@@ -88,8 +88,8 @@ def workload(name: str):
 
 
 # phase events (HIP events at every phase boundary of sph_step) are recorded on
-# one timed step in TIMING_EVERY: each recorded boundary idles the GPU for a
-# few microseconds, which sampling keeps out of the throughput
+# one timed step in TIMING_EVERY: a stamp costs a fraction of a microsecond per
+# phase, which sampling keeps out of the throughput
 TIMING_EVERY = 8
 
 

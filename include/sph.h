@@ -229,20 +229,24 @@ sph_status sph_neighbours(sph_ctx* ctx, const sph_particles* p, int32_t mode, in
    rebuilt at the current h; particles still flagged went through the walking
    kernels, and the sets then come from the group walk with the same exact
    predicate (as sph_neighbours).  Needs n_group 4 or 8 and a density pass on
-   the current tree.  Errors: SPH_E_ARG, SPH_E_HIP. */
+   the current tree.  Errors: SPH_E_ARG, SPH_E_OVERFLOW (the tree did not fit
+   its node arrays), SPH_E_HIP. */
 sph_status sph_list_pairs(sph_ctx* ctx, const sph_particles* p, int32_t mode, int64_t* offsets,
                           int32_t* idx, int64_t cap);
 
 /* Mean duration of the launches of each phase since the previous call, in
    milliseconds, from HIP events that the last kernel before and the last
    kernel of each phase stamp when they complete (so a phase holds the gap
-   before its first kernel; at most 1024 launches per phase are kept): out[0..11] = {keys+sort,
-   permute, tree, density, force, integrate, total step, neighbour lists,
-   density of flagged groups, force of flagged groups, adjoint kernels of
-   sph_eval_adjoint / sph_step_adjoint, the force-adjoint kernel alone}.
-   The density, force, integrate, neighbour-list, flagged-group and
-   force-adjoint phases each bracket exactly one kernel.  Clears the kept
-   events.  Synchronises. */
+   before its first kernel; at most 1024 launches per phase are kept):
+   out[0..11] = {keys+sort, permute, tree, density, force, integrate, total
+   step, neighbour lists, density of flagged groups, force of flagged groups,
+   adjoint kernels of sph_eval_adjoint / sph_step_adjoint, the force-adjoint
+   kernel alone}.  The density, force, integrate, flagged-group and
+   force-adjoint phases each bracket exactly one kernel, the neighbour lists
+   two (leaf walks, rows).  The total step runs from the end of the step's
+   first kernel (which clears the counters and takes dt, 3 to 4 us) to the end
+   of the corrector, in sph_step_adjoint to the end of the force.  Clears the
+   kept events.  Synchronises. */
 sph_status sph_timings(sph_ctx* ctx, double out[12]);
 
 /* Which calls record the phase events of sph_timings: sph_step records them
@@ -304,7 +308,8 @@ typedef struct {
    adjoint call on a context allocates its adjoint workspace (about 100 bytes
    per particle of n_max); later calls allocate nothing.
    Errors: SPH_E_ARG, SPH_E_NOMEM (workspace), SPH_E_OVERFLOW (a neighbour row
-   cannot hold all neighbours), SPH_E_HIP. */
+   cannot hold all neighbours, or the tree did not fit its node arrays),
+   SPH_E_HIP. */
 sph_status sph_eval_adjoint(sph_ctx* ctx, const sph_particles* p, sph_cotangents* g);
 
 /* Adjoint of one leapfrog step.  p must hold the state at the START of the
