@@ -21,7 +21,7 @@ constexpr int kLeafWaves = 6;   // wavefronts per SIMD of the list kernels' tree
 // Wavefronts of that walk: as many as are resident at once.
 inline int leaf_walk_waves(int n_cu) { return kLeafWaves * 4 * n_cu / 8 * 8; }
 // Leaf-list space, in units of 16 entries per particle.  A tree of leaves of
-// up to 8 particles can have one leaf per particle (a cell of 2^3 lattice
+// up to 7 particles can have one leaf per particle (a cell of 2^3 lattice
 // sites splits into eight leaves at n_leaf 7), and eight groups then reach
 // some 1000 leaves: with the space and the limit of larger leaves a third of
 // the groups of 64^3 particles (M6, Wendland C6) had no list.

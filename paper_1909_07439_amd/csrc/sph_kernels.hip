@@ -606,7 +606,9 @@ __global__ __launch_bounds__(256) void k_radix_pass(const uint64_t* __restrict__
 // kRunMax keys: every key counts the keys of its run that go before it.
 // Other blocks read the keys that a block moves only for their sorted bits,
 // which the moves keep.  Longer runs are listed and, if one is out of order,
-// left to k_resort.  TILE: 2048 keys, or 512 where 2048 would leave CUs idle.
+// left to k_resort.  TILE: 512 keys as long as a CU gets few tiles (8.5 against
+// 4.3 us with 2048 and 512 at 30,000 particles, 8.6 against 6.0 at 10^6), 2048
+// beyond (10.9 against 14.2 at 4 10^6: the halos).
 // Bound by one read of the keys: runs are found from one bit
 // per key (followed key by key, runs of clustered particles took 20 to 100 us).
 constexpr int kRunMax = 64;
@@ -924,17 +926,19 @@ __device__ __forceinline__ void sort_run(RunLds& L, uint64_t* __restrict__ keys,
 // the stage before its own to end: those items belong to blocks that already
 // run, so the wait ends however many blocks are resident.
 // Sort (all its launches) in random order: 30,000 particles of a Plummer sphere
-// of 1/100 of the box 62 us, 10^6 189 (eight passes over everything: 80 and 236;
-// uniform: 44 and 146); a body of 1/1000 of the box, its runs longer than
-// kRunBlock from 33,000 particles on: 10^5 119 us, 10^6 266, 4 10^6 626 (91, 237,
+// of 1/100 of the box 62 us, 10^6 168 (eight passes over everything: 80 and 236;
+// uniform: 44 and 144); a body of 1/1000 of the box, its runs longer than
+// kRunBlock from 33,000 particles on: 10^5 116 us, 10^6 267, 4 10^6 628 (91, 237,
 // 546).
 //
 // Between stages data passes from one XCD's L2 to another's.  All of it is
 // stored and loaded past them (tile_store, tile_load): a release and an acquire
-// fence for every tile, each of which goes over an L2, took 60 us of a pass over
-// 10^6 particles that takes 25 in launches of its own.
+// fence for every tile, each of which goes over an L2, took 15 us of a stage at
+// 10^6 particles when one wavefront of a block made them, some 80 when all four
+// did.  A stage there takes 18 us, a pass in a launch of its own 25.
+//
 // The last item of a stage tells the blocks that wait, by words of their own:
-// polls of the counter itself hold up the additions to it (75 us a stage).
+// polls of the counter itself hold up the additions to it (40 us a stage).
 __device__ __forceinline__ void stage_end(SortHead* head, const RunWs& ws, int stage, int items) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's stores are done
   __syncthreads();
@@ -4826,13 +4830,15 @@ hipError_t launch_sort(sph_ctx* c) {
   }
   // the permute's staging space is free during the sort
   const RunWs ws(reinterpret_cast<uint32_t*>(c->gtmp), n);
-  if (nblk < c->n_cu)
+  if (nblk < 4 * c->n_cu)
     hipLaunchKernelGGL(k_sort_fix<512>, dim3((n + 511) / 512), dim3(256), 0, c->stream, c->keys[0],
                        c->vals[0], n, ws, w.head);
   else
     hipLaunchKernelGGL(k_sort_fix<kSortTile>, dim3(nblk), dim3(256), 0, c->stream, c->keys[0],
                        c->vals[0], n, ws, w.head);
   // enough blocks for many runs at once, few enough to end quickly without one
+  // (30,000 particles: 15 blocks 1.6 us without a run and 64 with a cluster's,
+  // 128 blocks 1.7 and 9, 462 blocks 3.0)
   const int blocks = n > (1 << 17) ? 3 * c->n_cu : std::max(nblk + nblk / 2, c->n_cu / 2);
   launch_last(c, k_resort, dim3(std::min(blocks, 3 * c->n_cu)), dim3(256), c->keys[0], c->vals[0],
               c->keys[1], c->vals[1], n, w.status, ws, w.head, &c->ds->err);
